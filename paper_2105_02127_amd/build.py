@@ -14,10 +14,13 @@ ARCH = os.environ.get("TENO_OFFLOAD_ARCH", "gfx950")
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-pthread", "-ffp-contract=off", "-fno-fast-math",
               "-Wall", "-Wextra", "-Wno-unused-parameter"]
 # Packed FP32 instructions are disabled; FP64 kernels may contract to FMA.
+# MachineLICM is off: it lifts the constant tables of the persistent kernels out
+# of their item loops and spills them (160-400 scalar registers at order 5).
 # Code object v5 loads on both the system HIP runtime and the one bundled with
 # the PyTorch wheel.
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-mcode-object-version=5",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-mllvm", "-disable-machine-licm",
              "-Wall", "-Wno-unused-parameter", "-Wno-unused-result"]
 
 

@@ -36,13 +36,63 @@ struct Dims {
 
 Dims dims_for(int order, int nq_req, bool dense);
 
-// Largest number of distinct stencil members a 16-cell tile may have (their
-// states are staged in LDS, 32 bytes each).
+// Largest number of distinct stencil members that 16 consecutive cells of the
+// internal order may have.
 constexpr int kMaxTileMembers = 384;
 static_assert(kMaxTileMembers <= 512, "member slots take 9 bits of the adjoint's slot word");
 
 constexpr int kSmallRows = 11;
 constexpr int kSmallCoef = 5;
+
+// ---- matrix-free least squares (device layouts) ---------------------------
+// Cells are packed in an order of their own, recursive bisection of the
+// centroids into blocks of several tiles and into tiles of 16 (the Morton
+// order's runs are compact only where they fall on its quadrants); this
+// section's arrays and the adjoint's lists are in packed order.  A block stages
+// the distinct members of all its cells' stencils in LDS: per member a geometry
+// record and its state.  A record holds, in the block's frame: the centroid (x, y), the weight |V|^2 of the
+// member's row, and the central moments E[H_a(X) H_b(Y)], 2 <= a + b <= r, in
+// the basis order (xx, xy, yy, xxx, ...).  H_n is the monic Hermite polynomial
+// of variance kHermite; being an Appell sequence it shifts by the binomial
+// rule that monomials obey, so the rows of an almost orthogonal basis cost
+// what monomial rows cost.  A stencil's basis is centred on the mean of its
+// members (its centre, exact in FP32).  Records are stored with the stride they
+// have in LDS, an odd number of 16-byte units, so that they start on different
+// banks and the copy to LDS is a plain one.
+constexpr double kHermite = 0.4;  // the frame has unit variance over a stencil
+constexpr int rec_units(int nu) { return ((nu + 2) / 2) | 1; }  // nu + 1 doubles
+// LDS of one staged block: states (32 B each), records.
+constexpr int block_lds_bytes(int nu, int members) { return members * (16 * rec_units(nu) + 32); }
+// A workgroup holds two of them (one when they do not fit), and two lists of
+// member ids (padded to whole wavefront loads).
+constexpr int ids_bytes(int members) { return (members + 63) / 64 * 256; }
+constexpr int group_lds_bytes(int nu, int members, int buffers) {
+  return buffers * (block_lds_bytes(nu, members) + ids_bytes(members));
+}
+constexpr int kLdsPerCu = 160 * 1024;
+// Tiles (wavefronts) per block: workgroups of four, two or more to a CU, at
+// orders 3 and 4; at orders 5 and 6, whose records are longer and whose
+// registers allow two wavefronts per SIMD, one of eight, whose cells share more
+// members.
+constexpr int block_tiles(int order) { return order >= 5 ? 8 : 4; }
+constexpr int kMaxBlockTiles = 8;
+// LDS a workgroup of w tiles may take to keep eight wavefronts on a CU
+constexpr int lds_budget(int w) { return w >= 8 ? kLdsPerCu : kLdsPerCu / 8 * w; }
+// Packed symmetric inverses of the normal matrices of a cell's stencils: three
+// small ones (degree 2), then the large one, each its upper triangle row by
+// row in 16-byte pairs.  Lane g of a cell loads pairs 4q + g, so a tile holds
+// [q][64 lanes][2]; a stencil is padded to whole groups of four pairs.
+constexpr int sym_quads(int n) { return ((n * (n + 1) / 2 + 1) / 2 + 3) / 4; }
+constexpr int normal_quads(int nu) { return 3 * sym_quads(kSmallCoef) + sym_quads(nu); }
+// Row slots of a tile: lane g of a cell owns rows 4j + g of each stencil; its
+// member slots, ten bits each, three to a word, stencil by stencil and j by j,
+// in words [word][64 lanes].  Lanes without a row name their own cell
+// (difference 0).
+constexpr int kSlotBits = 10;
+constexpr int row_groups(int nrow) { return (nrow + 3) / 4; }
+constexpr int lane_groups(int nl) { return 3 * row_groups(kSmallRows) + row_groups(nl); }
+constexpr int slot_words(int nl) { return (lane_groups(nl) + 2) / 3; }
+constexpr int adj_words(int nl) { return (lane_groups(nl) + 1) / 2; }  // 16 bits each
 
 void set_error(const std::string& msg);
 int fail(int code, const std::string& msg);
@@ -74,12 +124,10 @@ struct Mesh {
   // ---- packed device images, internal order, tile-major ----
   int n_pad = 0, n_tiles = 0;
   std::vector<int32_t> idx;     // [n_tiles][rows4][16][4] stencil members (internal; host)
-  // distinct stencil members of each tile, staged in LDS by the kernel
+  // distinct stencil members of each tile (the adjoint's accumulators)
   int ustride = 0;              // list length per tile (largest count, rounded up)
   std::vector<int32_t> tmem;    // [n_tiles][ustride] sorted, padded with the last
   std::vector<int32_t> tcount;  // [n_tiles] distinct members of each tile (unpadded)
-  std::vector<uint16_t> slot;   // [n_tiles][rows4][16][4] position of each member in its
-                                // tile's list (packed like idx)
   std::vector<double> M;        // [n_tiles][Jp/2][kTile][2] operator entries (pairs)
   std::vector<int32_t> nbinfo;  // [n_pad][4]: 3 neighbours + packed edge/side bits
   std::vector<double> geo;      // [n_pad][10]: (nx, ny, len) x 3 edges, area
@@ -92,11 +140,23 @@ struct Mesh {
   std::vector<int32_t> cell_faces;  // [n_pad][4]: sorted face of local edges 0..2;
                                     //   bit e of [3] set when the cell is that face's L
   std::vector<double> vol;          // [n_pad] |V| (1 for padding cells)
-  // adjoint accumulation order: aslot[tile][rows4][16][4] = slot | round << 9,
-  // where round = how many earlier cells of the tile name the same member
-  // in that row; tround[tile] = the tile's largest round plus one
-  std::vector<uint16_t> aslot;
-  std::vector<int32_t> tround;
+  // matrix-free least squares: blocks of bwaves tiles, nbuf of them in LDS
+  int bwaves = 0, nbuf = 2;
+  int bmax = 0;                    // largest member count of a block
+  std::vector<int32_t> pack;       // [n_pad] internal cell of each packed position, -1: none
+  std::vector<int32_t> boff;       // [n_blocks + 1] first member of a block
+  std::vector<int32_t> bmem;       // [n_blocks][bmax] member cells (internal), the block's own
+                                   // first; rest 0: read at once, without boff
+  std::vector<double> brec;        // geometry records, rec_units units each
+  std::vector<uint32_t> bslot;     // [n_tiles][slot_words][64]
+  std::vector<double> N;           // [n_tiles][normal_quads][64][2]
+  std::vector<double> jac;         // [n_pad][4]: a third of the map's columns, block frame
+  std::vector<float> centre;       // [n_pad][4][2]: centre of each stencil's basis, block
+                                   // frame, relative to the cell
+  // adjoint accumulation order, by lane and row group as bslot, 16 bits each,
+  // [n_tiles][adj_words][64]: slot in the tile's list | round << 9, where
+  // round = how many earlier lanes of the row group name the same member
+  std::vector<uint32_t> aslot;
   // reverse member lists (adjoint gather): the tile member slots naming cell j
   std::vector<int32_t> rev_ptr; // [n_cell + 1]
   std::vector<int32_t> rev_ent; // tile * ustride + slot, by tile

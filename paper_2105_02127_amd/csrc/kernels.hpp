@@ -1,18 +1,13 @@
 // HIP kernels of the TENO residual for gfx950 (MI355X), FP64.
 //
-//   k_reconstruct  one 64-lane wavefront per tile of 16 cells, four lanes per
-//                  cell.  Least-squares phase (Sec. 2.2 eqs. 08-10): the four
-//                  lanes split the coefficient index (lane g owns l = g,
-//                  g+4, ...) and carry all four conservative variables, so
-//                  every operator entry is loaded by exactly one lane and a
-//                  wavefront load moves 512 contiguous bytes; stencil
-//                  differences are gathered one variable per lane and shared
-//                  by DPP quad broadcasts.  Selection phase: DPP quad
-//                  transposes give lane g the full coefficient vector of
-//                  variable g, which then forms the smoothness indicators
-//                  (Sec. 2.3), the strong scale separation and the two-step
-//                  ENO-like selection (Sec. 3.2-3.3), and the face
-//                  Gauss-point states, written once.
+//   k_reconstruct  blocks of four wavefronts, one tile of 16 cells each, four
+//                  lanes per cell.  Least-squares phase (Sec. 2.2 eqs. 08-10)
+//                  without stored operators (below).  Selection phase: lane g
+//                  holds the full coefficient vectors of variable g, forms the
+//                  smoothness indicators (Sec. 2.3), the strong scale
+//                  separation and the two-step ENO-like selection
+//                  (Sec. 3.2-3.3), and the face Gauss-point states, written
+//                  once.
 //  k_face_flux     one lane per face: rotated HLL flux with Einfeldt/Roe wave
 //                  speeds (Sec. 4) at the face's Gauss point pairs and the
 //                  face quadrature, written once per face.
@@ -54,13 +49,6 @@ __device__ __forceinline__ int xcd_remap(int b, int nblk) {
 // ---------------------------------------------------------------------------
 // Euler helpers
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool physical(double r, double mx, double my, double e, double g) {
-  if (isnan(r) || isnan(mx) || isnan(my) || isnan(e)) return false;
-  if (!(r > 0.0)) return false;
-  const double p = (g - 1.0) * (e - 0.5 * (mx * mx + my * my) / r);
-  return p > 0.0;
-}
-
 // HLL flux through unit normal (nx, ny): rotate into the face frame, HLL with
 // S_L = min(u_L - c_L, u~ - c~), S_R = max(u_R + c_R, u~ + c~) from Roe
 // averages (both velocity components in c~), rotate back.  The quotients
@@ -251,15 +239,543 @@ __device__ __forceinline__ void hll_vjp(const double uL[4], const double uR[4], 
 }
 
 // ---------------------------------------------------------------------------
+// Least-squares phase (Sec. 2.2 eqs. 08-10), without stored operators.
+//
+// With rows A_s (moments of member s about the target, zero mean over it) and
+// weights w_s = |V_s|^2, the coefficients of one stencil are
+//   a = N sum_s w_s A_s (U_s - U_0),   N = (sum_s w_s A_s A_s^T)^-1.
+// Stored operators a = M d are n_u x n_l doubles per cell and stage (4.6 KB at
+// order 5) and bound this kernel to HBM: 461 us per launch on 524,288 cells at
+// order 5 (5.7 TB/s).  N is symmetric (1.2 KB), and A_s follows from the
+// member's own central moments by a Taylor shift, a few multiply-adds per entry
+// from a record that the whole block shares: 310 us, bound by FP64 issue (65-73%
+// of the cycles) with memory at 3.5 TB/s.  At orders 3, 4, 6 (180,000 cells):
+// 73, 105, 270 us stored, 49, 69, 178 us like this.
+//
+// Precision: the normal matrix squares the condition of A, so the basis is
+// chosen to keep that small: moments in a frame that gives the block's
+// displacements unit variance, of Hermite polynomials (they shift by the same
+// binomial rule as monomials), about the mean of each stencil's members; N is
+// formed and inverted in extended precision.  Against 128 bits the face values
+// are closer than the stored operators' (rms error 0.44, 0.13, 0.07, 0.02 of
+// theirs at orders 3-6 on jittered meshes).
+//
+// A block of wavefronts (16 cells each, four lanes per cell) stages the distinct
+// members of all its stencils in LDS: about 190 records and states for four
+// wavefronts and 300 for eight, 2.3 to 3 per cell, where one wavefront alone
+// would stage 7.  Lane g of a cell owns rows 4j + g of each stencil and adds
+// them for all four variables.  Its accumulators and differences are ordered by
+// i = v xor g, so that the sum over the cell's four lanes hands lane g variable
+// g by three DPP exchanges of whole registers, without selects.  The sum's order
+// is fixed: results do not depend on timing.
+// ---------------------------------------------------------------------------
+struct BlockArgs {
+  const int* __restrict__ boff;        // [n_blocks + 1] first member of a block
+  const int* __restrict__ bmem;        // [block][mstride] member cells, the block's own first
+  const double2* __restrict__ brec;    // geometry records (internal.h)
+  const unsigned* __restrict__ bslot;  // [n_tiles][slot_words][64] row slots
+  const double2* __restrict__ N;       // [n_tiles][normal_quads][64]
+  const double2* __restrict__ jac;     // [n_pad][2]
+  const float2* __restrict__ centre;   // [n_pad][4] centre of each stencil's basis
+  const int* __restrict__ pack;        // [n_pad] cell of each packed position, -1: none
+  int bwaves;                          // wavefronts (tiles) per block
+  int mstride;                         // members of the mesh's largest block
+  int bmax;                            // of all the launch's meshes: lays out the LDS
+  int nbuf;                            // staged blocks in LDS (2 or 1)
+};
+
+// Arguments in constant memory (a kernel's own, or a batch's descriptors):
+// fields are loaded through the scalar cache where they are used.
+#define TENO_CONST const __attribute__((address_space(4)))
+
+// LDS of a reconstruction workgroup: nbuf staged blocks (states at 0, records
+// at 32 bmax), then nbuf lists of member ids.
+__device__ __forceinline__ unsigned buf_offset(TENO_CONST BlockArgs& b, int nu, int k) {
+  return (b.nbuf == 2 ? k & 1 : 0) * block_lds_bytes(nu, b.bmax);
+}
+__device__ __forceinline__ unsigned ids_offset(TENO_CONST BlockArgs& b, int nu, int k) {
+  return b.nbuf * block_lds_bytes(nu, b.bmax) + (b.nbuf == 2 ? k & 1 : 0) * ids_bytes(b.bmax);
+}
+
+// Copies from memory straight to LDS (no registers): lane l's 16 (or 4) bytes
+// go to lds + 16 l (4 l); lds is uniform.  The copies are counted with the
+// wavefront's other memory operations and are complete after lds_copy_wait.
+// In assembly, because the compiler waits for such a copy before any later LDS
+// read; nothing is returned in a register.
+__device__ __forceinline__ void lds_copy16(const void* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(lds), "v"(src) : "memory");
+}
+__device__ __forceinline__ void lds_copy4(const void* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+               :: "s"(lds), "v"(src) : "memory");
+}
+// A uniform load through the scalar cache (of data that no kernel writes); the
+// copies' memory clobbers would otherwise turn it into a vector load.
+__device__ __forceinline__ int scalar_load(const int* p, int i) {
+  return ((const __attribute__((address_space(4))) int*)(uintptr_t)p)[i];
+}
+__device__ __forceinline__ void lds_copy_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+template <int K>
+__device__ __forceinline__ double quad_perm_dpp(double x) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), K, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), K, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Broadcast lane K of every group of four lanes (DPP quad permutation).
+template <int K>
+__device__ __forceinline__ double quad_bcast(double x) {
+  constexpr int ctrl = K * 0x55;  // quad_perm(K, K, K, K)
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ctrl, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ctrl, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+
+// x of lane g ^ I of the quad
+template <int I>
+__device__ __forceinline__ double quad_xor(double x) {
+  if constexpr (I == 0) return x;
+  else return quad_perm_dpp<I == 1 ? 0xB1 : (I == 2 ? 0x4E : 0x1B)>(x);
+}
+
+// Sum over the cell's four lanes of variable g, from sums x[i] of variable
+// i ^ g.  Called with all four lanes active.
+__device__ __forceinline__ double quad_sum(const double (&x)[4]) {
+  return (x[0] + quad_xor<1>(x[1])) + (quad_xor<2>(x[2]) + quad_xor<3>(x[3]));
+}
+
+// A constant table behind an opaque pointer: its entries come through the
+// scalar cache where they are used, instead of as literals that the compiler
+// collects in scalar registers for all their uses and spills.
+__device__ __forceinline__ TENO_CONST double* table(const double* p) {
+  auto q = (TENO_CONST double*)(uintptr_t)p;
+  asm volatile("" : "+s"(q));
+  return q;
+}
+
+__device__ __forceinline__ void opaque(double& x) { asm volatile("" : "+v"(x)); }
+
+// Index of X^(d-k) Y^k in the graded basis.
+constexpr int mono(int d, int k) { return d * (d + 1) / 2 - 1 + k; }
+
+// Starts the copies of block blk's records (to rec), and of its members' states
+// (to st), whose ids are at mem, by nthr threads.
+template <int NU>
+__device__ __forceinline__ void copy_records(TENO_CONST BlockArgs& b, int blk, unsigned rec, int nthr) {
+  constexpr int RU = rec_units(NU);
+  const int m0 = scalar_load(b.boff, blk), n = (scalar_load(b.boff, blk + 1) - m0) * RU;
+  const char* src = reinterpret_cast<const char*>(b.brec) + (size_t)m0 * (16 * RU);
+  const unsigned w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+  for (int i = 0; i < n; i += nthr)
+    if (i + (int)threadIdx.x < n) lds_copy16(src + 16 * (i + threadIdx.x), rec + 16 * (i + w0));
+}
+__device__ __forceinline__ void copy_states(const double* __restrict__ U, const int* mem, int nm,
+                                            unsigned st, int nthr) {
+  const unsigned w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+  // ids two passes at a time: one wait for both
+  for (int i = 0; i < 2 * nm; i += 2 * nthr) {
+    const int k = i + threadIdx.x, k2 = k + nthr;
+    const int id = k < 2 * nm ? mem[k >> 1] : 0, id2 = k2 < 2 * nm ? mem[k2 >> 1] : 0;
+    if (k < 2 * nm) lds_copy16(U + (size_t)id * 4 + (k & 1) * 2, st + 16 * (i + w0));
+    if (k2 < 2 * nm) lds_copy16(U + (size_t)id2 * 4 + (k & 1) * 2, st + 16 * (i + nthr + w0));
+  }
+}
+__device__ __forceinline__ void copy_ids(TENO_CONST BlockArgs& b, int blk, unsigned ids, int nthr) {
+  const int nm = scalar_load(b.boff, blk + 1) - scalar_load(b.boff, blk);
+  const int* __restrict__ mem = b.bmem + (size_t)blk * b.mstride;
+  const unsigned w0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+  for (int i = 0; i < nm; i += nthr)
+    if (i + (int)threadIdx.x < nm) lds_copy4(mem + i + threadIdx.x, ids + 4 * (i + w0));
+}
+
+// The lane's row slots: NG groups, BITS bits each, packed in words [word][64].
+template <int NG, int BITS>
+struct RowSlots {
+  static constexpr int PER = 32 / BITS, NW = (NG + PER - 1) / PER;
+  unsigned w[NW];
+  __device__ __forceinline__ void load(const unsigned* __restrict__ p, int tile, int lane) {
+    const unsigned* __restrict__ t = p + (size_t)tile * (NW * 64);  // uniform
+    static_for<0, NW>([&](auto k) { w[k] = t[k * 64 + (unsigned)lane]; });
+  }
+  template <int G>
+  __device__ __forceinline__ unsigned get() const {
+    return (w[G / PER] >> (BITS * (G % PER))) & ((1u << BITS) - 1);
+  }
+};
+template <int NL>
+using MemberSlots = RowSlots<lane_groups(NL), kSlotBits>;
+
+// Moments E[H_a(x + X) H_b(y + Y)], 1 <= a + b <= R, from central moments mu
+// (the record's order): a binomial shift along x, then along y.
+template <int R>
+__device__ __forceinline__ void shift_moments(double x, double y, const double* mu, double* out) {
+  double t[R + 1][R + 1];
+  static_for<0, R + 1>([&](auto bc) {
+    constexpr int b = bc, n = R - b;
+    double v[n + 1];
+    static_for<0, n + 1>([&](auto ac) {
+      constexpr int a = ac;
+      if constexpr (a + b >= 2) v[a] = mu[mono(a + b, b) - 2];
+    });
+    // first pass, with mu_00 = 1 and mu_10 = mu_01 = 0 folded in
+    constexpr int first = b == 0 ? 3 : (b == 1 ? 2 : 1);
+    static_for<0, n + 1>([&](auto ac) {
+      constexpr int a = n - ac;
+      if constexpr (a >= first) v[a] = fma(x, v[a - 1], v[a]);
+    });
+    if constexpr (b == 0) v[1] = x;
+    static_for<2, n + 1>([&](auto ic) {
+      constexpr int i = ic;
+      static_for<0, n + 1 - i>([&](auto ac) {
+        constexpr int a = n - ac;
+        v[a] = fma(x, v[a - 1], v[a]);
+      });
+    });
+    static_for<1, n + 1>([&](auto ac) { t[ac][b] = v[ac]; });
+    if constexpr (b >= 2) t[0][b] = v[0];
+  });
+  static_for<0, R + 1>([&](auto ac) {
+    constexpr int a = ac, n = R - a;
+    double v[n + 1];
+    static_for<0, n + 1>([&](auto bc) {
+      constexpr int b = bc;
+      if constexpr (a + b >= 2 || a == 1) v[b] = t[a][b];
+    });
+    constexpr int first = a == 0 ? 3 : 1;
+    static_for<0, n + 1>([&](auto bc) {
+      constexpr int b = n - bc;
+      if constexpr (b >= first) v[b] = fma(y, v[b - 1], v[b]);
+    });
+    if constexpr (a == 0) v[1] = y;
+    static_for<2, n + 1>([&](auto ic) {
+      constexpr int i = ic;
+      static_for<0, n + 1 - i>([&](auto bc) {
+        constexpr int b = n - bc;
+        v[b] = fma(y, v[b - 1], v[b]);
+      });
+    });
+    static_for<0, n + 1>([&](auto bc) {
+      constexpr int b = bc;
+      if constexpr (a + b >= 1) out[mono(a + b, b)] = v[b];
+    });
+  });
+}
+
+// A block as one cell's lane sees it.
+struct CellView {
+  const double* us;      // LDS: member states
+  const double* geo;     // LDS: records
+  double x, y;           // the cell's centroid
+  double u0[4];          // its means, u0[i] = variable i ^ g
+  int g;
+};
+
+// c = N r of one stencil.  Each lane of a cell loads a quarter of the packed
+// triangle (a wavefront load is 1 KB, each byte once) and broadcasts its
+// entries to the quad as they are used: two DPP moves an entry, where loading
+// every entry in all four lanes took four times the loads and, with no
+// registers to hold them ahead, a round trip to memory per few entries.  Two
+// chunks of CH quads are in registers, one in flight while one is used.
+template <int N, int CH = sym_quads(N)>
+struct NormalMatrix {
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  static constexpr int NQ = sym_quads(N), NE = N * (N + 1) / 2, NC = (NQ + CH - 1) / CH;
+  v2d w[NC > 1 ? 2 : 1][CH];
+  // loads chunk K of the stencil's matrix (p: its first quad, uniform)
+  template <int K>
+  __device__ __forceinline__ void load(const double2* __restrict__ p, int lane) {
+    static_for<0, CH>([&](auto i) {
+      constexpr int q = K * CH + i;
+      if constexpr (q < NQ)
+        w[K % 2][i] =
+            __builtin_nontemporal_load(reinterpret_cast<const v2d*>(&p[q * 64 + (unsigned)lane]));
+    });
+  }
+  static constexpr int row_of(int e) {
+    int i = 0;
+    while (e >= N - i) e -= N - i++;
+    return i;
+  }
+  static constexpr int col_of(int e) {
+    int i = 0;
+    while (e >= N - i) e -= N - i++;
+    return i + e;
+  }
+  // load<0> must have been called; called with all four lanes of the cell active
+  __device__ __forceinline__ void apply(const double2* __restrict__ p, int lane, const double* r,
+                                        double* c) {
+    static_for<0, N>([&](auto l) { c[l] = 0.0; });
+    static_for<0, NC>([&](auto k) {
+      if constexpr (k + 1 < NC) {
+        load<k + 1>(p, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      static_for<0, 8 * CH>([&](auto ec) {
+        constexpr int e = 8 * CH * k + ec;
+        if constexpr (e < NE) {
+          constexpr int i = row_of(e), j = col_of(e);
+          const v2d x2 = w[k % 2][ec / 8];
+          const double x = quad_bcast<(e / 2) % 4>(e % 2 ? x2.y : x2.x);
+          c[i] = fma(x, r[j], c[i]);
+          if constexpr (i != j) c[j] = fma(x, r[i], c[j]);
+        }
+      });
+      if constexpr (k + 1 < NC) __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+};
+
+// The map from the block's frame to the basis, x = j0 X + j1 Y and
+// y = j2 X + j3 Y: forms y^k, k = 2..R, shared by the degrees.
+template <int R>
+struct Frame {
+  double j0, j1, j2, j3;
+  double yp[R + 1][R + 1];
+  __device__ __forceinline__ void init(double2 a, double2 b) {
+    j0 = a.x;
+    j1 = a.y;
+    j2 = b.x;
+    j3 = b.y;
+    yp[1][0] = j2;
+    yp[1][1] = j3;
+    static_for<2, R + 1>([&](auto kc) {
+      constexpr int k = kc;
+      yp[k][0] = j2 * yp[k - 1][0];
+      static_for<1, k>([&](auto ic) {
+        constexpr int i = ic;
+        yp[k][i] = fma(j2, yp[k - 1][i], j3 * yp[k - 1][i - 1]);
+      });
+      yp[k][k] = j3 * yp[k - 1][k - 1];
+    });
+  }
+  // coefficients of x^a y^b -> coefficients of X^a Y^b, degree by degree, in
+  // place: p_0 = c_0, p_k = p_{k-1} x + c_k y^k
+  template <int D>
+  __device__ __forceinline__ void to_basis(double* c) const {
+    static_for<1, D + 1>([&](auto dc) {
+      constexpr int d = dc;
+      double p[d + 1];
+      p[0] = c[mono(d, 0)];
+      static_for<1, d + 1>([&](auto kc) {
+        constexpr int k = kc;
+        const double ck = c[mono(d, k)];
+        p[k] = fma(ck, yp[k][k], j1 * p[k - 1]);
+        static_for<1, k>([&](auto ic) {
+          constexpr int i = k - ic;
+          p[i] = fma(ck, yp[k][i], fma(j0, p[i], j1 * p[i - 1]));
+        });
+        p[0] = fma(ck, yp[k][0], j0 * p[0]);
+      });
+      static_for<0, d + 1>([&](auto kc) { c[mono(d, kc)] = p[kc]; });
+    });
+  }
+  // its transpose (adjoints of basis coefficients -> of frame coefficients)
+  template <int D>
+  __device__ __forceinline__ void from_basis_adjoint(double* c) const {
+    static_for<1, D + 1>([&](auto dc) {
+      constexpr int d = dc;
+      double p[d + 1];
+      static_for<0, d + 1>([&](auto kc) { p[kc] = c[mono(d, kc)]; });
+      static_for<0, d>([&](auto kc) {
+        constexpr int k = d - kc;
+        double s = p[0] * yp[k][0];
+        static_for<1, k + 1>([&](auto ic) { s = fma(p[ic], yp[k][ic], s); });
+        c[mono(d, k)] = s;
+        static_for<0, k>([&](auto ic) {
+          constexpr int i = ic;
+          p[i] = fma(j0, p[i], j1 * p[i + 1]);
+        });
+      });
+      c[mono(d, 0)] = p[0];
+    });
+  }
+};
+
+// The cell's own moments about the centre (cx, cy).
+template <int R>
+__device__ __forceinline__ void own_moments(const double* own, double cx, double cy, bool shift,
+                                            double* h) {
+  constexpr int N = (R + 1) * (R + 2) / 2 - 1;
+  h[0] = h[1] = 0.0;
+  static_for<2, N>([&](auto l) { h[l] = own[l + 1]; });
+  if (shift) {
+    double t[N];
+    shift_moments<R>(-cx, -cy, h + 2, t);
+    static_for<0, N>([&](auto l) { h[l] = t[l]; });
+  }
+}
+
+// Coefficients of H_a(x - cx) H_b(y - cy) -> coefficients of x^a y^b, in place
+// (the constant is not kept): shifted to the cell's centroid, then expanded.
+template <int R>
+__device__ __forceinline__ void hermite_to_monomials(double* c, double cx, double cy, bool shift) {
+  if (shift) {
+    static_for<0, R>([&](auto bc) {
+      constexpr int b = bc, n = R - b;
+      static_for<0, n>([&](auto ic) {
+        static_for<0, n - ic>([&](auto jc) {
+          constexpr int a = n - 1 - jc;
+          if constexpr (a + b >= 1)
+            c[mono(a + b, b)] = fma(-cx, c[mono(a + 1 + b, b)], c[mono(a + b, b)]);
+        });
+      });
+    });
+    static_for<0, R>([&](auto ac) {
+      constexpr int a = ac, n = R - a;
+      static_for<0, n>([&](auto ic) {
+        static_for<0, n - ic>([&](auto jc) {
+          constexpr int b = n - 1 - jc;
+          if constexpr (a + b >= 1)
+            c[mono(a + b, b)] = fma(-cy, c[mono(a + b + 1, b + 1)], c[mono(a + b, b)]);
+        });
+      });
+    });
+  }
+  static_for<0, R>([&](auto bc) {
+    static_for<0, R + 1 - bc>([&](auto ac) {
+      constexpr int a = ac, b = bc, n = R - b;
+      if constexpr (a + b >= 1 && a + 2 <= n) {
+        double v = fma(cx_hermite(a + 2, 1), c[mono(a + 2 + b, b)], c[mono(a + b, b)]);
+        if constexpr (a + 4 <= n) v = fma(cx_hermite(a + 4, 2), c[mono(a + 4 + b, b)], v);
+        c[mono(a + b, b)] = v;
+      }
+    });
+  });
+  static_for<0, R>([&](auto ac) {
+    static_for<0, R + 1 - ac>([&](auto bc) {
+      constexpr int a = ac, b = bc, n = R - a;
+      if constexpr (a + b >= 1 && b + 2 <= n) {
+        double v = fma(cx_hermite(b + 2, 1), c[mono(a + b + 2, b + 2)], c[mono(a + b, b)]);
+        if constexpr (b + 4 <= n) v = fma(cx_hermite(b + 4, 2), c[mono(a + b + 4, b + 4)], v);
+        c[mono(a + b, b)] = v;
+      }
+    });
+  });
+}
+
+// Its transpose (adjoints of monomial coefficients -> of the stencil's).
+template <int R>
+__device__ __forceinline__ void hermite_to_monomials_adjoint(double* c, double cx, double cy,
+                                                             bool shift) {
+  static_for<0, R>([&](auto ac) {
+    static_for<0, R + 1 - ac>([&](auto jc) {
+      constexpr int a = ac, b = R - a - jc;
+      if constexpr (a + b >= 1 && b >= 2) {
+        double v = c[mono(a + b, b)];
+        if constexpr (a + b - 2 >= 1) v = fma(cx_hermite(b, 1), c[mono(a + b - 2, b - 2)], v);
+        if constexpr (b >= 4 && a + b - 4 >= 1)
+          v = fma(cx_hermite(b, 2), c[mono(a + b - 4, b - 4)], v);
+        c[mono(a + b, b)] = v;
+      }
+    });
+  });
+  static_for<0, R>([&](auto bc) {
+    static_for<0, R + 1 - bc>([&](auto jc) {
+      constexpr int b = bc, a = R - b - jc;
+      if constexpr (a + b >= 1 && a >= 2) {
+        double v = c[mono(a + b, b)];
+        if constexpr (a + b - 2 >= 1) v = fma(cx_hermite(a, 1), c[mono(a + b - 2, b)], v);
+        if constexpr (a >= 4 && a + b - 4 >= 1)
+          v = fma(cx_hermite(a, 2), c[mono(a + b - 4, b)], v);
+        c[mono(a + b, b)] = v;
+      }
+    });
+  });
+  if (shift) {
+    static_for<0, R>([&](auto ac) {
+      constexpr int a = ac, n = R - a;
+      static_for<0, n>([&](auto ic) {
+        static_for<0, ic + 1>([&](auto jc) {
+          constexpr int b = n - 1 - ic + jc;
+          if constexpr (a + b >= 1)
+            c[mono(a + b + 1, b + 1)] = fma(-cy, c[mono(a + b, b)], c[mono(a + b + 1, b + 1)]);
+        });
+      });
+    });
+    static_for<0, R>([&](auto bc) {
+      constexpr int b = bc, n = R - b;
+      static_for<0, n>([&](auto ic) {
+        static_for<0, ic + 1>([&](auto jc) {
+          constexpr int a = n - 1 - ic + jc;
+          if constexpr (a + b >= 1)
+            c[mono(a + b + 1, b)] = fma(-cx, c[mono(a + b, b)], c[mono(a + b + 1, b)]);
+        });
+      });
+    });
+  }
+}
+
+// Right-hand side of one stencil's normal equations: rhs[l] of the lane's
+// variable g.  NR rows of degree R about the centre (cx, cy), slot groups
+// G0...; the record of the cell itself is at own.  With S < R the rows are
+// read twice, for the functions of degree S and less and for the others: the
+// moments cost more, but fewer row sums are in registers at once.
+template <int R, int NR, int G0, int NU, int S, class Slots>
+__device__ __forceinline__ void stencil_sums(const CellView& cv, const Slots& slots,
+                                             const double* own, double cx, double cy, bool shift,
+                                             double* rhs) {
+  constexpr int N = (R + 1) * (R + 2) / 2 - 1;
+  constexpr int RS = 2 * rec_units(NU);
+  const double x0 = cv.x + cx, y0 = cv.y + cy;
+  double r0 = 0.0;
+  static_for<0, S < R ? 2 : 1>([&](auto pc) {
+    // degrees (D0, D1] in this pass, functions [L0, L1)
+    constexpr int D0 = pc == 0 ? 0 : S, D1 = pc == 0 && S < R ? S : R;
+    constexpr int L0 = mono(D0 + 1, 0), L1 = mono(D1, D1) + 1;
+    double acc[L1 - L0][4], acc0[4];
+    static_for<0, row_groups(NR)>([&](auto jc) {
+      unsigned m = slots.template get<G0 + jc>();
+      asm volatile("" : "+v"(m));  // each pass reads its records again
+      const double* rec = cv.geo + m * RS;
+      double q[L1 + 1], mo[L1], d[4];
+      static_for<0, L1 + 1>([&](auto l) { q[l] = rec[l]; });
+      const double* u = cv.us + m * 4;
+      static_for<0, 4>([&](auto i) { d[i] = (u[cv.g ^ i] - cv.u0[i]) * q[2]; });
+      shift_moments<D1>(q[0] - x0, q[1] - y0, q + 3, mo);
+      static_for<0, 4>([&](auto i) {
+        if constexpr (jc == 0) {
+          acc0[i] = d[i];
+          static_for<L0, L1>([&](auto l) { acc[l - L0][i] = mo[l] * d[i]; });
+        } else {
+          if constexpr (pc == 0) acc0[i] += d[i];
+          static_for<L0, L1>([&](auto l) { acc[l - L0][i] = fma(mo[l], d[i], acc[l - L0][i]); });
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);  // one group's record at a time in registers
+    });
+    // the pass ends here: an opaque use of each sum, or the compiler sinks the
+    // rows' arithmetic past what follows and holds every record till then
+    if constexpr (pc == 0) {
+      r0 = quad_sum(acc0);
+      opaque(r0);
+    }
+    static_for<L0, L1>([&](auto l) {
+      rhs[l] = quad_sum(acc[l - L0]);
+      opaque(rhs[l]);
+    });
+  });
+  // rows have zero mean over the cell: less its own moments
+  double h[N];
+  own_moments<R>(own, cx, cy, shift, h);
+  static_for<0, N>([&](auto l) { rhs[l] = fma(-h[l], r0, rhs[l]); });
+}
+
+// ---------------------------------------------------------------------------
 // reconstruction
 // ---------------------------------------------------------------------------
 struct ReconArgs {
   const double* __restrict__ U;        // [n_cell][4]
-  const int4* __restrict__ slot;       // [n_tiles][rows4][16][4] uint16, 8 per int4
-  const int* __restrict__ tmem;        // [n_tiles][ustride] distinct members of a tile
-  int ustride;                         // members per tile list
-  int lds_stride;                      // LDS per wavefront in int4 (stage_int4)
-  const double2* __restrict__ M;       // [n_tiles][JP * kTile] doubles: the tile's blocks
+  BlockArgs b;                         // stencils and least squares
   double* __restrict__ fp;             // [3 nq][n_pad][4]
   uint16_t* flags;                     // out, or in when frozen
   const int32_t* __restrict__ user_of; // [n_pad]
@@ -274,7 +790,7 @@ struct ReconArgs {
 };
 
 // chi within the near-tie window around C_T (counted, never decided on).
-__device__ __forceinline__ int near_tie(const ReconArgs& a, double chi) {
+__device__ __forceinline__ int near_tie(TENO_CONST ReconArgs& a, double chi) {
   return (chi >= a.tie_lo && chi <= a.tie_hi) ? 1 : 0;
 }
 
@@ -294,293 +810,25 @@ __device__ __forceinline__ double gamma_k(double beta, double eps, int power) {
   return 1.0 / xp;
 }
 
-template <int N>
-__device__ __forceinline__ double quad_form(const double (&B)[N][N], const double* a) {
-  double s = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) {
-    double t = 0.0;
-#pragma unroll
-    for (int m = 0; m < N; ++m) t = fma(B[l][m], a[m], t);
-    s = fma(a[l], t, s);
-  }
-  return s;
-}
-
-// The same form from U, the upper triangle of B with its off-diagonal
-// entries doubled: about half the multiply-adds, but with fewer
-// instructions between them the compiler keeps more values live.
-template <int N>
-__device__ __forceinline__ double quad_form_upper(const double (&U)[N][N], const double* a) {
-  double s = 0.0;
-#pragma unroll
-  for (int l = 0; l < N; ++l) {
-    double t = U[l][l] * a[l];
-#pragma unroll
-    for (int m = l + 1; m < N; ++m) t = fma(U[l][m], a[m], t);
-    s = fma(a[l], t, s);
-  }
-  return s;
-}
-
-// beta = a^T B a of degree R from the full table, or from its doubled upper
-// triangle (UP).
-template <int R, bool UP>
+// beta = a^T B a from U, the upper triangle of B with its off-diagonal entries
+// doubled.
+template <int R>
 __device__ __forceinline__ double smoothness(const double* a) {
-  if constexpr (UP)
-    return quad_form_upper(SmoothForm<R>::U.v, a);
-  else
-    return quad_form(SmoothForm<R>::B.v, a);
-}
-
-// Broadcast lane K of every group of four lanes (DPP quad permutation).
-template <int K>
-__device__ __forceinline__ double quad_bcast(double x) {
-  constexpr int ctrl = K * 0x55;  // quad_perm(K, K, K, K)
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ctrl, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ctrl, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
+  using S = SmoothForm<R>;
+  constexpr int N = S::N;
+  double s = 0.0;
+  static_for<0, N>([&](auto lc) {
+    constexpr int l = lc;
+    double t = S::U.v[l][l] * a[l];
+    static_for<l + 1, N>([&](auto m) { t = fma(S::U.v[l][m], a[m], t); });
+    s = fma(a[l], t, s);
+  });
+  return s;
 }
 
 __device__ __forceinline__ double pick4(double t0, double t1, double t2, double t3, int g) {
   return g == 0 ? t0 : (g == 1 ? t1 : (g == 2 ? t2 : t3));
 }
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
-// Least-squares phase (Sec. 2.2 eqs. 08-10) of one stencil as a stream of
-// its NR rows: a = M d with d_s = U_member(s) - U_0, row s of M^T stored at
-// entries J0 + s*RS .. (RS even; entries past the coefficient count are
-// zero).  Each cell has LPC = 64 / kTile lanes (g = 0..LPC-1); lane g gathers
-// variable g % 4 of the row's member, the four lanes share d for all four
-// variables by quad broadcast, and lane g adds the entry pairs p = g + LPC t
-// it owns (coefficients 2p and 2p+1, one 16-byte load each) into
-// acc[t][k][v].  Every entry is loaded by exactly one lane, and every
-// coefficient adds the rows one at a time in row order, as a plain GEMV does.
-//
-// The states of the tile's distinct stencil members and each row's slot among
-// them are staged in LDS once per tile, so the row loop's only memory loads
-// are the operator entries.  NB row buffers live in fixed registers and the row
-// loop is unrolled by NB: while one row is accumulated the next NB-1 are in
-// flight, and no register changes role between iterations (a rotating
-// buffer would force a full wait every row).  prime() issues the first
-// NB-1 rows, so a caller can start the stream before it finishes other work.
-#ifndef TENO_ROW_BUFFERS
-#define TENO_ROW_BUFFERS 3
-#endif
-#ifndef TENO_M_NONTEMPORAL
-#define TENO_M_NONTEMPORAL 1
-#endif
-
-template <int R0, int NR, int RS>
-struct RowStream {
-  static constexpr int NB = TENO_ROW_BUFFERS;
-  static constexpr int LPC = kLanesPerCell;
-  static constexpr int NPAIR = RS / 2;                // pairs per row
-  static constexpr int NT = (NPAIR + LPC - 1) / LPC;  // pair slots per lane
-  static_assert(RS % 2 == 0, "rows are whole pairs");
-  using Acc = double[NT][2][4];
-
-  const double* us;                    // LDS: states of the tile's distinct members
-  const uint16_t* sidx;                // LDS: each stencil row's member slot
-  const double2* __restrict__ mp;      // this cell's pairs of the block
-  int c, g;
-  double u0g;
-  double xq[NB];
-  double2 mq[NB][NT];
-
-  __device__ __forceinline__ void issue(int s, double& x, double2 (&m)[NT]) const {
-    s = s < NR ? s : NR - 1;  // loads past the last row re-read it (never used)
-    const int r = R0 + s;
-    const int id = sidx[(r >> 2) * (kTile * 4) + c * 4 + (r & 3)];
-    x = us[id * 4 + (g & 3)];
-    const double2* __restrict__ mr = mp + (size_t)(s * RS / 2) * kTile;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      // Lanes past the row's last pair re-read that pair: the load stays
-      // unconditional (a predicated load merged with a zero would make the
-      // compiler copy the buffers and wait for every load at the back edge),
-      // and the accumulators it feeds are never read.
-      const int pr = (LPC * t + LPC - 1 < NPAIR) ? g + LPC * t : min(g + LPC * t, NPAIR - 1);
-#if TENO_M_NONTEMPORAL
-      // operator entries are read once per stage: keep them out of the way
-      // of the gathered states in the caches
-      typedef double v2d __attribute__((ext_vector_type(2)));
-      const v2d w = __builtin_nontemporal_load(reinterpret_cast<const v2d*>(&mr[(size_t)pr * kTile]));
-      m[t] = make_double2(w.x, w.y);
-#else
-      m[t] = mr[(size_t)pr * kTile];
-#endif
-    }
-  }
-
-  __device__ __forceinline__ void accumulate(double xv, const double2 (&m)[NT], Acc& acc) const {
-    const double x = xv - u0g;
-    const double d[4] = {quad_bcast<0>(x), quad_bcast<1>(x), quad_bcast<2>(x), quad_bcast<3>(x)};
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc[t][0][q] = fma(m[t].x, d[q], acc[t][0][q]);
-        acc[t][1][q] = fma(m[t].y, d[q], acc[t][1][q]);
-      }
-  }
-
-  __device__ __forceinline__ void prime() {
-    static_for<0, NB - 1>([&](auto k) { issue(k, xq[k], mq[k]); });
-  }
-
-  // All rows into acc; prime() must have been called.
-  __device__ __forceinline__ void run(Acc& acc) {
-    int s = 0;
-#pragma unroll 1
-    for (; s + NB - 1 < NR; s += NB) {
-      static_for<0, NB>([&](auto k) {
-        constexpr int nb = (k + NB - 1) % NB;
-        issue(s + k + NB - 1, xq[nb], mq[nb]);
-        accumulate(xq[k], mq[k], acc);
-      });
-    }
-    static_for<0, NB - 1>([&](auto k) {
-      if (s + k < NR) accumulate(xq[k], mq[k], acc);
-    });
-  }
-
-  // Coefficient l (variable v): pair l/2 is held by lane (l/2) % LPC of the
-  // cell's lane group in slot (l/2) / LPC, component l % 2.
-  template <int l>
-  __device__ __forceinline__ static double coef(const Acc& acc, int v, int lane) {
-    constexpr int src = (l / 2) % LPC, t = (l / 2) / LPC, k = l % 2;
-    if constexpr (LPC == 4) {
-      return pick4(quad_bcast<src>(acc[t][k][0]), quad_bcast<src>(acc[t][k][1]),
-                   quad_bcast<src>(acc[t][k][2]), quad_bcast<src>(acc[t][k][3]), v);
-    } else {
-      const int sl = (lane & ~(LPC - 1)) | src;
-      return pick4(__shfl(acc[t][k][0], sl), __shfl(acc[t][k][1], sl), __shfl(acc[t][k][2], sl),
-                   __shfl(acc[t][k][3], sl), v);
-    }
-  }
-};
-
-// The same least-squares phase for a block stored rows by lane (odd L, see
-// block_offset): the NR rows come in groups of four, lane g of a cell owns
-// row 4j + g of group j and adds all L entries of it into all four
-// variables, acc[l][v] += M_l d_v, with d read from the staged member states
-// (all four variables of the member).  Every lane's loads are distinct and
-// contiguous across the wavefront, and no difference is broadcast.  Lanes
-// past the last group's rows re-read its last row with d = 0.  The groups
-// are few (3 for a small stencil, 5 for the large one at order 4) and fully
-// unrolled; NB of them are in flight.  coef<l>() sums the four lanes'
-// partial sums of coefficient l in a fixed order (lanes {0,1} and {2,3}
-// first) and hands lane g variable g.
-#ifndef TENO_LANE_BUFFERS
-#define TENO_LANE_BUFFERS 2
-#endif
-
-template <class T>
-struct TypeTag {
-  using type = T;
-};
-
-template <int K>
-__device__ __forceinline__ double quad_perm_dpp(double x) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), K, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), K, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-template <int R0, int NR, int L>
-struct RowLanes {
-  static constexpr int NG = (NR + 3) / 4;
-  static constexpr int NB = TENO_LANE_BUFFERS < NG ? TENO_LANE_BUFFERS : NG;
-  static_assert(kTile == 16, "rows by lane need four lanes per cell");
-  using Acc = double[L][4];
-
-  const double* us;                    // LDS: states of the tile's distinct members
-  const uint16_t* sidx;                // LDS: each stencil row's member slot
-  const double* __restrict__ mb;       // the tile's block
-  int c, g;
-  double u0[4];                        // the cell's means, all four variables
-  double xq[NB][4];
-  double mq[NB][L];
-
-  template <int J>
-  __device__ __forceinline__ void issue(double (&x)[4], double (&m)[L]) const {
-    constexpr int rg = group_rows(NR, J);
-    const int gg = g < rg ? g : rg - 1;
-    const int r = R0 + 4 * J + gg;
-    const int id = sidx[(r >> 2) * (kTile * 4) + c * 4 + (r & 3)];
-    const double2* u = reinterpret_cast<const double2*>(us + id * 4);
-    const double2 a0 = u[0], a1 = u[1];
-    x[0] = a0.x;
-    x[1] = a0.y;
-    x[2] = a1.x;
-    x[3] = a1.y;
-    const double* __restrict__ p = mb + 4 * kTile * L * J + c * rg + gg;
-#pragma unroll
-    for (int l = 0; l < L; ++l) m[l] = __builtin_nontemporal_load(p + l * kTile * rg);
-  }
-
-  template <int J>
-  __device__ __forceinline__ void accumulate(const double (&x)[4], const double (&m)[L],
-                                             Acc& acc) const {
-    constexpr int rg = group_rows(NR, J);
-    const bool on = rg == 4 || g < rg;
-    double d[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) d[v] = on ? x[v] - u0[v] : 0.0;
-#pragma unroll
-    for (int l = 0; l < L; ++l)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[l][v] = fma(m[l], d[v], acc[l][v]);
-  }
-
-  __device__ __forceinline__ void prime() {
-    static_for<0, NB - 1>([&](auto k) { issue<k>(xq[k], mq[k]); });
-  }
-
-  __device__ __forceinline__ void run(Acc& acc) {
-    static_for<0, NG>([&](auto j) {
-      constexpr int nj = j + NB - 1;
-      if constexpr (nj < NG) issue<nj>(xq[nj % NB], mq[nj % NB]);
-      accumulate<j>(xq[j % NB], mq[j % NB], acc);
-    });
-  }
-
-  // Coefficient l of variable v = g: reduce-scatter over the cell's four
-  // lanes.  Lane g keeps the variables of its parity and takes its
-  // neighbour's (g ^ 1) sums of them, then keeps variable g and takes
-  // lane g ^ 2's pair sum of it.  Called with all four lanes active.
-  template <int l>
-  __device__ __forceinline__ static double coef(const Acc& acc, int v, int lane) {
-    const bool odd = lane & 1, hi = lane & 2;
-    const double k0 = odd ? acc[l][1] : acc[l][0];
-    const double k1 = odd ? acc[l][3] : acc[l][2];
-    const double s0 = odd ? acc[l][0] : acc[l][1];
-    const double s1 = odd ? acc[l][2] : acc[l][3];
-    const double p0 = k0 + quad_perm_dpp<0xB1>(s0);  // quad_perm(1, 0, 3, 2)
-    const double p1 = k1 + quad_perm_dpp<0xB1>(s1);
-    const double keep = hi ? p1 : p0, send = hi ? p0 : p1;
-    return keep + quad_perm_dpp<0x4E>(send);  // quad_perm(2, 3, 0, 1)
-  }
-};
-
-// Occupancy target of the reconstruction kernel (waves per SIMD); 0 leaves
-// the register budget to the compiler.
-#ifndef TENO_RECON_WAVES_PER_EU
-#define TENO_RECON_WAVES_PER_EU 0
-#endif
-#if TENO_RECON_WAVES_PER_EU > 0
-#define TENO_RECON_ATTR __attribute__((amdgpu_waves_per_eu(TENO_RECON_WAVES_PER_EU)))
-#else
-#define TENO_RECON_ATTR
-#endif
 
 // LDS ordering between the lanes of one wavefront (staged indices).
 __device__ __forceinline__ void wave_lds_sync() {
@@ -589,114 +837,99 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS of one wavefront, in int4: the tile's member slots (uint16, 8 per
-// int4), then the states of its distinct members (two int4 each).
-__host__ __device__ constexpr int slot_int4(int rows4) { return rows4 * kTile / 2; }
-__host__ __device__ constexpr int stage_int4(int rows4, int ustride) {
-  return slot_int4(rows4) + 2 * ustride;
-}
-
-// Selection of one variable from its stencils' coefficients, in two parts so
-// that the small stencils' part can run while the large stencil's rows
-// stream in.  Small part: TENO step two over the small stencils (Sec. 3.3)
-// and their mean, or the CWENO sums of alpha_k a^k and d_k a^k (Sec. 2.4).
-template <bool CW>
-struct SmallPart {
-  unsigned nsm = 0;  // kept small stencils (bit k)
-  int ties = 0;      // near ties among the small stencils' chi
-  double ssum = 0.0; // sum of their gammas (TENO) or alphas (CWENO)
-  double asm_[5];    // mean of the kept ones (TENO) or sum alpha_k a^k (CWENO)
-  double dsm[CW ? 5 : 1];  // CWENO: sum d_k a^k
-};
-
-// bcoef(k, l) and coef(k, l): coefficient l of small stencil k, read for
-// the indicators and for the combination (a caller may recompute it rather
-// than hold all fifteen values).  Both are called by all lanes of a cell
-// together, never under a lane-dependent condition.
-template <bool CW, bool UP = false, class BCoef, class CCoef>
-__device__ __forceinline__ void small_part(const ReconArgs& a, bool frozen, unsigned nib_in,
-                                           BCoef&& bcoef, CCoef&& coef, SmallPart<CW>& sp) {
-  auto beta = [&](int k) {
-    double w[5];
-#pragma unroll
-    for (int l = 0; l < 5; ++l) w[l] = bcoef(k, l);
-    return smoothness<2, UP>(w);
-  };
-  sp.nsm = nib_in & 7u;
-  if (!CW && !frozen && a.variant == 0) {
-    const double g0 = gamma_k(beta(0), a.eps, a.power);
-    const double g1 = gamma_k(beta(1), a.eps, a.power);
-    const double g2 = gamma_k(beta(2), a.eps, a.power);
-    sp.ssum = (g0 + g1) + g2;
-    const double is = 1.0 / sp.ssum;
-    const double x0 = g0 * is, x1 = g1 * is, x2 = g2 * is;
-    sp.ties += near_tie(a, x0) + near_tie(a, x1) + near_tie(a, x2);
-    sp.nsm = (x0 >= a.ct ? 1u : 0u) | (x1 >= a.ct ? 2u : 0u) | (x2 >= a.ct ? 4u : 0u);
-  }
-  if constexpr (!CW) {
-    const unsigned nsm = sp.nsm;
-    const int cnt = (int)(nsm & 1u) + (int)((nsm >> 1) & 1u) + (int)((nsm >> 2) & 1u);
-#pragma unroll
-    for (int l = 0; l < 5; ++l) {
-      // read outside the lane-dependent conditions: a coefficient formed by
-      // quad broadcasts needs all four lanes of the cell active
-      const double c0 = coef(0, l), c1 = coef(1, l), c2 = coef(2, l);
-      double acc = 0.0;
-      if (nsm & 1u) acc += c0;
-      if (nsm & 2u) acc += c1;
-      if (nsm & 4u) acc += c2;
-      sp.asm_[l] = cnt > 0 ? acc / (double)cnt : 0.0;
-    }
-  } else {
-    // alpha_k = d_k / (beta_k + eps)^power of the small stencils; their
-    // shares of the combination are finished once the large stencil's
-    // weight is known
-    const double w0 = a.cw_ds * gamma_k(beta(0), a.eps, a.power);
-    const double w1 = a.cw_ds * gamma_k(beta(1), a.eps, a.power);
-    const double w2 = a.cw_ds * gamma_k(beta(2), a.eps, a.power);
-    sp.ssum = (w0 + w1) + w2;
-#pragma unroll
-    for (int l = 0; l < 5; ++l) {
-      const double c0 = coef(0, l), c1 = coef(1, l), c2 = coef(2, l);
-      sp.asm_[l] = (w0 * c0 + w1 * c1) + w2 * c2;
-      sp.dsm[l] = a.cw_ds * ((c0 + c1) + c2);
-    }
-  }
-}
-
-// Large part: TENO step one (Sec. 3.2) and the selected coefficients, or
-// the CWENO combination P = (w_K/d_K)(P_K - sum_k d_k P_k) + sum_k w_k P_k.
-// ab gets the combined coefficients, nib the variable's 4-bit flag.
-template <int P, bool CW, bool UP = false>
-__device__ __forceinline__ void large_part(const ReconArgs& a, bool frozen, unsigned nib_in,
-                                           const SmallPart<CW>& sp,
-                                           const double (&aK)[OrderT<P>::NU],
-                                           double (&ab)[OrderT<P>::NU], unsigned& nib, int& ties) {
+// Selection of one variable from its stencils' coefficients (Sec. 3.2-3.3):
+// step one keeps the large stencil or not; where a lane of the wavefront
+// rejects it, step two and the mean of the small stencils it keeps.  aK becomes
+// the selected coefficients; returns the variable's 4-bit flag.
+template <int P>
+__device__ __forceinline__ unsigned teno_select(TENO_CONST ReconArgs& a, bool frozen, unsigned nib_in,
+                                                const double (&as)[3][5],
+                                                double (&aK)[OrderT<P>::NU], int& ties) {
   using O = OrderT<P>;
-  constexpr int NU = O::NU;
-  if constexpr (CW) {
-    const double wK = a.cw_dK * gamma_k(smoothness<O::R, UP>(aK), a.eps, a.power);
-    const double iS = 1.0 / (sp.ssum + wK);
-    const double cK = wK / a.cw_dK;
-#pragma unroll
-    for (int l = 0; l < NU; ++l)
-      ab[l] = l < 5 ? (cK * (aK[l] - sp.dsm[l]) + sp.asm_[l]) * iS : (cK * aK[l]) * iS;
-    nib = 0u;
-  } else {
-    bool keepK = true;
-    if (frozen) {
-      keepK = (nib_in & 8u) != 0;
-    } else if (a.variant == 0) {
-      const double gK = gamma_k(smoothness<O::R, UP>(aK), a.eps, a.power);
-      const double chiK = gK / (sp.ssum + gK);
-      ties += near_tie(a, chiK);
-      keepK = chiK >= a.ct;
-      if (!keepK) ties += sp.ties;
-    }
-    nib = keepK ? 8u : sp.nsm;
-#pragma unroll
-    for (int l = 0; l < NU; ++l) ab[l] = keepK ? aK[l] : (l < 5 ? sp.asm_[l] : 0.0);
+  unsigned nib = 8u;
+  double gk[3] = {0.0, 0.0, 0.0}, ssum = 1.0;
+  if (frozen) {
+    nib = nib_in;
+  } else if (a.variant == 0) {
+    static_for<0, 3>([&](auto k) { gk[k] = gamma_k(smoothness<2>(as[k]), a.eps, a.power); });
+    ssum = (gk[0] + gk[1]) + gk[2];
+    const double gK = gamma_k(smoothness<O::R>(aK), a.eps, a.power);
+    const double chiK = gK / (ssum + gK);
+    ties += near_tie(a, chiK);
+    nib = chiK >= a.ct ? 8u : 0u;
   }
+  if (__any(!(nib & 8u))) {
+    const bool rej = !(nib & 8u);
+    if (rej && !frozen) {
+      const double is = 1.0 / ssum;
+      static_for<0, 3>([&](auto k) {
+        const double x = gk[k] * is;
+        ties += near_tie(a, x);
+        nib |= x >= a.ct ? 1u << k : 0u;
+      });
+    }
+    const int cnt = (int)(nib & 1u) + (int)((nib >> 1) & 1u) + (int)((nib >> 2) & 1u);
+    const double inv = cnt == 3 ? 1.0 / 3.0 : (cnt == 2 ? 0.5 : (cnt == 1 ? 1.0 : 0.0));
+    static_for<0, O::NU>([&](auto l) {
+      double x = 0.0;
+      if constexpr (l < 5) {
+        if (nib & 1u) x += as[0][l];
+        if (nib & 2u) x += as[1][l];
+        if (nib & 4u) x += as[2][l];
+        x *= inv;
+      }
+      aK[l] = rej ? x : aK[l];
+    });
+    if (rej) nib &= 7u;
+  }
+  return nib;
+}
+
+// CWENO (Sec. 2.4): P = (w_K/d_K)(P_K - sum_k d_k P_k) + sum_k w_k P_k with
+// alpha_k = d_k / (beta_k + eps)^power, w = alpha / sum alpha.
+template <int P>
+__device__ __forceinline__ void cweno_combine(TENO_CONST ReconArgs& a, const double (&as)[3][5],
+                                              double (&aK)[OrderT<P>::NU]) {
+  using O = OrderT<P>;
+  double w[3];
+  static_for<0, 3>([&](auto k) { w[k] = a.cw_ds * gamma_k(smoothness<2>(as[k]), a.eps, a.power); });
+  const double wK = a.cw_dK * gamma_k(smoothness<O::R>(aK), a.eps, a.power);
+  const double iS = 1.0 / (((w[0] + w[1]) + w[2]) + wK);
+  const double cK = wK / a.cw_dK;
+  static_for<0, O::NU>([&](auto l) {
+    if constexpr (l < 5) {
+      const double dsm = a.cw_ds * ((as[0][l] + as[1][l]) + as[2][l]);
+      const double asm_ = (w[0] * as[0][l] + w[1] * as[1][l]) + w[2] * as[2][l];
+      aK[l] = (cK * (aK[l] - dsm) + asm_) * iS;
+    } else {
+      aK[l] = (cK * aK[l]) * iS;
+    }
+  });
+}
+
+// Whether a state held one variable per lane of the quad is physical (rho > 0
+// and p > 0, false for NaN), tested as (g - 1)(rho E - (mx^2 + my^2) / 2) > 0
+// so that the quad shares one sum and no division.  Each lane returns its part;
+// the state is physical where all four lanes say so (quad_all).  Called with
+// all four lanes active.
+struct QuadPhysical {
+  double cs;  // factor of the lane's own square
+  double cp;  // factor of its product with lane v ^ 3 (rho E on lane 0)
+  bool rho;
+  __device__ __forceinline__ void init(int v, double g) {
+    cs = (v == 1 || v == 2) ? -0.5 * (g - 1.0) : 0.0;
+    cp = v == 0 ? g - 1.0 : 0.0;
+    rho = v == 0;
+  }
+  __device__ __forceinline__ bool operator()(double x) const {
+    double t = x * fma(cp, quad_xor<3>(x), cs * x);
+    t += quad_xor<1>(t);
+    t += quad_xor<2>(t);
+    return t > 0.0 && (!rho || x > 0.0);
+  }
+};
+__device__ __forceinline__ bool quad_all(bool ok, int lane) {
+  return ((__ballot(!ok) >> (lane & 60)) & 15ull) == 0ull;
 }
 
 // Characteristic projection of lane variable v (Sec. 2.3): row v of L
@@ -800,113 +1033,6 @@ __device__ __forceinline__ double quad_dot(const double (&row)[4], double x) {
   return s;
 }
 
-// Characteristic-variable phase of one cell (Sec. 2.3), after the
-// least-squares phase: for each local edge, project the coefficients of
-// all four stencils onto the edge's characteristic variables (lane v:
-// variable v), select (or weight) per variable, evaluate at the edge's
-// Gauss points and map back.  Edges run one after another (a loop, not
-// unrolled) so that only one edge's projected coefficients are live; each
-// edge's states and flags are written as soon as they are known and
-// overwritten if the cell falls back to first order.
-template <int P, int NQ, bool CW>
-__device__ __forceinline__ void char_edges(const ReconArgs& a, const double (&as)[3][5],
-                                           const double (&aK)[OrderT<P>::NU], double u0, int cell,
-                                           bool live, bool writer, int g, int v) {
-  using O = OrderT<P>;
-  constexpr int NU = O::NU;
-  const bool avg_ok = physical(quad_bcast<0>(u0), quad_bcast<1>(u0), quad_bcast<2>(u0),
-                               quad_bcast<3>(u0), a.gamma);
-  const double* __restrict__ gc = a.geo + (size_t)(live ? cell : 0) * 10;
-  const int side = a.nbinfo[live ? cell : 0].w;  // face normals point out of the L side
-  int ties = 0;
-  bool fp_ok = true;
-  // TENO keeps the costly part of the projection state across the edges;
-  // CWENO, with more registers live, forms it again on each edge
-  constexpr bool keep_core = !CW;
-  // the indicators from the doubled upper triangles (half the multiply-adds)
-  // where that keeps the kernel's waves per SIMD: TENO up to order 5; at
-  // order 6 and for CWENO it costs a wave and measured 6-9% slower
-  constexpr bool kUpper = !CW && P <= 5;
-  const CharCore core = keep_core ? char_core(char_state(u0, a.gamma)) : CharCore{};
-  auto state = [&]() { return keep_core ? char_expand(core, a.gamma) : char_state(u0, a.gamma); };
-  static_for<0, 3>([&](auto E) {
-    constexpr int e = E;
-    // one edge at a time: keeps the scheduler from overlapping the edges
-    __builtin_amdgcn_sched_barrier(0);
-    // outward unit normal of edge e
-    const double sg = ((side >> (6 + e)) & 1) ? 1.0 : -1.0;
-    const double nx = sg * gc[3 * e], ny = sg * gc[3 * e + 1];
-    double wK[NU], ab[NU];
-    SmallPart<CW> sp;
-    {
-      double lrow[4];
-      char_lrow(state(), nx, ny, avg_ok, v, lrow);
-#pragma unroll
-      for (int l = 0; l < NU; ++l) wK[l] = quad_dot(lrow, aK[l]);
-      // The small stencils' projected coefficients are held for the
-      // indicators and the combination where that keeps the kernel's waves
-      // per SIMD (CWENO, orders 3 and 5); for TENO at orders 4 and 6 holding
-      // them costs a wave per SIMD (120 -> 134, 164 -> 178 VGPRs) and
-      // projecting them twice measured faster.
-      constexpr bool hold = CW || P == 3 || P == 5;
-      if constexpr (!hold) {
-        auto proj = [&](int k, int l) { return quad_dot(lrow, as[k][l]); };
-        small_part<CW, kUpper>(a, false, 8u, proj, proj, sp);
-      } else {
-        double ws[3][5];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-          for (int l = 0; l < 5; ++l) ws[k][l] = quad_dot(lrow, as[k][l]);
-        auto held = [&](int k, int l) { return ws[k][l]; };
-        small_part<CW, kUpper>(a, false, 8u, held, held, sp);
-      }
-    }
-    unsigned nib = 0u;
-    large_part<P, CW, kUpper>(a, false, 8u, sp, wK, ab, nib, ties);
-    double rrow[4];
-    char_rrow(state(), nx, ny, avg_ok, v, rrow);
-    const double* __restrict__ fb = &FaceBasis<O::R, NQ>::P.v[e * NQ][0];
-#pragma unroll
-    for (int kq = 0; kq < NQ; ++kq) {
-      double dw = 0.0;
-#pragma unroll
-      for (int l = 0; l < NU; ++l) dw = fma(ab[l], fb[kq * NU + l], dw);
-      const double val = u0 + quad_dot(rrow, dw);
-      fp_ok = fp_ok && physical(quad_bcast<0>(val), quad_bcast<1>(val), quad_bcast<2>(val),
-                                quad_bcast<3>(val), a.gamma);
-      if (live && writer) a.fp[((size_t)(e * NQ + kq) * a.n_pad + cell) * 4 + v] = val;
-    }
-    if (a.flags) {  // one word per local edge: flags[e][n_cell]
-      unsigned f = nib << (4 * v);
-      f |= __shfl_xor(f, 1);
-      f |= __shfl_xor(f, 2);
-      if (live && g == 0) a.flags[(size_t)e * a.n_cell + cell] = (uint16_t)f;
-    }
-  });
-  __builtin_amdgcn_sched_barrier(0);
-  // ---- non-physical states (all four lanes of a cell agree) ----
-  if (live && g == 0 && !(avg_ok && fp_ok)) {
-    atomicAdd(&a.diag->nonphysical, 1ull);
-    atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
-  }
-  if (!fp_ok && avg_ok && a.fallback) {
-    if (live && writer)
-      for (int q = 0; q < 3 * NQ; ++q) a.fp[((size_t)q * a.n_pad + cell) * 4 + v] = u0;
-    if (a.flags && live && g == 0)
-      for (int e = 0; e < 3; ++e) a.flags[(size_t)e * a.n_cell + cell] = 0;
-    if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
-  }
-  if (live && writer && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
-}
-
-// Reconstruction of one tile of kTile cells by one wavefront; `stage` is
-// this wavefront's LDS area (stage_int4(ROWS4, a.ustride) int4).  CW selects the
-// CWENO weighting (Sec. 2.4) instead of the TENO selection (Sec. 3); CH
-// selects in characteristic variables, edge by edge (Sec. 2.3).
-#ifndef TENO_CHAR_GRAM
-#define TENO_CHAR_GRAM 1
-#endif
 // Characteristic TENO (and Linear) without projecting the coefficients for
 // the indicators.  For each stencil the Gram matrix G = sum_lm B_lm a_l a_m^T
 // of the four variables' coefficient vectors (4 x 4, symmetric) is formed
@@ -916,11 +1042,10 @@ __device__ __forceinline__ void char_edges(const ReconArgs& a, const double (&as
 // select alike on an edge (every smooth cell, and any jump that all fields
 // see), the projection cancels (R L = I) and the face states are the
 // conservative combination of the same stencils; only cells whose fields
-// select differently project the coefficients and map back, as in
-// char_edges.  The Gram matrices live in the wave's staging LDS (16 cells x
+// select differently project the coefficients and map back.  The Gram
+// matrices live in the block's staging LDS (16 cells x
 // 4 stencils x 10 entries), which the least-squares phase no longer needs.
 constexpr int kCharGramDoubles = kTile * 4 * 10;
-__host__ __device__ constexpr int char_gram_int4() { return kCharGramDoubles * 8 / 16; }
 
 __device__ __forceinline__ int gram_off(int i, int j) {  // i <= j
   return i * 4 - (i * (i - 1)) / 2 + (j - i);
@@ -999,18 +1124,19 @@ __device__ __forceinline__ double gram_dot(const double* G, const double (&q)[10
 }
 
 template <int P, int NQ>
-__device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double (&as)[3][5],
+__device__ __forceinline__ void char_edges_gram(TENO_CONST ReconArgs& a, const double (&as)[3][5],
                                                 const double (&aK)[OrderT<P>::NU], double u0,
-                                                int cell, bool live, bool writer, int g, int v,
-                                                int c, int4* stage) {
+                                                int cell, bool live, int g, int v, int c, int lane,
+                                                double* gram0) {
   using O = OrderT<P>;
   constexpr int NU = O::NU;
-  const bool avg_ok = physical(quad_bcast<0>(u0), quad_bcast<1>(u0), quad_bcast<2>(u0),
-                               quad_bcast<3>(u0), a.gamma);
+  QuadPhysical phys;
+  phys.init(v, a.gamma);
+  const bool avg_ok = quad_all(phys(u0), lane);
   const double* __restrict__ gc = a.geo + (size_t)(live ? cell : 0) * 10;
   const int side = a.nbinfo[live ? cell : 0].w;  // face normals point out of the L side
   // ---- Gram matrices of the four stencils (the staging LDS is free now) ----
-  double* gram = reinterpret_cast<double*>(stage) + c * 40;
+  double* gram = gram0 + c * 40;
   wave_lds_sync();
   if (a.variant == 0) {
 #pragma unroll
@@ -1036,7 +1162,7 @@ __device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double
       // once and held in registers across the three edges
       int goff = c * 40;
       asm volatile("" : "+v"(goff));
-      const double* gram = reinterpret_cast<const double*>(stage) + goff;
+      const double* gram = gram0 + goff;
       double q[10];
       gram_weights(lrow, q);
       const double g0 = gamma_k(gram_dot(gram, q), a.eps, a.power);
@@ -1060,7 +1186,7 @@ __device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double
     const unsigned n2 = (unsigned)__builtin_amdgcn_mov_dpp((int)nib, 0xAA, 0xF, 0xF, false);
     const unsigned n3 = (unsigned)__builtin_amdgcn_mov_dpp((int)nib, 0xFF, 0xF, 0xF, false);
     const bool alike = n0 == n1 && n1 == n2 && n2 == n3;
-    const double* __restrict__ fb = &FaceBasis<O::R, NQ>::P.v[e * NQ][0];
+    TENO_CONST double* fb = table(&FaceBasis<O::R, NQ>::P.v[e * NQ][0]);
     // the combined coefficients one at a time, straight into the face sums
     const int cnt = (int)(nib & 1u) + (int)((nib >> 1) & 1u) + (int)((nib >> 2) & 1u);
     const double inv = cnt == 3 ? 1.0 / 3.0 : (cnt == 2 ? 0.5 : (cnt == 1 ? 1.0 : 0.0));
@@ -1117,9 +1243,8 @@ __device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double
     }
 #pragma unroll
     for (int kq = 0; kq < NQ; ++kq) {
-      fp_ok = fp_ok && physical(quad_bcast<0>(val[kq]), quad_bcast<1>(val[kq]),
-                                quad_bcast<2>(val[kq]), quad_bcast<3>(val[kq]), a.gamma);
-      if (live && writer) a.fp[((size_t)(e * NQ + kq) * a.n_pad + cell) * 4 + v] = val[kq];
+      fp_ok = phys(val[kq]) && fp_ok;
+      if (live) (a.fp + (size_t)(e * NQ + kq) * a.n_pad * 4)[4u * cell + v] = val[kq];
     }
     if (a.flags) {  // one word per local edge: flags[e][n_cell]
       unsigned f = nib << (4 * v);
@@ -1130,18 +1255,19 @@ __device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double
   });
   __builtin_amdgcn_sched_barrier(0);
   // ---- non-physical states (all four lanes of a cell agree) ----
+  fp_ok = quad_all(fp_ok, lane);
   if (live && g == 0 && !(avg_ok && fp_ok)) {
     atomicAdd(&a.diag->nonphysical, 1ull);
     atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
   }
   if (!fp_ok && avg_ok && a.fallback) {
-    if (live && writer)
+    if (live)
       for (int q = 0; q < 3 * NQ; ++q) a.fp[((size_t)q * a.n_pad + cell) * 4 + v] = u0;
     if (a.flags && live && g == 0)
       for (int e = 0; e < 3; ++e) a.flags[(size_t)e * a.n_cell + cell] = 0;
     if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
   }
-  if (live && writer && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
+  if (live && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
 }
 
 // Characteristic CWENO (Sec. 2.4 in the variables of Sec. 2.3) with the
@@ -1152,19 +1278,19 @@ __device__ __forceinline__ void char_edges_gram(const ReconArgs& a, const double
 // Gauss points in conservative variables and only those point values are
 // projected (four stencils x NQ points instead of every coefficient).
 template <int P, int NQ>
-__device__ __forceinline__ void char_edges_cweno_gram(const ReconArgs& a,
+__device__ __forceinline__ void char_edges_cweno_gram(TENO_CONST ReconArgs& a,
                                                       const double (&as)[3][5],
                                                       const double (&aK)[OrderT<P>::NU],
                                                       double u0, int cell, bool live,
-                                                      bool writer, int g, int v, int c,
-                                                      int4* stage) {
+                                                      int g, int v, int c, int lane, double* gram0) {
   using O = OrderT<P>;
   constexpr int NU = O::NU;
-  const bool avg_ok = physical(quad_bcast<0>(u0), quad_bcast<1>(u0), quad_bcast<2>(u0),
-                               quad_bcast<3>(u0), a.gamma);
+  QuadPhysical phys;
+  phys.init(v, a.gamma);
+  const bool avg_ok = quad_all(phys(u0), lane);
   const double* __restrict__ gc = a.geo + (size_t)(live ? cell : 0) * 10;
   const int side = a.nbinfo[live ? cell : 0].w;  // face normals point out of the L side
-  double* gram = reinterpret_cast<double*>(stage) + c * 40;
+  double* gram = gram0 + c * 40;
   wave_lds_sync();
 #pragma unroll
   for (int k = 0; k < 3; ++k) gram_rows<2>(as[k], v, gram + 10 * k);
@@ -1182,7 +1308,7 @@ __device__ __forceinline__ void char_edges_cweno_gram(const ReconArgs& a,
     char_lrow_lane(state(), nx, ny, avg_ok, v, lrow);
     int goff = c * 40;
     asm volatile("" : "+v"(goff));
-    const double* gm = reinterpret_cast<const double*>(stage) + goff;
+    const double* gm = gram0 + goff;
     double q[10];
     gram_weights(lrow, q);
     const double w0 = a.cw_ds * gamma_k(gram_dot(gm, q), a.eps, a.power);
@@ -1196,7 +1322,7 @@ __device__ __forceinline__ void char_edges_cweno_gram(const ReconArgs& a,
                  l2 = (w2 - cK * a.cw_ds) * iS;
     double rrow[4];
     char_rrow(state(), nx, ny, avg_ok, v, rrow);
-    const double* __restrict__ fb = &FaceBasis<O::R, NQ>::P.v[e * NQ][0];
+    TENO_CONST double* fb = table(&FaceBasis<O::R, NQ>::P.v[e * NQ][0]);
 #pragma unroll
     for (int kq = 0; kq < NQ; ++kq) {
       // the four stencils' values of the lane's conservative variable
@@ -1213,247 +1339,300 @@ __device__ __forceinline__ void char_edges_cweno_gram(const ReconArgs& a,
                         ((l0 * quad_dot(lrow, p0) + l1 * quad_dot(lrow, p1)) +
                          l2 * quad_dot(lrow, p2));
       const double val = u0 + quad_dot(rrow, dw);
-      fp_ok = fp_ok && physical(quad_bcast<0>(val), quad_bcast<1>(val), quad_bcast<2>(val),
-                                quad_bcast<3>(val), a.gamma);
-      if (live && writer) a.fp[((size_t)(e * NQ + kq) * a.n_pad + cell) * 4 + v] = val;
+      fp_ok = phys(val) && fp_ok;
+      if (live) (a.fp + (size_t)(e * NQ + kq) * a.n_pad * 4)[4u * cell + v] = val;
     }
     if (a.flags && live && g == 0) a.flags[(size_t)e * a.n_cell + cell] = 0;
   });
   __builtin_amdgcn_sched_barrier(0);
   // ---- non-physical states (all four lanes of a cell agree) ----
+  fp_ok = quad_all(fp_ok, lane);
   if (live && g == 0 && !(avg_ok && fp_ok)) {
     atomicAdd(&a.diag->nonphysical, 1ull);
     atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
   }
   if (!fp_ok && avg_ok && a.fallback) {
-    if (live && writer)
+    if (live)
       for (int q = 0; q < 3 * NQ; ++q) a.fp[((size_t)q * a.n_pad + cell) * 4 + v] = u0;
     if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
   }
 }
 
-#ifndef TENO_CHAR_CWENO_GRAM
-#define TENO_CHAR_CWENO_GRAM 1
-#endif
-template <int P, int NQ, bool CW = false, bool CH = false>
-__device__ __forceinline__ void reconstruct_tile(const ReconArgs& a, int tile, int lane,
-                                                 int4* stage) {
+// Degree at which the large stencil's rows are split into two passes: one pass
+// keeps (degree <= split) sums of four variables in registers, the other the
+// rest.  Order 6 on 180,000 cells: 177.5 us split at degree 3, 185.1 at 4;
+// order 5 on 262,088: 159.2 at 4, 170.3 at 3.
+constexpr int split_degree(int p) { return p == 3 ? 2 : (p == 4 ? 3 : (p == 5 ? 4 : 3)); }
+// 16-byte loads of the large normal matrix per chunk, two chunks in flight: as
+// many as the registers hold beside the row sums (7 to 19 at order 5 and 5 to 9
+// at order 6 measured within 3%).  Loading the first chunk a tile ahead costs
+// order 3 its third wavefront per SIMD (53.3 against 48.8 us on 180,000 cells)
+// and gains nothing at the others.
+constexpr int solve_chunk(int p) { return p == 5 ? 14 : (p == 6 ? 9 : 99); }
+
+// What a wavefront needs of its next tile before the first row: loaded while the
+// previous tile's selection runs.
+template <int P>
+struct TileAhead {
+  static constexpr int NU = OrderT<P>::NU, NL = OrderT<P>::NL;
+  static constexpr int CH = solve_chunk(P) < sym_quads(NU) ? solve_chunk(P) : sym_quads(NU);
+  MemberSlots<NL> slots;
+  int cell;  // -1: none
+  double2 ja, jb;
+  float2 cen[4];
+  __device__ __forceinline__ void load(TENO_CONST BlockArgs& b, int tile, int lane) {
+    cell = (b.pack + (size_t)tile * kTile)[(unsigned)lane >> 2];
+    slots.load(b.bslot, tile, lane);
+    const unsigned c = (unsigned)lane >> 2;
+    const float2* __restrict__ ce = b.centre + (size_t)tile * (4 * kTile);
+    const double2* __restrict__ jc = b.jac + (size_t)tile * (2 * kTile);
+    static_for<0, 4>([&](auto k) { cen[k] = ce[4 * c + k]; });
+    ja = jc[2 * c];
+    jb = jc[2 * c + 1];
+  }
+};
+
+// Reconstruction of the blocks of a work list by one workgroup: items
+// [k0, k1) in steps, item k = (arguments, block) from items(k).  Two blocks are
+// staged in LDS: while one is computed, the next one's records and states are
+// copied in behind it and the ids of the one after, so the only wait for
+// memory is for the part of the large normal matrix that the registers cannot
+// hold ahead.  (One block per workgroup and launch slot left the phases of the
+// resident wavefronts aligned: at order 5 a quarter of a wavefront's time went to
+// loading and a fifth of the slots stood empty between workgroups.)
+template <int P, int NQ, bool CW, bool CH, class Items>
+__device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int k1, int step,
+                                                 char* lds) {
   using O = OrderT<P>;
-  constexpr int NU = O::NU;
+  constexpr int NU = O::NU, NL = O::NL, R = O::R;
   constexpr int NP = 3 * NQ;
-  static_assert(!CH || kLanesPerCell == 4, "the projection shares values within a quad");
-  // stage this tile's member slots ([row4][cell][4] uint16) and the states
-  // of its distinct stencil members in LDS
-  wave_lds_sync();  // earlier readers of `stage` are done
+  constexpr int GS = row_groups(kSmallRows), QS = sym_quads(kSmallCoef);
+  if (k0 >= k1) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nthr = blockDim.x;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  auto tile_of = [&](TENO_CONST ReconArgs& a, int blk) {  // the wavefront's tile, -1: none
+    const int t = blk * a.b.bwaves + wave;
+    return wave < a.b.bwaves && t < a.n_tiles ? t : -1;
+  };
+  // ---- the first block: ids straight from memory ----
+  TileAhead<P> ta;
+  int tile_n;  // the wavefront's tile of the next item
   {
-    constexpr int NS = slot_int4(O::ROWS4);
-    const int4* __restrict__ src = a.slot + (size_t)tile * NS;
-    for (int i = lane; i < NS; i += 64) stage[i] = src[i];
-    double2* ust = reinterpret_cast<double2*>(stage + NS);
-    const int* __restrict__ mem = a.tmem + (size_t)tile * a.ustride;
-    for (int i = lane; i < a.ustride; i += 64) {
-      const double2* u = reinterpret_cast<const double2*>(a.U + (size_t)mem[i] * 4);
-      ust[2 * i] = u[0];
-      ust[2 * i + 1] = u[1];
+    TENO_CONST ReconArgs& a = items.args(k0);
+    const int blk = items.block(k0);
+    // all of its places: the lists' lengths are one load further away
+    copy_states(a.U, a.b.bmem + (size_t)blk * a.b.mstride, a.b.mstride, lds0, nthr);
+    copy_records<NU>(a.b, blk, lds0 + 32 * a.b.bmax, nthr);
+    if (k0 + step < k1) {
+      TENO_CONST ReconArgs& n = items.args(k0 + step);
+      copy_ids(n.b, items.block(k0 + step), lds0 + ids_offset(n.b, NU, 1), nthr);
     }
+    tile_n = tile_of(a, blk);
+    ta.load(a.b, max(tile_n, 0), threadIdx.x & 63);
+    lds_copy_wait();
   }
-  wave_lds_sync();
-  const uint16_t* sidx = reinterpret_cast<const uint16_t*>(stage);
-  const double* us = reinterpret_cast<const double*>(stage + slot_int4(O::ROWS4));
-  // g: coefficient group of the lane within its cell; v = g % 4: the
-  // variable it gathers and, in the selection phase, the variable it owns
-  // (with 8 lanes per cell, lanes 4..7 repeat 0..3 and do not write).
-  const int c = lane / kLanesPerCell, g = lane % kLanesPerCell, v = g & 3;
-  const bool writer = g < 4;
-  const int cell = tile * kTile + c;
-  const bool live = cell < a.n_cell;
-  const double u0 = a.U[(size_t)(live ? cell : 0) * 4 + v];
-  // the tile's operator stream (JP doubles per cell) and its blocks; meshes
-  // in conservative variables are dense
-  constexpr bool D = !CH;
-  constexpr int JP = O::template JPD<D>;
-  const double* __restrict__ mt = reinterpret_cast<const double*>(a.M) + (size_t)tile * JP * kTile;
-  auto pairs = [&](int k) {
-    return reinterpret_cast<const double2*>(mt + (size_t)block_start(k, D) * kTile) + c;
-  };
-  auto lanes = [&](int k) { return mt + (size_t)block_start(k, D) * kTile; };
-  const bool frozen = a.frozen != 0;
-  const unsigned nib_in = (frozen && live) ? ((a.flags[cell] >> (4 * v)) & 0xFu) : 8u;
-
-  // ---- small stencils (rows 0..32), then step two of the selection, which
-  //      needs only their indicators.  Each stream is started before the
-  //      previous stencil's coefficients are gathered, and the large
-  //      stencil's first rows load during that last step ----
-  constexpr bool LL = large_lane_rows(O::NU, D), SL = lane_rows(kSmallCoef, D);
-  using LargeS = std::conditional_t<LL, RowLanes<33, O::NL, O::NU>,
-                                    RowStream<33, O::NL, stored_row(O::NU)>>;
-  double u0q[4] = {u0, u0, u0, u0};
-  if constexpr (LL || SL) {
-    u0q[0] = quad_bcast<0>(u0);
-    u0q[1] = quad_bcast<1>(u0);
-    u0q[2] = quad_bcast<2>(u0);
-    u0q[3] = quad_bcast<3>(u0);
-  }
-  auto make_large = [&]() {
-    if constexpr (LL)
-      return LargeS{us, sidx, lanes(3), c, g, {u0q[0], u0q[1], u0q[2], u0q[3]}};
-    else
-      return LargeS{us, sidx, pairs(3), c, g, u0};
-  };
-  LargeS ls = make_large();
-  double as[3][5];
-  {
-    using S0 = std::conditional_t<SL, RowLanes<0, 11, 5>, RowStream<0, 11, stored_row(5)>>;
-    using S1 = std::conditional_t<SL, RowLanes<11, 11, 5>, RowStream<11, 11, stored_row(5)>>;
-    using S2 = std::conditional_t<SL, RowLanes<22, 11, 5>, RowStream<22, 11, stored_row(5)>>;
-    auto make = [&](auto tag, int k) {
-      using S = typename decltype(tag)::type;
-      if constexpr (SL)
-        return S{us, sidx, lanes(k), c, g, {u0q[0], u0q[1], u0q[2], u0q[3]}};
-      else
-        return S{us, sidx, pairs(k), c, g, u0};
+  int it = 0;
+#pragma unroll 1
+  for (int k = k0; k < k1; k += step, ++it) {
+    TENO_CONST ReconArgs& a = items.args(k);
+    const bool on = tile_n >= 0;
+    const int tile = max(tile_n, 0);
+    __syncthreads();  // this block is staged, the other buffer is no longer read
+    // opaque, so that what derives from the lane is formed where it is used and
+    // not held in registers across the items
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int c = lane >> 2, g = lane & 3, v = g;
+    auto stage_next = [&]() {
+      if (k + step < k1) {
+        TENO_CONST ReconArgs& n = items.args(k + step);
+        const int nb = items.block(k + step);
+        const unsigned st = lds0 + buf_offset(n.b, NU, it + 1);
+        const int* ids = reinterpret_cast<const int*>(lds + ids_offset(n.b, NU, it + 1));
+        copy_states(n.U, ids, scalar_load(n.b.boff, nb + 1) - scalar_load(n.b.boff, nb), st, nthr);
+        copy_records<NU>(n.b, nb, st + 32 * n.b.bmax, nthr);
+      }
     };
-    S0 s0 = make(TypeTag<S0>{}, 0);
-    S1 s1 = make(TypeTag<S1>{}, 1);
-    S2 s2 = make(TypeTag<S2>{}, 2);
-    typename S0::Acc sk0 = {}, sk1 = {}, sk2 = {};
-    s0.prime();
-    s0.run(sk0);
-    s1.prime();
-    static_for<0, 5>([&](auto L) { as[0][L] = S0::template coef<L>(sk0, v, lane); });
-    s1.run(sk1);
-    s2.prime();
-    static_for<0, 5>([&](auto L) { as[1][L] = S1::template coef<L>(sk1, v, lane); });
-    s2.run(sk2);
-    ls.prime();
-    static_for<0, 5>([&](auto L) { as[2][L] = S2::template coef<L>(sk2, v, lane); });
-  }
-  SmallPart<CW> sp;
-  if constexpr (!CH) {
-    auto c = [&](int k, int l) { return as[k][l]; };
-    small_part<CW>(a, frozen, nib_in, c, c, sp);
-  }
-
-  // ---- large stencil (rows 33.., entries 165..) ----
-  double aK[NU];
-  {
-    typename LargeS::Acc sk = {};
-    ls.run(sk);
-    static_for<0, NU>([&](auto L) { aK[L] = LargeS::template coef<L>(sk, v, lane); });
-  }
-  if constexpr (CH) {
-#if TENO_CHAR_GRAM
-    if constexpr (!CW)
-      char_edges_gram<P, NQ>(a, as, aK, u0, cell, live, writer, g, v, c, stage);
-    else if constexpr (TENO_CHAR_CWENO_GRAM)
-      char_edges_cweno_gram<P, NQ>(a, as, aK, u0, cell, live, writer, g, v, c, stage);
+    if (a.b.nbuf == 2) {
+      stage_next();
+      if (k + 2 * step < k1) {
+        TENO_CONST ReconArgs& n = items.args(k + 2 * step);
+        copy_ids(n.b, items.block(k + 2 * step), lds0 + ids_offset(n.b, NU, it), nthr);
+      }
+    }
+    const char* buf = lds + buf_offset(a.b, NU, it);
+    const int own_slot = min(wave, a.b.bwaves - 1) * kTile + c;
+    const int cell = ta.cell;
+    const bool live = on && cell >= 0;
+    CellView cv;
+    cv.us = reinterpret_cast<const double*>(buf);
+    cv.geo = reinterpret_cast<const double*>(buf + 32 * a.b.bmax);
+    cv.g = g;
+    const double* own = cv.geo + own_slot * (2 * rec_units(NU));
+    cv.x = own[0];
+    cv.y = own[1];
+    static_for<0, 4>([&](auto i) { cv.u0[i] = cv.us[own_slot * 4 + (g ^ i)]; });
+    const double u0 = cv.u0[0];
+    const bool frozen = a.frozen != 0;
+    const double2* __restrict__ np = a.b.N + (size_t)tile * (normal_quads(NU) * 64);
+    const bool small = CW || frozen || a.variant != 1;
+    double aK[NU], as[3][5];
+    NormalMatrix<kSmallCoef> ns[3];
+    // ---- large stencil ----
+    {
+      double r[NU];
+      const float2 ce = ta.cen[3];
+      const bool shift = __any(ce.x != 0.0f || ce.y != 0.0f);
+      stencil_sums<R, NL, 3 * GS, NU, split_degree(P)>(cv, ta.slots, own, ce.x, ce.y, shift, r);
+      NormalMatrix<NU, TileAhead<P>::CH> nl;
+      nl.template load<0>(np + 3 * QS * 64, lane);
+      if (small) ns[0].template load<0>(np, lane);
+      nl.apply(np + 3 * QS * 64, lane, r, aK);
+      hermite_to_monomials<R>(aK, ce.x, ce.y, shift);
+      Frame<R> fr;
+      fr.init(ta.ja, ta.jb);
+      fr.template to_basis<R>(aK);
+      static_for<0, NU>([&](auto l) { opaque(aK[l]); });
+    }
+    // ---- small stencils; the linear scheme keeps the large stencil and never
+    //      reads them ----
+    if (small) {
+      Frame<2> fr;
+      fr.init(ta.ja, ta.jb);
+      static_for<0, 3>([&](auto q) {
+        double r[kSmallCoef];
+        const float2 ce = ta.cen[q];
+        if constexpr (q < 2) ns[q + 1].template load<0>(np + QS * (q + 1) * 64, lane);
+        stencil_sums<2, kSmallRows, GS * q, NU, 2>(cv, ta.slots, own, ce.x, ce.y, true, r);
+        ns[q].apply(np, lane, r, as[q]);
+        hermite_to_monomials<2>(as[q], ce.x, ce.y, true);
+        fr.template to_basis<2>(as[q]);
+        static_for<0, 5>([&](auto l) { opaque(as[q][l]); });
+      });
+    } else {
+      static_for<0, 3>([&](auto q) { static_for<0, 5>([&](auto l) { as[q][l] = 0.0; }); });
+    }
+    // every copy and load so far is complete (they return in order)
+    lds_copy_wait();
+    if (k + step < k1) {
+      TENO_CONST ReconArgs& n = items.args(k + step);
+      tile_n = tile_of(n, items.block(k + step));
+      ta.load(n.b, max(tile_n, 0), lane);
+    }
+    if (a.b.nbuf == 1 && k + step < k1) {  // the next block in the same LDS
+      TENO_CONST ReconArgs& n = items.args(k + step);
+      __syncthreads();
+      copy_ids(n.b, items.block(k + step), lds0 + ids_offset(n.b, NU, 0), nthr);
+      lds_copy_wait();
+      __syncthreads();
+      if constexpr (!CH) {
+        stage_next();
+        lds_copy_wait();
+      }
+    }
+    if constexpr (CH) {
+      __syncthreads();  // every wavefront is done with the staged members
+      double* gram = reinterpret_cast<double*>(const_cast<char*>(buf)) + wave * kCharGramDoubles;
+      if constexpr (CW)
+        char_edges_cweno_gram<P, NQ>(a, as, aK, u0, cell, live, g, v, c, lane, gram);
+      else
+        char_edges_gram<P, NQ>(a, as, aK, u0, cell, live, g, v, c, lane, gram);
+      if (a.b.nbuf == 1 && k + step < k1) {
+        __syncthreads();
+        stage_next();
+        lds_copy_wait();
+      }
+      continue;
+    }
+    const unsigned nib_in = (frozen && live) ? ((a.flags[cell] >> (4 * v)) & 0xFu) : 8u;
+    int ties = 0;
+    unsigned nib = 0u;
+    if constexpr (CW)
+      cweno_combine<P>(a, as, aK);
     else
-#endif
-      char_edges<P, NQ, CW>(a, as, aK, u0, cell, live, writer, g, v);
-    return;
-  }
-  int ties = 0;
-  unsigned nib = 0u;
-  double val[NP];
-  {
-    double ab[NU];
-    large_part<P, CW>(a, frozen, nib_in, sp, aK, ab, nib, ties);
+      nib = teno_select<P>(a, frozen, nib_in, as, aK, ties);
     // ---- face Gauss points (variable v of this cell) ----
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
+    double val[NP];
+    static_for<0, NP>([&](auto q) {
       double s = u0;
-#pragma unroll
-      for (int l = 0; l < NU; ++l) s = fma(ab[l], FaceBasis<O::R, NQ>::P.v[q][l], s);
+      static_for<0, NU>([&](auto l) { s = fma(aK[l], FaceBasis<O::R, NQ>::P.v[q][l], s); });
       val[q] = s;
+    });
+    // ---- non-physical states (all four lanes of a cell agree) ----
+    if (!frozen) {
+      QuadPhysical phys;
+      phys.init(v, a.gamma);
+      const bool avg_ok = quad_all(phys(u0), lane);
+      bool ok = true;
+      static_for<0, NP>([&](auto q) { ok = phys(val[q]) && ok; });
+      const bool fp_ok = quad_all(ok, lane);
+      if (live && g == 0 && !(avg_ok && fp_ok)) {  // one lane per cell
+        atomicAdd(&a.diag->nonphysical, 1ull);
+        atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
+      }
+      if (!fp_ok && avg_ok && a.fallback) {
+        static_for<0, NP>([&](auto q) { val[q] = u0; });
+        nib = 0u;
+        if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
+      }
+      if (live && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
     }
-  }
-  // ---- non-physical states (all four lanes of a cell agree) ----
-  if (!frozen) {
-    const bool avg_ok = physical(quad_bcast<0>(u0), quad_bcast<1>(u0), quad_bcast<2>(u0),
-                                 quad_bcast<3>(u0), a.gamma);
-    bool fp_ok = true;
-#pragma unroll
-    for (int q = 0; q < NP; ++q)
-      fp_ok = fp_ok && physical(quad_bcast<0>(val[q]), quad_bcast<1>(val[q]),
-                                quad_bcast<2>(val[q]), quad_bcast<3>(val[q]), a.gamma);
-    if (live && g == 0 && !(avg_ok && fp_ok)) {  // one lane per cell
-      atomicAdd(&a.diag->nonphysical, 1ull);
-      atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
+    if (live)
+      static_for<0, NP>([&](auto q) {
+        (a.fp + (size_t)q * a.n_pad * 4)[4u * cell + v] = val[q];
+      });
+    if (!frozen && a.flags) {
+      unsigned f = nib << (4 * v);
+      f |= __shfl_xor(f, 1);
+      f |= __shfl_xor(f, 2);
+      if (live && g == 0) a.flags[cell] = (uint16_t)f;
     }
-    if (!fp_ok && avg_ok && a.fallback) {
-#pragma unroll
-      for (int q = 0; q < NP; ++q) val[q] = u0;
-      nib = 0u;
-      if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
-    }
-    if (live && writer && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
-  }
-  if (live && writer) {
-#pragma unroll
-    for (int q = 0; q < NP; ++q) a.fp[((size_t)q * a.n_pad + cell) * 4 + v] = val[q];
-  }
-  if (!frozen && a.flags) {
-    unsigned f = nib << (4 * v);
-    f |= __shfl_xor(f, 1);
-    f |= __shfl_xor(f, 2);
-    if (live && g == 0) a.flags[cell] = (uint16_t)f;
   }
 }
 
-// Per-order occupancy targets (waves per SIMD; 1 leaves the budget to the
-// compiler): TENO at order 3 in rows-by-lane blocks needs 132 registers left
-// alone and runs faster held to 128 (four waves); TENO at order 5 (130
-// registers, 2 spilled when held to 128) measured 1% faster at four waves
-// with one wavefront per block.  The other kernels measured best
-// unconstrained (order 4 and CWENO 6 lose 10-14% at four waves).
-template <int P, bool CW>
-struct ReconWaves {
-  static constexpr int value = TENO_RECON_WAVES_PER_EU > 0 ? TENO_RECON_WAVES_PER_EU
-                               : ((P == 3 || P == 5) && !CW && lane_rows(kSmallCoef, true)) ? 4
-                                                                                        : 1;
+// The blocks of one mesh, dealt to the workgroups of an XCD in turn: workgroups
+// are dispatched round-robin over the 8 XCDs, and each XCD gets a contiguous
+// range of blocks, so that its L2 holds the neighbourhood it gathers.
+struct MeshItems {
+  int first;
+  // the kernel's first argument, through an opaque pointer: what an item reads
+  // is not held in scalar registers across the items
+  __device__ __forceinline__ TENO_CONST ReconArgs& args(int) const {
+    auto p = (TENO_CONST ReconArgs*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+  }
+  __device__ __forceinline__ int block(int k) const { return first + k; }
 };
-
-// Wavefronts per block of the reconstruction kernels (one tile each).  One
-// wavefront per block lets the dispatcher start each tile on its own, so
-// the streaming and selection phases of the wavefronts on a SIMD drift
-// apart; it measured 1.5-3% faster than four per block.
-#ifndef TENO_RECON_BLOCK_WAVES
-#define TENO_RECON_BLOCK_WAVES 1
-#endif
-constexpr int kReconBlockWaves = TENO_RECON_BLOCK_WAVES;
-
-template <int P, int NQ, bool CW>
-__global__ __launch_bounds__(64 * kReconBlockWaves)
-__attribute__((amdgpu_waves_per_eu(ReconWaves<P, CW>::value)))
-void k_reconstruct(ReconArgs a) {
-  extern __shared__ int4 lds[];  // kReconBlockWaves wavefronts x a.lds_stride
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kReconBlockWaves + wave;
-  if (tile >= a.n_tiles) return;  // whole wavefront leaves together
-  reconstruct_tile<P, NQ, CW, false>(a, tile, lane, lds + wave * a.lds_stride);
+template <int P, int NQ, bool CW, bool CH>
+__device__ __forceinline__ void reconstruct_mesh(int n_blocks) {
+  extern __shared__ int4 lds[];
+  const int x = blockIdx.x & 7, j = blockIdx.x >> 3, G = gridDim.x;
+  const int q = n_blocks / 8, r = n_blocks % 8;
+  const MeshItems items{x * q + min(x, r)};
+  reconstruct_loop<P, NQ, CW, CH>(items, j, q + (x < r ? 1 : 0), G / 8 + (x < G % 8 ? 1 : 0),
+                                  reinterpret_cast<char*>(lds));
 }
 
-// The same in characteristic variables.  The TENO kernel's register budget
-// is capped at TENO_CHAR_WAVES_PER_EU wavefronts per SIMD (left alone, the
-// order-6 kernel takes 175 VGPRs and two waves); the CWENO kernel, which
-// holds the projected coefficients of every stencil across its weights, is
-// left to the compiler.
-#ifndef TENO_CHAR_WAVES_PER_EU
-#define TENO_CHAR_WAVES_PER_EU 3
-#endif
-template <bool CW>
-struct CharWaves {
-  static constexpr int value = (!CW && TENO_CHAR_WAVES_PER_EU > 0) ? TENO_CHAR_WAVES_PER_EU : 1;
-};
+// Occupancy targets (waves per SIMD) of the reconstruction kernels: the third
+// wavefront pays at order 3 (48.8 against 53.3 us on 180,000 cells); at order 4
+// its 168 registers spill (97 against 68 us).
+constexpr int recon_waves(int p) { return p == 3 ? 3 : 2; }
+
 template <int P, int NQ, bool CW>
-__global__ __launch_bounds__(64 * kReconBlockWaves)
-__attribute__((amdgpu_waves_per_eu(CharWaves<CW>::value)))
-void k_reconstruct_char(ReconArgs a) {
-  extern __shared__ int4 lds[];  // kReconBlockWaves wavefronts x a.lds_stride
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x) * kReconBlockWaves + wave;
-  if (tile >= a.n_tiles) return;  // whole wavefront leaves together
-  reconstruct_tile<P, NQ, CW, true>(a, tile, lane, lds + wave * a.lds_stride);
+__global__ __launch_bounds__(64 * block_tiles(P))
+__attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct(ReconArgs a,
+                                                                         int n_blocks) {
+  reconstruct_mesh<P, NQ, CW, false>(n_blocks);
+}
+
+// The same in characteristic variables.
+template <int P, int NQ, bool CW>
+__global__ __launch_bounds__(64 * block_tiles(P))
+__attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct_char(ReconArgs a,
+                                                                              int n_blocks) {
+  reconstruct_mesh<P, NQ, CW, true>(n_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1789,24 +1968,22 @@ __global__ __launch_bounds__(256) void k_adj_boundary(AdjFaceArgs a, const int* 
 }
 
 // Phase 2 (one wavefront per tile, four lanes per cell): transpose of the
-// reconstruction.  The adjoint of each stencil difference d_s = U_s - U_0
-// goes to the tile's member slot of U_s, summed in LDS (one accumulator per
-// distinct member and variable) in a fixed order.  Blocks stored rows by
-// lane are read as the forward kernel reads them: lane g of a cell takes row
-// 4j + g of group j for all four variables (the coefficient adjoints of the
-// cell are shared across its four lanes first); blocks of entry pairs are
-// read by lane v for variable v, row by row.  Within one LDS instruction the
-// lanes that name the same member add in rounds that set-up assigns (in lane
-// order for a group of rows, in cell order for one row), so no instruction
-// has two lanes on one address and every sum is formed in the same order on
-// every run.  The tile's sums are written once to tbar; the cell's own part
-// (the -U_0 of its differences and its face points) goes to own[n][4].
+// reconstruction.  Lane v forms the adjoints of variable v's coefficients from
+// its face points and, per stencil that a variable of the wavefront keeps,
+// z = N times them (in the block's frame).  The cell's four lanes share z, and
+// lane g takes rows 4j + g for all four variables, as the forward kernel does:
+// the adjoint of difference d_s is w_s A_s^T z, with A_s from the staged
+// records.  It goes to the tile's member slot of U_s, summed in LDS (one
+// accumulator per distinct member of the tile and variable) in a fixed order:
+// the lanes of a group of rows that name the same member add in rounds that
+// set-up assigns, so no LDS instruction has two lanes on one address.  The
+// tile's sums are written once to tbar; the cell's own part (the -U_0 of its
+// differences and its face points) goes to own[n][4].
 struct AdjReconArgs {
   const double* __restrict__ fpbar;
   const uint16_t* __restrict__ flags;
-  const double2* __restrict__ M;
-  const int4* __restrict__ aslot;   // [n_tiles][rows4][16][4] uint16: slot | round << 9
-  const int* __restrict__ tround;   // [n_tiles] rounds of the tile (largest round + 1)
+  BlockArgs b;
+  const unsigned* __restrict__ aslot;  // [n_tiles][adj_words][64]: slot | round << 9
   double* __restrict__ tbar;      // [n_tiles][ustride][4]
   double* __restrict__ own;       // [n_pad][4]
   int ustride;
@@ -1822,32 +1999,99 @@ __device__ __forceinline__ unsigned quad_bcast_u(unsigned x, int k) {
   }
 }
 
-// wavefronts per block of the adjoint reconstruction (one tile each); one,
-// as for the forward kernels, measured 4% faster on the backward pass
-#ifndef TENO_ADJ_BLOCK_WAVES
-#define TENO_ADJ_BLOCK_WAVES 1
-#endif
-constexpr int kAdjBlockWaves = TENO_ADJ_BLOCK_WAVES;
+// Rows of one stencil: adjoints of its differences from z (the lane's own
+// variable), added to acc; returns the lane's sums over its rows in dq.
+// VP variables at a time: two passes form the moments twice, where the shared z
+// of all four would not fit the registers.
+template <int R, int NR, int G0, int NU, int VP, class Slots, class AdjSlots>
+__device__ __forceinline__ void adj_rows(const CellView& cv, const Slots& slots,
+                                         const AdjSlots& aslots, const double* own,
+                                         double cx, double cy, bool shift, double* z,
+                                         double* acc, double (&dq)[4]) {
+  constexpr int N = (R + 1) * (R + 2) / 2 - 1;
+  constexpr int RS = 2 * rec_units(NU);
+  // zero mean of the rows over the cell
+  double h[N];
+  own_moments<R>(own, cx, cy, shift, h);
+  double z0 = 0.0;
+  static_for<0, N>([&](auto l) { z0 = fma(-h[l], z[l], z0); });
+  const double x0 = cv.x + cx, y0 = cv.y + cy;
+  static_for<0, 4 / VP>([&](auto pc) {
+    constexpr int I0 = pc * VP;
+    double zq[N][VP], z0q[VP];
+    opaque(z0);  // (or every pass's exchange is formed ahead and held)
+    static_for<0, N>([&](auto l) { opaque(z[l]); });
+    static_for<0, VP>([&](auto i) {
+      z0q[i] = quad_xor<I0 + i>(z0);
+      static_for<0, N>([&](auto l) { zq[l][i] = quad_xor<I0 + i>(z[l]); });
+    });
+    static_for<0, row_groups(NR)>([&](auto jc) {
+      unsigned m = slots.template get<G0 + jc>();
+      asm volatile("" : "+v"(m));  // each pass reads its records again
+      const unsigned w = aslots.template get<G0 + jc>();
+      const double* rec = cv.geo + m * RS;
+      double q[N + 1], mo[N], d[VP];
+      static_for<0, N + 1>([&](auto l) { q[l] = rec[l]; });
+      shift_moments<R>(q[0] - x0, q[1] - y0, q + 3, mo);
+      const bool row = 4 * jc + cv.g < NR;
+      static_for<0, VP>([&](auto i) {
+        double t = z0q[i];
+        static_for<0, N>([&](auto l) { t = fma(mo[l], zq[l][i], t); });
+        d[i] = row ? t * q[2] : 0.0;
+        dq[I0 + i] += d[i];
+      });
+      double* dst = acc + (w & 511) * 4;
+      const int mine = row ? (int)(w >> 9) : -1;
+      for (int r = 0; __any(mine >= r); ++r)
+        if (mine == r) static_for<0, VP>([&](auto i) { atomicAdd(dst + (cv.g ^ (I0 + i)), d[i]); });
+    });
+  });
+}
+
+// The adjoint's: 72 against 78 us at order 4 with three (131,072 cells).
+constexpr int adj_waves(int p) { return p <= 4 ? 3 : 2; }
 
 template <int P, int NQ>
-__global__ __launch_bounds__(64 * kAdjBlockWaves) void k_adj_recon(AdjReconArgs a) {
+__global__ __launch_bounds__(64 * block_tiles(P))
+__attribute__((amdgpu_waves_per_eu(adj_waves(P)))) void k_adj_recon(AdjReconArgs a) {
   using O = OrderT<P>;
-  constexpr int NU = O::NU;
+  constexpr int NU = O::NU, NL = O::NL, R = O::R;
   constexpr int NP = 3 * NQ;
-  constexpr bool SL = lane_rows(kSmallCoef, true), LL = large_lane_rows(NU, true);
-  static_assert(kTile == 16, "four lanes per cell");
-  extern __shared__ double lds_acc[];  // kAdjBlockWaves wavefronts x ustride x 4
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tile =
-      __builtin_amdgcn_readfirstlane(xcd_remap(blockIdx.x, gridDim.x) * kAdjBlockWaves + wave);
+  constexpr int GS = row_groups(kSmallRows), QS = sym_quads(kSmallCoef);
+  extern __shared__ int4 lds4[];  // records, then bwaves x ustride x 4 doubles
+  char* lds = reinterpret_cast<char*>(lds4);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int tile = blk * a.b.bwaves + wave;
+  double* accs = reinterpret_cast<double*>(lds + 16 * rec_units(NU) * a.b.bmax);
+  for (int i = threadIdx.x; i < 4 * a.b.bwaves * a.ustride; i += blockDim.x) accs[i] = 0.0;
+  copy_records<NU>(((TENO_CONST AdjReconArgs*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr())->b,
+                   blk, (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds,
+                   blockDim.x);
+  lds_copy_wait();
+  __syncthreads();
   if (tile >= a.n_tiles) return;  // whole wavefront leaves together
-  double* acc = lds_acc + (size_t)wave * a.ustride * 4;
-  for (int i = lane; i < 4 * a.ustride; i += 64) acc[i] = 0.0;
-  wave_lds_sync();
-  const int c = lane / kLanesPerCell, v = lane % kLanesPerCell, g = v;
-  const int cell = tile * kTile + c;
-  const bool live = cell < a.n_cell;
-  const int cl = live ? cell : tile * kTile;
+  double* acc = accs + (size_t)wave * a.ustride * 4;
+  const int c = lane >> 2, v = lane & 3;
+  const int pos = tile * kTile + c, cell = a.b.pack[pos];
+  const bool live = cell >= 0;
+  const int cl = live ? cell : 0;
+  MemberSlots<NL> slots;
+  slots.load(a.b.bslot, tile, lane);
+  RowSlots<lane_groups(NL), 16> aslots;
+  aslots.load(a.aslot, tile, lane);
+  CellView cv;
+  cv.us = nullptr;
+  cv.geo = reinterpret_cast<const double*>(lds);
+  cv.g = v;
+  const double* own = cv.geo + (wave * kTile + c) * (2 * rec_units(NU));
+  cv.x = own[0];
+  cv.y = own[1];
+  const double2* __restrict__ np = a.b.N + (size_t)tile * (normal_quads(NU) * 64);
+  const double2* __restrict__ jp = a.b.jac + 2 * (size_t)pos;
+  const float2* __restrict__ cen = a.b.centre + 4 * (size_t)pos;
+  Frame<R> fr;
+  fr.init(jp[0], jp[1]);
   const unsigned nib = live ? ((a.flags[cl] >> (4 * v)) & 0xFu) : 0u;
   double gsum = 0.0;
   double ab[NU];
@@ -1860,141 +2104,46 @@ __global__ __launch_bounds__(64 * kAdjBlockWaves) void k_adj_recon(AdjReconArgs 
 #pragma unroll
     for (int l = 0; l < NU; ++l) ab[l] = fma(FaceBasis<O::R, NQ>::P.v[q][l], gq, ab[l]);
   }
-  // the tile's operator stream (dense: the adjoint runs on meshes in
-  // conservative variables)
-  const double* __restrict__ mt =
-      reinterpret_cast<const double*>(a.M) + (size_t)tile * O::template JPD<true> * kTile;
-  const uint16_t* __restrict__ sl =
-      reinterpret_cast<const uint16_t*>(a.aslot + (size_t)tile * slot_int4(O::ROWS4));
-  const int rounds = a.tround[tile];  // >= 1, the same for the whole wavefront
-  auto slot_of = [&](int r) { return (int)sl[(r >> 2) * (kTile * 4) + c * 4 + (r & 3)]; };
-  // adds d into accumulator column q of the row's member, in the row's round
-  // (the first round unconditionally, so the slot word is loaded with the
-  // row's operator entries rather than after them)
-  auto add_in_round = [&](int w, int q, double d, bool on) {
-    double* dst = &acc[(w & 511) * 4 + q];
-    const int mine = w >> 9;
-    int r = 0;
-    do {
-      if (on && mine == r) atomicAdd(dst, d);
-    } while (++r < rounds);
-  };
+  // adjoints of the frame's coefficients (the small stencils' basis is the
+  // first functions of the large one)
+  static_for<0, NU>([&](auto l) { opaque(ab[l]); });
+  fr.template from_basis_adjoint<R>(ab);
+  static_for<0, NU>([&](auto l) { opaque(ab[l]); });
   const bool keepK = nib & 8u;
   const int cnt = (int)(nib & 1u) + (int)((nib >> 1) & 1u) + (int)((nib >> 2) & 1u);
-  // the flags of the cell's four variables, on all four lanes
-  unsigned nq[4];
+  double dq[4] = {0.0, 0.0, 0.0, 0.0};
+  // ---- small stencils: each kept one counts 1/cnt where step two decided ----
+  static_for<0, 3>([&](auto k) {
+    const bool kept = !keepK && ((nib >> k) & 1u);
+    if (!__any(kept)) return;
+    const double w = kept ? 1.0 / (double)cnt : 0.0;
+    double r[kSmallCoef], z[kSmallCoef];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) nq[q] = quad_bcast_u(nib, q);
-  // weight of stencil k (3 = large) for variable q: a small stencil counts
-  // 1/cnt where step two kept it, the large one 1 where step one kept it
-  auto weight = [&](int k, int q) {
-    const unsigned f = nq[q];
-    if (!live) return 0.0;
-    if (k == 3) return (f & 8u) ? 1.0 : 0.0;
-    const int cq = (int)(f & 1u) + (int)((f >> 1) & 1u) + (int)((f >> 2) & 1u);
-    return (!(f & 8u) && ((f >> k) & 1u) && cq > 0) ? 1.0 / (double)cq : 0.0;
-  };
-  double dsum = 0.0;                    // rows read by variable (lane v)
-  double dq[4] = {0.0, 0.0, 0.0, 0.0};  // rows read by lane: this lane's rows, per variable
-
-  // rows by lane: a block of NR rows of L entries at block k of the stream,
-  // with coefficient adjoints ab4 of all four variables and weights w
-  auto lane_block = [&](auto kc, auto nrc, auto lc, const auto& ab4) {
-    constexpr int K = decltype(kc)::value, NR = decltype(nrc)::value, L = decltype(lc)::value;
-    constexpr int R0 = K == 3 ? 33 : kSmallRows * K;
-    const double w[4] = {weight(K, 0), weight(K, 1), weight(K, 2), weight(K, 3)};
-    const bool need = (w[0] != 0.0) | (w[1] != 0.0) | (w[2] != 0.0) | (w[3] != 0.0);
-    if (!__any(need)) return;
-    const double* __restrict__ mb = mt + (size_t)block_start(K, true) * kTile;
-    static_for<0, (NR + 3) / 4>([&](auto jc) {
-      constexpr int J = jc, rg = group_rows(NR, J);
-      const int gg = g < rg ? g : rg - 1;
-      const bool on = g < rg;
-      const int s = 4 * J + gg;
-      double m[L];
-#pragma unroll
-      for (int l = 0; l < L; ++l) m[l] = mb[4 * kTile * L * J + (l * kTile + c) * rg + gg];
-      const int w0 = slot_of(R0 + s);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double t = 0.0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) t = fma(m[l], ab4[l][q], t);
-        const double d = (on && w[q] != 0.0) ? t * w[q] : 0.0;
-        dq[q] += d;
-        add_in_round(w0, q, d, on && w[q] != 0.0);
-      }
-    });
-  };
-
-  // ---- small stencils ----
-  if constexpr (SL) {
-    double ab4[kSmallCoef][4];
-#pragma unroll
-    for (int l = 0; l < kSmallCoef; ++l) {
-      ab4[l][0] = quad_bcast<0>(ab[l]);
-      ab4[l][1] = quad_bcast<1>(ab[l]);
-      ab4[l][2] = quad_bcast<2>(ab[l]);
-      ab4[l][3] = quad_bcast<3>(ab[l]);
-    }
-    using I = std::integral_constant<int, kSmallRows>;
-    using C = std::integral_constant<int, kSmallCoef>;
-    lane_block(std::integral_constant<int, 0>{}, I{}, C{}, ab4);
-    lane_block(std::integral_constant<int, 1>{}, I{}, C{}, ab4);
-    lane_block(std::integral_constant<int, 2>{}, I{}, C{}, ab4);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const bool kept = live && !keepK && (nib & (1u << k)) && cnt > 0;
-      if (kept) {
-        const double wk = 1.0 / (double)cnt;
-#pragma unroll
-        for (int s = 0; s < kSmallRows; ++s) {
-          double d = 0.0;
-#pragma unroll
-          for (int l = 0; l < kSmallCoef; ++l)
-            d = fma(mt[(size_t)block_start(k, true) * kTile + block_offset(kSmallRows, kSmallCoef, true, c, s, l)],
-                    ab[l], d);
-          d *= wk;
-          dsum += d;
-          add_in_round(slot_of(small_row(k, s)), v, d, true);
-        }
-      }
-    }
-  }
+    for (int l = 0; l < kSmallCoef; ++l) r[l] = w * ab[l];
+    const float2 ce = cen[k];
+    hermite_to_monomials_adjoint<2>(r, ce.x, ce.y, true);
+    NormalMatrix<kSmallCoef> nm;
+    nm.template load<0>(np + QS * k * 64, lane);
+    nm.apply(np, lane, r, z);
+    static_for<0, kSmallCoef>([&](auto l) { opaque(z[l]); });
+    adj_rows<2, kSmallRows, GS * k, NU, 4>(cv, slots, aslots, own, ce.x, ce.y, true, z, acc, dq);
+  });
   // ---- large stencil ----
-  if constexpr (LL) {
-    double ab4[NU][4];
+  if (__any(keepK)) {
+    double z[NU];
 #pragma unroll
-    for (int l = 0; l < NU; ++l) {
-      ab4[l][0] = quad_bcast<0>(ab[l]);
-      ab4[l][1] = quad_bcast<1>(ab[l]);
-      ab4[l][2] = quad_bcast<2>(ab[l]);
-      ab4[l][3] = quad_bcast<3>(ab[l]);
-    }
-    lane_block(std::integral_constant<int, 3>{}, std::integral_constant<int, O::NL>{},
-               std::integral_constant<int, NU>{}, ab4);
-  } else if (live && keepK) {
-#pragma unroll 1
-    for (int s = 0; s < O::NL; ++s) {
-      double d = 0.0;
-#pragma unroll
-      for (int l = 0; l < NU; ++l)
-        d = fma(mt[(size_t)block_start(3, true) * kTile + large_block_offset(O::NL, NU, true, c, s, l)],
-                ab[l], d);
-      dsum += d;
-      add_in_round(slot_of(large_row(s)), v, d, true);
-    }
+    for (int l = 0; l < NU; ++l) ab[l] = keepK ? ab[l] : 0.0;
+    const float2 ce = cen[3];
+    const bool shift = __any(ce.x != 0.0f || ce.y != 0.0f);
+    hermite_to_monomials_adjoint<R>(ab, ce.x, ce.y, shift);
+    static_for<0, NU>([&](auto l) { opaque(ab[l]); });
+    NormalMatrix<NU, TileAhead<P>::CH> nm;
+    nm.template load<0>(np + 3 * QS * 64, lane);
+    nm.apply(np + 3 * QS * 64, lane, ab, z);
+    static_for<0, NU>([&](auto l) { opaque(z[l]); });  // (no part of it sinks past a branch)
+    adj_rows<R, NL, 3 * GS, NU, (P >= 5 ? 2 : 4)>(cv, slots, aslots, own, ce.x, ce.y, shift, z, acc, dq);
   }
-  // the rows read by lane: variable v's sum over the cell's four lanes
-  if constexpr (SL || LL) {
-    const bool odd = lane & 1, hi = lane & 2;
-    const double k0 = odd ? dq[1] : dq[0], k1 = odd ? dq[3] : dq[2];
-    const double s0 = odd ? dq[0] : dq[1], s1 = odd ? dq[2] : dq[3];
-    const double p0 = k0 + quad_perm_dpp<0xB1>(s0), p1 = k1 + quad_perm_dpp<0xB1>(s1);
-    const double keep = hi ? p1 : p0, send = hi ? p0 : p1;
-    dsum = (keep + quad_perm_dpp<0x4E>(send)) + dsum;
-  }
+  const double dsum = quad_sum(dq);
   if (live) a.own[(size_t)cell * 4 + v] = gsum - dsum;
   wave_lds_sync();
   double* __restrict__ tb = a.tbar + (size_t)tile * a.ustride * 4;
@@ -2062,68 +2211,62 @@ struct BatchMeshDev {
   int n_bface;
 };
 
-// Runs reconstruct_tile for pq (any supported pair when PQ == 0, otherwise
-// only PQ, so a per-order launch keeps that order's register budget).
-template <int PQ>
-__device__ __forceinline__ void batch_tile(int pq, const ReconArgs& a, int tile, int lane,
-                                           int4* stage) {
-  if (PQ != 0) pq = PQ;
-  switch (pq) {
-    case 32: reconstruct_tile<3, 2>(a, tile, lane, stage); break;
-    case 42: reconstruct_tile<4, 2>(a, tile, lane, stage); break;
-    case 53: reconstruct_tile<5, 3>(a, tile, lane, stage); break;
-    case 63: reconstruct_tile<6, 3>(a, tile, lane, stage); break;
-    case 33: if (PQ == 0 || PQ == 33) reconstruct_tile<3, 3>(a, tile, lane, stage); break;
-    case 43: if (PQ == 0 || PQ == 43) reconstruct_tile<4, 3>(a, tile, lane, stage); break;
-    case 52: if (PQ == 0 || PQ == 52) reconstruct_tile<5, 2>(a, tile, lane, stage); break;
-    case 62: if (PQ == 0 || PQ == 62) reconstruct_tile<6, 2>(a, tile, lane, stage); break;
-    default: break;
+// Items of a batch's work list: (mesh, block).
+struct BatchItems {
+  const BatchMeshDev* __restrict__ meshes;
+  const int2* __restrict__ items;
+  int stage_k;
+  __device__ __forceinline__ TENO_CONST ReconArgs& args(int k) const {
+    const int m = scalar_load(reinterpret_cast<const int*>(items), 2 * k);
+    return *(TENO_CONST ReconArgs*)(uintptr_t)&meshes[m].r[stage_k];
   }
-}
-
-// Persistent reconstruction over a work list of (mesh, tile) items: each
-// wavefront takes the contiguous, cost-balanced item range
-// [wave_start[w], wave_start[w+1]) and leaves when it is done.
-template <int PQ>
-__global__ __launch_bounds__(256) void k_batch_reconstruct(const BatchMeshDev* __restrict__ meshes,
-                                                           const int2* __restrict__ items,
-                                                           const int* __restrict__ wave_start,
-                                                           int n_waves, int stage_k,
-                                                           int lds_stride) {
-  extern __shared__ int4 lds[];  // 4 wavefronts x lds_stride (the largest mesh's)
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int w = xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
-  if (w >= n_waves) return;
-  const int i0 = wave_start[w], i1 = wave_start[w + 1];
-  for (int i = i0; i < i1; ++i) {
-    const int2 it = items[i];
-    const int m = __builtin_amdgcn_readfirstlane(it.x);
-    const int tile = __builtin_amdgcn_readfirstlane(it.y);
-    const BatchMeshDev& d = meshes[m];
-    batch_tile<PQ>(d.pq, d.r[stage_k], tile, lane, lds + wave * lds_stride);
+  __device__ __forceinline__ int block(int k) const {
+    return scalar_load(reinterpret_cast<const int*>(items), 2 * k + 1);
   }
-}
+};
 
-// The same with one (mesh, tile) item per wavefront and no loop.  In the
-// persistent form the compiler hoists the constant tables' addresses out of
-// the item loop and holds them, spilling scalar registers into vector ones
-// (141 VGPRs at order 5 against 104 for one mesh); without the loop it keeps
-// the single-mesh kernel's budget.
-// Blocks of kReconBlockWaves wavefronts, as for one mesh.
+// Reconstruction over items of one order and face-point count.  start: each
+// workgroup takes the contiguous, cost-balanced range [start[w], start[w+1]);
+// null: the n_items items are dealt out in turn.
 template <int PQ>
-__global__ __launch_bounds__(64 * kReconBlockWaves)
-void k_batch_reconstruct_one(const BatchMeshDev* __restrict__ meshes,
-                             const int2* __restrict__ items, int n_items, int stage_k,
-                             int lds_stride) {
+__global__ __launch_bounds__(64 * block_tiles(PQ / 10))
+__attribute__((amdgpu_waves_per_eu(recon_waves(PQ / 10)))) void k_batch_reconstruct(
+    const BatchMeshDev* __restrict__ meshes, const int2* __restrict__ items,
+    const int* __restrict__ start, int n_items, int stage_k) {
   extern __shared__ int4 lds[];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int w = xcd_remap(blockIdx.x, gridDim.x) * kReconBlockWaves + wave;
-  if (w >= n_items) return;
-  const int2 it = items[w];
-  const int m = __builtin_amdgcn_readfirstlane(it.x);
-  const int tile = __builtin_amdgcn_readfirstlane(it.y);
-  const BatchMeshDev& d = meshes[m];
-  batch_tile<PQ>(d.pq, d.r[stage_k], tile, lane, lds + wave * lds_stride);
+  const int w = xcd_remap(blockIdx.x, gridDim.x);
+  const BatchItems it{meshes, items, stage_k};
+  reconstruct_loop<PQ / 10, PQ % 10, false, false>(it, start ? start[w] : w,
+                                                   start ? start[w + 1] : n_items,
+                                                   start ? 1 : (int)gridDim.x,
+                                                   reinterpret_cast<char*>(lds));
+}
+
+// One launch for every order: each item is dispatched by its mesh's order, one at
+// a time (the pipeline of reconstruct_loop runs within one order).
+__global__ __launch_bounds__(64 * kMaxBlockTiles) __attribute__((amdgpu_waves_per_eu(2)))
+void k_batch_reconstruct_all(const BatchMeshDev* __restrict__ meshes,
+                             const int2* __restrict__ items, const int* __restrict__ start,
+                             int stage_k) {
+  extern __shared__ int4 lds4[];
+  char* lds = reinterpret_cast<char*>(lds4);
+  const int w = xcd_remap(blockIdx.x, gridDim.x);
+  const int i0 = start ? start[w] : w, i1 = start ? start[w + 1] : w + 1;
+  for (int i = i0; i < i1; ++i) {
+    if (i > i0) __syncthreads();  // the previous item's staged members are read
+    const BatchItems it{meshes, items, stage_k};
+    switch (meshes[__builtin_amdgcn_readfirstlane(items[i].x)].pq) {
+      case 32: reconstruct_loop<3, 2, false, false>(it, i, i + 1, 1, lds); break;
+      case 33: reconstruct_loop<3, 3, false, false>(it, i, i + 1, 1, lds); break;
+      case 42: reconstruct_loop<4, 2, false, false>(it, i, i + 1, 1, lds); break;
+      case 43: reconstruct_loop<4, 3, false, false>(it, i, i + 1, 1, lds); break;
+      case 52: reconstruct_loop<5, 2, false, false>(it, i, i + 1, 1, lds); break;
+      case 53: reconstruct_loop<5, 3, false, false>(it, i, i + 1, 1, lds); break;
+      case 62: reconstruct_loop<6, 2, false, false>(it, i, i + 1, 1, lds); break;
+      case 63: reconstruct_loop<6, 3, false, false>(it, i, i + 1, 1, lds); break;
+      default: break;
+    }
+  }
 }
 
 // Persistent face fluxes over (mesh, 64-face chunk) items.

@@ -503,6 +503,402 @@ static uint32_t spread16(uint32_t x) {
   return x;
 }
 
+// ---------------------------------------------------------------------------
+// matrix-free least squares: block member lists, geometry records and the
+// inverses of the normal matrices
+// ---------------------------------------------------------------------------
+// The operators a = M d of the least squares are never stored on the device:
+// with rows A_s (moments of the member about the target, in any basis) and
+// weights |V_s|, a = (sum_s |V_s|^2 A_s A_s^T)^-1 sum_s |V_s|^2 A_s d_s.  The
+// normal matrix squares the condition of the rows, so the basis is chosen to
+// be almost orthogonal over the stencil: the frame of a block whitens the
+// displacements of its stencils (also on stretched and sheared meshes), the
+// polynomials are Hermite's, and each stencil's are centred on its members'
+// mean (one-sided small stencils, stencils at a wall).  The matrices are formed
+// and inverted in extended precision and stored in FP64.  Against quad
+// precision the face values of random data come out closer than with the
+// stored operators of the reference triangle's monomials (rms, orders 3-6:
+// x 0.3-0.02), and the rounding noise of their sums is x 0.7-1.9 of a
+// plain product M d (orders 3-6, boxes included; monomials about the target
+// would give x 2-55).
+typedef long double Ext;
+
+// E[H_a(x + X) H_b(y + Y)] for 0 <= a + b <= r from the central moments
+// mu[a][b] = E[H_a(X) H_b(Y)] (the binomial shift of an Appell sequence)
+static void shift_moments(int r, Ext x, Ext y, const Ext (&mu)[6][6], Ext (&out)[6][6]) {
+  Ext t[6][6];
+  for (int b = 0; b <= r; ++b) {
+    Ext v[6];
+    const int n = r - b;
+    for (int a = 0; a <= n; ++a) v[a] = mu[a][b];
+    for (int i = 1; i <= n; ++i)
+      for (int a = n; a >= i; --a) v[a] += x * v[a - 1];
+    for (int a = 0; a <= n; ++a) t[a][b] = v[a];
+  }
+  for (int a = 0; a <= r; ++a) {
+    Ext v[6];
+    const int n = r - a;
+    for (int b = 0; b <= n; ++b) v[b] = t[a][b];
+    for (int i = 1; i <= n; ++i)
+      for (int b = n; b >= i; --b) v[b] += y * v[b - 1];
+    for (int b = 0; b <= n; ++b) out[a][b] = v[b];
+  }
+}
+
+// X = (A^T A)^-1 of the m x n row-major A: Cholesky, or the triangular factor
+// of a Householder QR where the normal matrix breaks down.
+void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& X) {
+  std::vector<Ext> L((size_t)n * n, 0);
+  bool ok = true;
+  for (int j = 0; j < n && ok; ++j)
+    for (int i = j; i < n; ++i) {
+      Ext s = 0;
+      for (int k = 0; k < m; ++k) s += A[(size_t)k * n + i] * A[(size_t)k * n + j];
+      const Ext d0 = s;
+      for (int k = 0; k < j; ++k) s -= L[(size_t)i * n + k] * L[(size_t)j * n + k];
+      if (i == j) {
+        if (!(s > d0 * 1e-16L)) {
+          ok = false;
+          break;
+        }
+        L[(size_t)j * n + j] = std::sqrt(s);
+      } else {
+        L[(size_t)i * n + j] = s / L[(size_t)j * n + j];
+      }
+    }
+  if (!ok) {
+    for (int j = 0; j < n; ++j) {
+      Ext nrm = 0;
+      for (int i = j; i < m; ++i) nrm += A[(size_t)i * n + j] * A[(size_t)i * n + j];
+      nrm = std::sqrt(nrm);
+      const Ext alpha = A[(size_t)j * n + j] > 0 ? -nrm : nrm;
+      A[(size_t)j * n + j] -= alpha;
+      Ext vv = 0;
+      for (int i = j; i < m; ++i) vv += A[(size_t)i * n + j] * A[(size_t)i * n + j];
+      for (int c = j + 1; c < n && vv > 0; ++c) {
+        Ext s = 0;
+        for (int i = j; i < m; ++i) s += A[(size_t)i * n + j] * A[(size_t)i * n + c];
+        s *= 2 / vv;
+        for (int i = j; i < m; ++i) A[(size_t)i * n + c] -= s * A[(size_t)i * n + j];
+      }
+      L[(size_t)j * n + j] = alpha;
+      for (int c = j + 1; c < n; ++c) L[(size_t)c * n + j] = A[(size_t)j * n + c];  // L = R^T
+    }
+  }
+  // L^-1 (lower triangular), then X = L^-T L^-1
+  std::vector<Ext> Li((size_t)n * n, 0);
+  for (int c = 0; c < n; ++c)
+    for (int i = c; i < n; ++i) {
+      Ext s = i == c ? 1 : 0;
+      for (int k = c; k < i; ++k) s -= L[(size_t)i * n + k] * Li[(size_t)k * n + c];
+      Li[(size_t)i * n + c] = s / L[(size_t)i * n + i];
+    }
+  X.assign((size_t)n * n, 0);
+  for (int i = 0; i < n; ++i)
+    for (int j = i; j < n; ++j) {
+      Ext s = 0;
+      for (int k = j; k < n; ++k) s += Li[(size_t)k * n + i] * Li[(size_t)k * n + j];
+      X[(size_t)i * n + j] = X[(size_t)j * n + i] = s;
+    }
+}
+
+// A stencil member as a block sees it: the cell and its periodic image.
+struct Image {
+  int32_t id;
+  int kx, ky;
+  bool operator<(const Image& o) const {
+    return id != o.id ? id < o.id : (kx != o.kx ? kx < o.kx : ky < o.ky);
+  }
+  bool operator==(const Image& o) const { return id == o.id && kx == o.kx && ky == o.ky; }
+};
+
+// Packed order of positions [lo, hi): bisection along the longer side of the
+// box of the centroids (wrapped on periodic axes), at multiples of `unit` cells
+// down to one block, then of a tile.
+static void pack_bisect(Mesh& m, int lo, int hi, int unit, int threads) {
+  if (hi - lo <= unit) {
+    if (unit > kTile) pack_bisect(m, lo, hi, kTile, 1);
+    return;
+  }
+  auto at = [&](int i, int a) { return bin_coord(m, a, m.cen[2 * (size_t)m.perm[i] + a]); };
+  double mn[2] = {INFINITY, INFINITY}, mx[2] = {-INFINITY, -INFINITY};
+  for (int k = lo; k < hi; ++k)
+    for (int a = 0; a < 2; ++a) {
+      const double x = at(m.pack[k], a);
+      mn[a] = std::min(mn[a], x);
+      mx[a] = std::max(mx[a], x);
+    }
+  const int a = mx[1] - mn[1] > mx[0] - mn[0] ? 1 : 0;
+  const int nb = (hi - lo + unit - 1) / unit, mid = lo + (nb / 2) * unit;
+  std::nth_element(m.pack.begin() + lo, m.pack.begin() + mid, m.pack.begin() + hi, [&](int x, int y) {
+    const double dx = at(x, a), dy = at(y, a);
+    return dx < dy || (dx == dy && x < y);
+  });
+  if (threads > 1 && hi - lo > 4096) {
+    std::thread left([&]() { pack_bisect(m, lo, mid, unit, threads / 2); });
+    pack_bisect(m, mid, hi, unit, threads - threads / 2);
+    left.join();
+  } else {
+    pack_bisect(m, lo, mid, unit, 1);
+    pack_bisect(m, mid, hi, unit, 1);
+  }
+}
+
+static void pack_blocks(Mesh& m) {
+  const Dims& d = m.d;
+  const int nc = m.nc, r = d.r, nu = d.nu, units = rec_units(nu);
+  // images relative to the origin cell o (both internal): K of cell j
+  auto image_of = [&](int j, int o, int& kx, int& ky) {
+    const int uj = m.perm[j], uo = m.perm[o];
+    double dx = m.cen[2 * (size_t)uj] - m.cen[2 * (size_t)uo];
+    double dy = m.cen[2 * (size_t)uj + 1] - m.cen[2 * (size_t)uo + 1], fx, fy;
+    wrap_delta(m, dx, dy, fx, fy);
+    kx = (int)fx;
+    ky = (int)fy;
+  };
+  m.pack.assign(m.n_pad, -1);
+  std::vector<std::vector<Image>> lists;
+  int n_blocks = 0;
+  // as many tiles per block as the LDS allows
+  for (m.bwaves = block_tiles(d.order), m.nbuf = 2;;) {
+    const int W = m.bwaves, cells = W * kTile;
+    n_blocks = (m.n_tiles + W - 1) / W;
+    for (int t = 0; t < nc; ++t) m.pack[t] = t;
+    pack_bisect(m, 0, nc, cells,
+                m.prm.n_threads > 0 ? m.prm.n_threads : (int)std::max(1u, std::thread::hardware_concurrency()));
+    for (int t = 0; t < nc; t += kTile)
+      std::sort(m.pack.begin() + t, m.pack.begin() + std::min(nc, t + kTile));
+    lists.assign(n_blocks, {});
+    std::atomic<int> top{0};
+    parallel_for(n_blocks, m.prm.n_threads, [&](int b) {
+      std::vector<Image>& u = lists[b];
+      const int t0 = b * cells, t1 = std::min(nc, t0 + cells), origin = m.pack[t0];
+      std::vector<Image> own(cells);
+      for (int c = 0; c < cells; ++c) {
+        Image& im = own[c];
+        im.id = m.pack[std::min(t0 + c, nc - 1)];
+        image_of(im.id, origin, im.kx, im.ky);
+      }
+      for (int t = t0; t < t1; ++t)
+        for (int row = 0; row < d.rows; ++row) {
+          Image im;
+          im.id = m.idx[packed_idx_index(m, m.pack[t], row)];
+          image_of(im.id, m.pack[t], im.kx, im.ky);
+          im.kx += own[t - t0].kx;
+          im.ky += own[t - t0].ky;
+          u.push_back(im);
+        }
+      std::sort(u.begin(), u.end());
+      u.erase(std::unique(u.begin(), u.end()), u.end());
+      std::vector<Image> so(own);
+      std::sort(so.begin(), so.end());
+      u.erase(std::remove_if(u.begin(), u.end(),
+                             [&](const Image& x) { return std::binary_search(so.begin(), so.end(), x); }),
+              u.end());
+      u.insert(u.begin(), own.begin(), own.end());
+      int cur = top.load();
+      while ((int)u.size() > cur && !top.compare_exchange_weak(cur, (int)u.size())) {
+      }
+    });
+    m.bmax = top.load();
+    if (group_lds_bytes(nu, m.bmax, m.nbuf) <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || W == 1)
+      break;
+    // two buffers do not fit: one, in workgroups of four or fewer
+    if (m.nbuf == 2 && W == 4) {
+      m.nbuf = 1;
+    } else {
+      m.nbuf = 1;
+      m.bwaves = W / 2;
+    }
+  }
+  m.boff.assign(n_blocks + 1, 0);
+  for (int b = 0; b < n_blocks; ++b) m.boff[b + 1] = m.boff[b] + (int32_t)lists[b].size();
+  m.bmem.assign((size_t)n_blocks * m.bmax, 0);
+  m.brec.resize((size_t)m.boff[n_blocks] * units * 2);
+  const int nw = slot_words(d.nl), nq4 = normal_quads(nu);
+  m.bslot.assign((size_t)m.n_tiles * nw * 64, 0);
+  m.N.resize((size_t)m.n_tiles * nq4 * 128);
+  m.jac.resize((size_t)m.n_pad * 4);
+  m.centre.assign((size_t)m.n_pad * 8, 0.0f);
+  // Radon's rule of degree 5, exact for every moment needed
+  Ext rl[7][3], rw[7];
+  {
+    const Ext s15 = std::sqrt((Ext)15);
+    const Ext a1 = (6 - s15) / 21, a2 = (6 + s15) / 21;
+    rw[0] = (Ext)9 / 40;
+    rl[0][0] = rl[0][1] = rl[0][2] = (Ext)1 / 3;
+    for (int h = 0; h < 2; ++h)
+      for (int k = 0; k < 3; ++k) {
+        const Ext a = h ? a2 : a1;
+        for (int j = 0; j < 3; ++j) rl[1 + 3 * h + k][j] = j == k ? 1 - 2 * a : a;
+        rw[1 + 3 * h + k] = (h ? 155 + s15 : 155 - s15) / 1200;
+      }
+  }
+  parallel_for(n_blocks, m.prm.n_threads, [&](int b) {
+    const std::vector<Image>& u = lists[b];
+    const int cells = m.bwaves * kTile;
+    const int t0 = b * cells, t1 = std::min(nc, t0 + cells);
+    // ---- frame: whitens the displacements of the large stencils ----
+    double cxx = 0, cxy = 0, cyy = 0;
+    for (int t = t0; t < t1; ++t)
+      for (int s = 0; s < d.nl; ++s) {
+        const int ui = m.perm[m.pack[t]];
+        const int uj = m.perm[m.idx[packed_idx_index(m, m.pack[t], large_row(s))]];
+        double dx = m.cen[2 * (size_t)uj] - m.cen[2 * (size_t)ui];
+        double dy = m.cen[2 * (size_t)uj + 1] - m.cen[2 * (size_t)ui + 1], kx, ky;
+        wrap_delta(m, dx, dy, kx, ky);
+        cxx += dx * dx;
+        cxy += dx * dy;
+        cyy += dy * dy;
+      }
+    const double n0 = (double)(t1 - t0) * d.nl;
+    const double l11 = std::sqrt(cxx / n0), l21 = cxy / n0 / l11;
+    double l22 = std::sqrt(std::max(0.0, cyy / n0 - l21 * l21));
+    if (!(l22 > 1e-12 * l11)) l22 = l11;
+    const Ext f00 = 1 / (Ext)l11, f10 = -(Ext)l21 / ((Ext)l11 * l22), f11 = 1 / (Ext)l22;
+    // ---- records ----
+    const double* Xo = &m.X[6 * (size_t)m.perm[m.pack[t0]]];
+    const Ext o[2] = {((Ext)Xo[0] + Xo[2] + Xo[4]) / 3, ((Ext)Xo[1] + Xo[3] + Xo[5]) / 3};
+    std::vector<double> rec(u.size() * (nu + 1));
+    for (size_t k = 0; k < u.size(); ++k) {
+      const double* Xj = &m.X[6 * (size_t)m.perm[u[k].id]];
+      Ext q[3][2], c[2] = {0, 0};
+      for (int v = 0; v < 3; ++v) {
+        const Ext px = (Ext)Xj[2 * v] - (Ext)m.P[0] * u[k].kx - o[0];
+        const Ext py = (Ext)Xj[2 * v + 1] - (Ext)m.P[1] * u[k].ky - o[1];
+        q[v][0] = f00 * px;
+        q[v][1] = f10 * px + f11 * py;
+        c[0] += q[v][0] / 3;
+        c[1] += q[v][1] / 3;
+      }
+      for (int v = 0; v < 3; ++v)
+        for (int a = 0; a < 2; ++a) q[v][a] -= c[a];
+      const Ext vol = ((q[1][0] - q[0][0]) * (q[2][1] - q[0][1]) -
+                       (q[2][0] - q[0][0]) * (q[1][1] - q[0][1])) / 2;
+      double* R = &rec[k * (nu + 1)];
+      R[0] = (double)c[0];
+      R[1] = (double)c[1];
+      R[2] = (double)(vol * vol);
+      Ext hx[7][6], hy[7][6];
+      for (int g = 0; g < 7; ++g) {
+        Ext x = 0, y = 0;
+        for (int v = 0; v < 3; ++v) {
+          x += rl[g][v] * q[v][0];
+          y += rl[g][v] * q[v][1];
+        }
+        hx[g][0] = hy[g][0] = 1;
+        hx[g][1] = x;
+        hy[g][1] = y;
+        for (int n = 2; n <= r; ++n) {
+          hx[g][n] = x * hx[g][n - 1] - (Ext)kHermite * (n - 1) * hx[g][n - 2];
+          hy[g][n] = y * hy[g][n - 1] - (Ext)kHermite * (n - 1) * hy[g][n - 2];
+        }
+      }
+      int l = 3;
+      for (int deg = 2; deg <= r; ++deg)
+        for (int e = deg; e >= 0; --e, ++l) {
+          Ext s = 0;
+          for (int g = 0; g < 7; ++g) s += rw[g] * hx[g][e] * hy[g][deg - e];
+          R[l] = (double)s;
+        }
+      m.bmem[(size_t)b * m.bmax + k] = u[k].id;
+      double* out = &m.brec[((size_t)m.boff[b] + k) * units * 2];
+      for (int x = 0; x < units * 2; ++x) out[x] = x < nu + 1 ? R[x] : 0.0;
+    }
+    // ---- slots and normal inverses ----
+    auto moments = [&](int k, Ext (&mu)[6][6]) {
+      const double* R = &rec[(size_t)k * (nu + 1)];
+      mu[0][0] = 1;
+      mu[1][0] = mu[0][1] = 0;
+      int l = 3;
+      for (int deg = 2; deg <= r; ++deg)
+        for (int e = deg; e >= 0; --e, ++l) mu[e][deg - e] = R[l];
+    };
+    std::vector<Ext> A, X;
+    for (int c = 0; c < cells; ++c) {
+      const int t = t0 + c, tile = t / kTile, tc = t % kTile;
+      if (tile >= m.n_tiles) break;
+      const bool live = t < nc;
+      uint32_t* sl = &m.bslot[(size_t)tile * nw * 64];
+      auto put = [&](int lane, int grp, int slot) {
+        uint32_t& w = sl[(size_t)(grp / 3) * 64 + lane];
+        const int sh = kSlotBits * (grp % 3);
+        w = (w & ~(((1u << kSlotBits) - 1) << sh)) | (uint32_t)slot << sh;
+      };
+      for (int g = 0; g < 4; ++g)
+        for (int grp = 0; grp < nw * 3; ++grp) put(tc * 4 + g, grp, c);
+      double* Nt = &m.N[(size_t)tile * nq4 * 128];
+      for (int q = 0; q < nq4; ++q)
+        for (int x = 0; x < 8; ++x) Nt[(size_t)q * 128 + tc * 8 + x] = 0.0;
+      double* J = &m.jac[(size_t)t * 4];
+      J[0] = J[3] = 1.0;
+      J[1] = J[2] = 0.0;
+      if (!live) continue;
+      {
+        const double* Xi = &m.X[6 * (size_t)m.perm[m.pack[t]]];
+        for (int v = 0; v < 2; ++v) {
+          const Ext ex = ((Ext)Xi[2 * v + 2] - Xi[0]) / 3, ey = ((Ext)Xi[2 * v + 3] - Xi[1]) / 3;
+          J[v] = (double)(f00 * ex);
+          J[2 + v] = (double)(f10 * ex + f11 * ey);
+        }
+      }
+      Ext mu0[6][6], own[6][6];
+      moments(c, mu0);
+      const double* R0 = &rec[(size_t)c * (nu + 1)];
+      int grp0 = 0, quad0 = 0;
+      std::vector<int> slots(d.nl);
+      for (int k = 0; k < 4; ++k) {
+        const bool big = k == 3;
+        const int nrow = big ? d.nl : kSmallRows, n = big ? nu : kSmallCoef, rk = big ? r : 2;
+        A.assign((size_t)nrow * n, 0);
+        Ext cx = 0, cy = 0;
+        slots.resize(std::max(nrow, d.nl));
+        for (int s = 0; s < nrow; ++s) {
+          Image im;
+          im.id = m.idx[packed_idx_index(m, m.pack[t], big ? large_row(s) : small_row(k, s))];
+          image_of(im.id, m.pack[t], im.kx, im.ky);
+          im.kx += u[c].kx;
+          im.ky += u[c].ky;
+          // a member among the block's own cells, or in the sorted rest
+          auto at = std::lower_bound(u.begin() + cells, u.end(), im);
+          if (at == u.end() || !(*at == im)) at = std::find(u.begin(), u.begin() + cells, im);
+          const int slot = (int)(at - u.begin());
+          put(tc * 4 + s % 4, grp0 + s / 4, slot);
+          slots[s] = slot;
+          const double* R = &rec[(size_t)slot * (nu + 1)];
+          cx += ((Ext)R[0] - R0[0]) / nrow;
+          cy += ((Ext)R[1] - R0[1]) / nrow;
+        }
+        // the centre; a large stencil's that is nearly the target's centroid
+        // is taken there (the kernel then skips the shift back)
+        if (big && cx * cx + cy * cy < 0.04L) cx = cy = 0;
+        const float fx = (float)cx, fy = (float)cy;
+        m.centre[((size_t)t * 4 + k) * 2] = fx;
+        m.centre[((size_t)t * 4 + k) * 2 + 1] = fy;
+        shift_moments(rk, -(Ext)fx, -(Ext)fy, mu0, own);
+        for (int s = 0; s < nrow; ++s) {
+          Ext mu[6][6], sh[6][6];
+          moments(slots[s], mu);
+          const double* R = &rec[(size_t)slots[s] * (nu + 1)];
+          shift_moments(rk, (Ext)R[0] - R0[0] - fx, (Ext)R[1] - R0[1] - fy, mu, sh);
+          const Ext w = std::sqrt((Ext)R[2]);
+          int l = 0;
+          for (int deg = 1; deg <= rk; ++deg)
+            for (int e = deg; e >= 0; --e, ++l)
+              A[(size_t)s * n + l] = w * (sh[e][deg - e] - own[e][deg - e]);
+        }
+        normal_inverse(nrow, n, A, X);
+        int j = 0;
+        for (int i = 0; i < n; ++i)
+          for (int q = i; q < n; ++q, ++j)
+            Nt[(size_t)(quad0 + j / 8) * 128 + tc * 8 + j % 8] = (double)X[(size_t)i * n + q];
+        grp0 += row_groups(nrow);
+        quad0 += sym_quads(n);
+      }
+    }
+  });
+}
+
 int mesh_setup(Mesh& m, const teno_params& p) {
   if (p.order < 3 || p.order > 6) return fail(TENO_EARG, "order must be 3..6");
   if (p.variant < 0 || p.variant > 2) return fail(TENO_EARG, "variant must be 0, 1 or 2");
@@ -686,66 +1082,67 @@ int mesh_setup(Mesh& m, const teno_params& p) {
     }
   }
 
-  // ---- distinct stencil members per tile and their LDS slots ----
+  // ---- distinct stencil members of 16 consecutive cells: a shuffled order is
+  //      refused ----
+  {
+    std::atomic<int> top{1};
+    parallel_for(m.n_tiles, p.n_threads, [&](int tile) {
+      std::vector<int32_t> u;
+      for (int t = tile * kTile; t < std::min(nc, (tile + 1) * kTile); ++t)
+        for (int r = 0; r < d.rows; ++r) u.push_back(m.idx[packed_idx_index(m, t, r)]);
+      std::sort(u.begin(), u.end());
+      const int n = (int)(std::unique(u.begin(), u.end()) - u.begin());
+      int cur = top.load();
+      while (n > cur && !top.compare_exchange_weak(cur, n)) {
+      }
+    });
+    if (top.load() > kMaxTileMembers)
+      return fail(TENO_ESTENCIL, "a 16-cell tile has " + std::to_string(top.load()) +
+                                     " distinct stencil members (limit " +
+                                     std::to_string(kMaxTileMembers) +
+                                     "); keep the default cell reordering");
+  }
+  pack_blocks(m);
+
+  // ---- distinct members of each (packed) tile, the adjoint's accumulators ----
   {
     std::vector<std::vector<int32_t>> lists(m.n_tiles);
     std::atomic<int> umax{1};
-    m.slot.assign(m.idx.size(), 0);
-    m.aslot.assign(m.idx.size(), 0);
-    m.tround.assign(m.n_tiles, 1);
+    const int nw = adj_words(d.nl);
+    m.aslot.assign((size_t)m.n_tiles * nw * 64, 0);
     parallel_for(m.n_tiles, p.n_threads, [&](int tile) {
       std::vector<int32_t>& u = lists[tile];
-      for (int c = 0; c < kTile; ++c) {
-        const int t = tile * kTile + c;
-        if (t >= nc) break;
-        for (int r = 0; r < d.rows; ++r) u.push_back(m.idx[packed_idx_index(m, t, r)]);
-      }
+      for (int t = tile * kTile; t < std::min(nc, (tile + 1) * kTile); ++t)
+        for (int r = 0; r < d.rows; ++r) u.push_back(m.idx[packed_idx_index(m, m.pack[t], r)]);
       std::sort(u.begin(), u.end());
       u.erase(std::unique(u.begin(), u.end()), u.end());
       int cur = umax.load();
       while ((int)u.size() > cur && !umax.compare_exchange_weak(cur, (int)u.size())) {
       }
-      for (int c = 0; c < kTile; ++c) {
-        const int t = tile * kTile + c;
-        if (t >= nc) break;
-        for (int r = 0; r < d.rows; ++r) {
-          const int64_t k = packed_idx_index(m, t, r);
-          m.slot[k] = (uint16_t)(std::lower_bound(u.begin(), u.end(), m.idx[k]) - u.begin());
+      // each row's slot in the tile's list and the round of the adjoint's
+      // addition: the rows 4j..4j+3 of a stencil are added by all cells at
+      // once (lane order c * 4 + g), and the lanes of such a group that name
+      // the same member add in lane order, one round each, so that no two
+      // lanes of one LDS instruction hit the same address
+      uint32_t* as = &m.aslot[(size_t)tile * nw * 64];
+      std::vector<uint16_t> seen(u.size());
+      int grp = 0;
+      for (int k = 0; k < 4; ++k) {
+        const int r0 = k == 3 ? large_row(0) : small_row(k, 0), nrow = k == 3 ? d.nl : kSmallRows;
+        for (int j = 0; j < row_groups(nrow); ++j, ++grp) {
+          std::fill(seen.begin(), seen.end(), 0);
+          for (int lane = 0; lane < 64; ++lane) {
+            const int t = tile * kTile + lane / 4, row = 4 * j + lane % 4;
+            if (t >= nc || row >= nrow) continue;
+            const int id = m.idx[packed_idx_index(m, m.pack[t], r0 + row)];
+            const int s = (int)(std::lower_bound(u.begin(), u.end(), id) - u.begin());
+            as[(size_t)(grp / 2) * 64 + lane] |= (uint32_t)((s & 511) | seen[s]++ << 9) << (16 * (grp % 2));
+          }
         }
       }
-      // rounds of the adjoint's additions, so that no two lanes of one LDS
-      // instruction hit the same address: a block stored rows by lane adds
-      // four rows of every cell at once (rows 4j..4j+3 of the block, lane
-      // order c * 4 + g), and the lanes of such a group that name the same
-      // member add in lane order, one round each; a block of entry pairs
-      // adds one row at a time, and the cells that name the same member in
-      // that row add in cell order
-      int top = 1;
-      auto rounds = [&](int r0, int nrow, bool by_lane) {
-        const int span = by_lane ? 4 : 1;
-        for (int j = 0; j * span < nrow; ++j) {
-          const int rg = std::min(span, nrow - j * span);
-          for (int c = 0; c < kTile && tile * kTile + c < nc; ++c)
-            for (int gq = 0; gq < rg; ++gq) {
-              const int64_t k = packed_idx_index(m, tile * kTile + c, r0 + j * span + gq);
-              int q = 0;
-              for (int c2 = 0; c2 <= c; ++c2)
-                for (int g2 = 0; g2 < rg && (c2 < c || g2 < gq); ++g2)
-                  if (m.slot[packed_idx_index(m, tile * kTile + c2, r0 + j * span + g2)] == m.slot[k]) ++q;
-              m.aslot[k] = (uint16_t)(m.slot[k] | q << 9);
-              top = std::max(top, q + 1);
-            }
-        }
-      };
-      for (int k = 0; k < 3; ++k) rounds(small_row(k, 0), kSmallRows, lane_rows(kSmallCoef, d.dense));
-      rounds(large_row(0), d.nl, large_lane_rows(d.nu, d.dense));
-      m.tround[tile] = top;
     });
-    if (umax.load() > kMaxTileMembers)
-      return fail(TENO_ESTENCIL, "a 16-cell tile has " + std::to_string(umax.load()) +
-                                     " distinct stencil members (limit " +
-                                     std::to_string(kMaxTileMembers) +
-                                     "); keep the default cell reordering");
+    if (umax.load() > 512)
+      return fail(TENO_ESTENCIL, "a tile has more than 512 distinct stencil members");
     m.ustride = (umax.load() + 15) / 16 * 16;
     m.tmem.assign((size_t)m.n_tiles * m.ustride, 0);
     m.tcount.assign(m.n_tiles, 0);

@@ -30,8 +30,8 @@ constexpr double cx_sqrt(double x) {
   return y;
 }
 
-// Monomials xi^a eta^b with 1 <= a+b <= r in graded order
-// (xi, eta, xi^2, xi eta, eta^2, xi^3, ...).
+// Exponents (a, b) of the monomials with 1 <= a+b <= r in graded order
+// (X, Y, X^2, X Y, Y^2, X^3, ...).
 struct Exps {
   int a[20] = {};
   int b[20] = {};
@@ -49,8 +49,39 @@ constexpr Exps cx_exps(int r) {
   return e;
 }
 
-// int over the reference triangle of xi^a eta^b = a! b! / (a+b+2)!
-constexpr double cx_moment(int a, int b) { return cx_fact(a) * cx_fact(b) / cx_fact(a + b + 2); }
+// The basis on the reference triangle: monomials in X = 3 xi - 1 and
+// Y = 3 eta - 1 (centred on the centroid), minus their means.
+
+// int over the reference triangle of X^a Y^b: a sum of integers
+// C(a,p) C(b,q) 3^(p+q) (-1)^(a-p+b-q) p! q! (a+b+2)! / (p+q+2)!, each exact
+// in FP64, over (a+b+2)!
+constexpr double cx_moment(int a, int b) {
+  double s = 0.0;
+  for (int p = 0; p <= a; ++p)
+    for (int q = 0; q <= b; ++q) {
+      double t = cx_fact(a) / (cx_fact(p) * cx_fact(a - p)) * (cx_fact(b) / (cx_fact(q) * cx_fact(b - q)));
+      for (int k = 0; k < p + q; ++k) t *= 3.0;
+      t *= cx_fact(p) * cx_fact(q);
+      for (int k = p + q + 3; k <= a + b + 2; ++k) t *= k;
+      s += ((a - p + b - q) & 1) ? -t : t;
+    }
+  return s / cx_fact(a + b + 2);
+}
+
+// Coefficient of x^(n-2k) in the monic Hermite polynomial H_n of variance
+// kHermite: (-variance/2)^k n! / (k! (n-2k)!)
+constexpr double cx_hermite(int n, int k) {
+  double t = cx_fact(n) / (cx_fact(k) * cx_fact(n - 2 * k));
+  for (int i = 0; i < k; ++i) t *= -0.5 * kHermite;
+  return t;
+}
+
+// 3^k (the derivatives of X and Y)
+constexpr double cx_pow3(int k) {
+  double t = 1.0;
+  for (int i = 0; i < k; ++i) t *= 3.0;
+  return t;
+}
 
 template <int R>
 struct SmoothForm {
@@ -72,7 +103,7 @@ struct SmoothForm {
             if (e.a[l] < ax || e.b[l] < ay || e.a[m] < ax || e.b[m] < ay) continue;
             const double cl = cx_falling(e.a[l], ax) * cx_falling(e.b[l], ay);
             const double cm = cx_falling(e.a[m], ax) * cx_falling(e.b[m], ay);
-            s += cl * cm * cx_moment(e.a[l] + e.a[m] - 2 * ax, e.b[l] + e.b[m] - 2 * ay);
+            s += cx_pow3(2 * d) * cl * cm * cx_moment(e.a[l] + e.a[m] - 2 * ax, e.b[l] + e.b[m] - 2 * ay);
           }
         M.v[l][m] = s;
       }
@@ -148,8 +179,8 @@ struct FaceBasis {
         const double eta = ed == 0 ? 0.0 : (ed == 1 ? t : 1.0 - t);
         for (int l = 0; l < N; ++l) {
           double p = 1.0;
-          for (int i = 0; i < e.a[l]; ++i) p *= xi;
-          for (int i = 0; i < e.b[l]; ++i) p *= eta;
+          for (int i = 0; i < e.a[l]; ++i) p *= 3.0 * xi - 1.0;
+          for (int i = 0; i < e.b[l]; ++i) p *= 3.0 * eta - 1.0;
           T.v[ed * NQ + k][l] = p - 2.0 * cx_moment(e.a[l], e.b[l]);
         }
       }
@@ -168,9 +199,6 @@ struct OrderT {
   static constexpr int ROWS = 33 + NL;
   static constexpr int ROWS4 = (ROWS + 3) / 4;
   static constexpr int J = 165 + NU * NL;         // operator entries
-  // stored entries per cell of a dense mesh (D) or of one on entry pairs
-  template <bool D>
-  static constexpr int JPD = 3 * small_block(D) + large_block(NL, NU, D);
 };
 
 }  // namespace teno

@@ -69,12 +69,19 @@ struct teno_solver {
   Dims d;
   teno_params prm{};
   int n_cell = 0, n_pad = 0, n_tiles = 0;
-  int4* slot = nullptr;     // member slots of each tile's stencil rows (uint16)
-  int4* aslot = nullptr;    // adjoint: member slot and accumulation round per row
-  int* tround = nullptr;    // adjoint: rounds per tile
-  int* tmem = nullptr;      // distinct stencil members of each tile
+  // blocks of the least-squares phase (internal.h)
+  int* boff = nullptr;
+  int* bmem = nullptr;
+  int* pack = nullptr;
+  double2* brec = nullptr;
+  unsigned* bslot = nullptr;
+  double2* N = nullptr;
+  double2* jac = nullptr;
+  float2* centre = nullptr;
+  int bwaves = 0, bmax = 0, nbuf = 2, n_blocks = 0;
+  int recon_groups = 1;     // reconstruction workgroups that the chip holds at once
+  unsigned* aslot = nullptr;    // adjoint: tile member slot and accumulation round per row
   int ustride = 0;
-  double2* M = nullptr;
   int4* nbinfo = nullptr;
   double* geo = nullptr;
   int4* fcell = nullptr;    // face-ordered flux data
@@ -181,6 +188,47 @@ static void set_tie_window(ReconArgs& a) {
   }
 }
 
+static BlockArgs block_args(const teno_solver* s) {
+  return {s->boff, s->bmem, s->brec, s->bslot, s->N, s->jac, s->centre, s->pack, s->bwaves, s->bmax, s->bmax, s->nbuf};
+}
+
+// Dynamic LDS of one reconstruction workgroup; in characteristic variables the
+// buffer of the current block also holds its Gram matrices.
+static size_t recon_lds(const Dims& d, int bwaves, int bmax, int nbuf, bool characteristic) {
+  size_t n = (size_t)group_lds_bytes(d.nu, bmax, nbuf);
+  if (characteristic) {
+    const size_t buf = (size_t)block_lds_bytes(d.nu, bmax);
+    const size_t gram = (size_t)bwaves * kCharGramDoubles * sizeof(double);
+    if (gram > buf) n += nbuf * (gram - buf);
+  }
+  return n;
+}
+static size_t recon_lds(const teno_solver* s) {
+  return recon_lds(s->d, s->bwaves, s->bmax, s->nbuf, s->prm.characteristic != 0);
+}
+
+// Workgroups of a kernel that the device holds at once.
+template <class K>
+static int resident_groups(K kernel, int threads, size_t lds, int device) {
+  int cus = 0, per = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) cus = 256;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, lds) != hipSuccess) per = 1;
+  return std::max(1, cus) * std::max(1, per);
+}
+
+// f(kernel) with the reconstruction kernel of a solver's order and scheme.
+template <class F>
+static void recon_kernel(const teno_solver* s, F&& f) {
+  const bool cw = s->prm.variant == 2, ch = s->prm.characteristic != 0;
+  dispatch(s->d.order, s->d.nq, [&](auto P, auto NQ) {
+    constexpr int p = decltype(P)::value, nq = decltype(NQ)::value;
+    if (ch && cw) f(k_reconstruct_char<p, nq, true>);
+    else if (ch) f(k_reconstruct_char<p, nq, false>);
+    else if (cw) f(k_reconstruct<p, nq, true>);
+    else f(k_reconstruct<p, nq, false>);
+  });
+}
+
 // Doubles of one stage's face states in the library layout [3 nq][n_pad][4].
 static size_t face_state_doubles(const teno_solver* s) { return (size_t)3 * s->d.nq * s->n_pad * 4; }
 
@@ -190,12 +238,7 @@ int launch_reconstruct(teno_solver* s, const double* U, uint16_t* flags, bool fr
                        hipStream_t st, double* fp = nullptr) {
   ReconArgs a;
   a.U = U;
-  a.slot = s->slot;
-  a.tmem = s->tmem;
-  a.ustride = s->ustride;
-  a.lds_stride = stage_int4(s->d.rows4, s->ustride);
-  if (s->prm.characteristic != 0) a.lds_stride = std::max(a.lds_stride, char_gram_int4());
-  a.M = s->M;
+  a.b = block_args(s);
   a.fp = fp ? fp : s->fp;
   a.flags = flags;
   a.user_of = s->user_of;
@@ -216,22 +259,11 @@ int launch_reconstruct(teno_solver* s, const double* U, uint16_t* flags, bool fr
   set_tie_window(a);
   a.cw_dK = 1.0 - 1.0 / s->prm.dk_prime;
   a.cw_ds = (1.0 - a.cw_dK) / 3.0;
-  const int blocks = (s->n_tiles + kReconBlockWaves - 1) / kReconBlockWaves;
-  const dim3 threads(64 * kReconBlockWaves);
-  const size_t lds = (size_t)kReconBlockWaves * a.lds_stride * sizeof(int4);
-  const bool cw = s->prm.variant == 2, ch = s->prm.characteristic != 0;
   int rc = TENO_OK;
-  dispatch(s->d.order, s->d.nq, [&](auto P, auto NQ) {
-    constexpr int p = decltype(P)::value, nq = decltype(NQ)::value;
+  recon_kernel(s, [&](auto kernel) {
     rc = timed(s, 0, st, [&]() {
-      if (ch && cw)
-        hipLaunchKernelGGL((k_reconstruct_char<p, nq, true>), dim3(blocks), threads, lds, st, a);
-      else if (ch)
-        hipLaunchKernelGGL((k_reconstruct_char<p, nq, false>), dim3(blocks), threads, lds, st, a);
-      else if (cw)
-        hipLaunchKernelGGL((k_reconstruct<p, nq, true>), dim3(blocks), threads, lds, st, a);
-      else
-        hipLaunchKernelGGL((k_reconstruct<p, nq, false>), dim3(blocks), threads, lds, st, a);
+      hipLaunchKernelGGL(kernel, dim3(std::min(s->n_blocks, s->recon_groups)),
+                         dim3(64 * s->bwaves), recon_lds(s), st, a, s->n_blocks);
     });
   });
   return rc;
@@ -327,16 +359,14 @@ int launch_vjp(teno_solver* s, const double* U, const uint16_t* flags, const dou
   AdjReconArgs ra;
   ra.fpbar = s->fpbar;
   ra.flags = flags;
-  ra.M = s->M;
+  ra.b = block_args(s);
   ra.aslot = s->aslot;
-  ra.tround = s->tround;
   ra.tbar = s->tbar;
   ra.ustride = s->ustride;
   ra.own = s->own;
   ra.n_cell = s->n_cell;
   ra.n_tiles = s->n_tiles;
   ra.n_pad = s->n_pad;
-  const int tblocks = (s->n_tiles + kAdjBlockWaves - 1) / kAdjBlockWaves;
   const int qblocks = (int)(((int64_t)s->n_cell * 4 + 255) / 256);
   dispatch(s->d.order, s->d.nq, [&](auto P, auto NQ) {
     rc = timed(s, 3, st, [&]() {
@@ -344,9 +374,11 @@ int launch_vjp(teno_solver* s, const double* U, const uint16_t* flags, const dou
       if (s->n_bface > 0)
         hipLaunchKernelGGL((k_adj_boundary<decltype(NQ)::value>), dim3((s->n_bface + 255) / 256),
                            dim3(256), 0, st, ff, (const int*)s->bface, s->n_bface);
-      hipLaunchKernelGGL((k_adj_recon<decltype(P)::value, decltype(NQ)::value>), dim3(tblocks),
-                         dim3(64 * kAdjBlockWaves),
-                         (size_t)kAdjBlockWaves * s->ustride * 4 * sizeof(double), st, ra);
+      hipLaunchKernelGGL((k_adj_recon<decltype(P)::value, decltype(NQ)::value>),
+                         dim3(s->n_blocks), dim3(64 * s->bwaves),
+                         (size_t)16 * rec_units(s->d.nu) * s->bmax +
+                             (size_t)s->bwaves * s->ustride * 4 * sizeof(double),
+                         st, ra);
       hipLaunchKernelGGL(k_adj_gather, dim3(qblocks), dim3(256), 0, st, s->own, s->tbar,
                          s->rev_ptr, s->rev_ent, s->n_cell, extra, beta, out);
     });
@@ -544,11 +576,19 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
     if (rc == TENO_OK) rc = s->alloc(p, n);
   };
   s->ustride = m.ustride;
-  A(s->slot, m.slot.size() / 8);
-  A(s->aslot, m.aslot.size() / 8);
-  A(s->tround, m.tround.size());
-  A(s->tmem, m.tmem.size());
-  A(s->M, m.M.size() / 2);
+  s->bwaves = m.bwaves;
+  s->bmax = m.bmax;
+  s->nbuf = m.nbuf;
+  s->n_blocks = (int)m.boff.size() - 1;
+  A(s->boff, m.boff.size());
+  A(s->bmem, m.bmem.size());
+  A(s->pack, m.pack.size());
+  A(s->brec, m.brec.size() / 2);
+  A(s->bslot, m.bslot.size());
+  A(s->N, m.N.size() / 2);
+  A(s->jac, m.jac.size() / 2);
+  A(s->centre, m.centre.size() / 2);
+  A(s->aslot, m.aslot.size());
   A(s->nbinfo, np);
   s->n_face = m.nf;
   s->n_bface = (int)m.bface.size();
@@ -583,11 +623,15 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
     void* dst;
     const void* src;
     size_t n;
-  } ups[] = {{s->slot, m.slot.data(), m.slot.size() * sizeof(uint16_t)},
-             {s->aslot, m.aslot.data(), m.aslot.size() * sizeof(uint16_t)},
-             {s->tround, m.tround.data(), m.tround.size() * sizeof(int32_t)},
-             {s->tmem, m.tmem.data(), m.tmem.size() * sizeof(int32_t)},
-             {s->M, m.M.data(), m.M.size() * sizeof(double)},
+  } ups[] = {{s->boff, m.boff.data(), m.boff.size() * sizeof(int32_t)},
+             {s->bmem, m.bmem.data(), m.bmem.size() * sizeof(int32_t)},
+             {s->pack, m.pack.data(), m.pack.size() * sizeof(int32_t)},
+             {s->brec, m.brec.data(), m.brec.size() * sizeof(double)},
+             {s->bslot, m.bslot.data(), m.bslot.size() * sizeof(uint32_t)},
+             {s->N, m.N.data(), m.N.size() * sizeof(double)},
+             {s->jac, m.jac.data(), m.jac.size() * sizeof(double)},
+             {s->centre, m.centre.data(), m.centre.size() * sizeof(float)},
+             {s->aslot, m.aslot.data(), m.aslot.size() * sizeof(uint32_t)},
              {s->nbinfo, m.nbinfo.data(), m.nbinfo.size() * sizeof(int32_t)},
              {s->bkind, m.bkind.data(), m.bkind.size() * sizeof(int32_t)},
              {s->bface, m.bface_sorted.data(), m.bface_sorted.size() * sizeof(int32_t)},
@@ -608,6 +652,9 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
       return hip_fail(e, "hipMemcpy upload");
     }
   }
+  recon_kernel(s, [&](auto kernel) {
+    s->recon_groups = resident_groups(kernel, 64 * s->bwaves, recon_lds(s), device);
+  });
   hipLaunchKernelGGL(k_diag_reset, dim3(1), dim3(64), 0, 0, s->diag);
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) {
@@ -868,10 +915,12 @@ struct teno_batch {
   double* partial = nullptr;
   // launch plan: per reconstruction launch (pq, item offset, wave offset, waves)
   struct RLaunch {
-    int pq, item0, wave0, n_waves;
-    int lds_stride;  // LDS per wavefront in int4, the largest of the launch's meshes
+    int pq, item0, n_items;   // items [item0, item0 + n_items)
+    int start0, n_groups;     // n_groups workgroups; their ranges, or -1: dealt out in turn
+    size_t lds;               // LDS per workgroup
   };
   std::vector<RLaunch> rplan;
+  std::vector<int> bmax, nbuf;  // per mesh: LDS layout of its launch (the largest block)
   int n_waves_f = 0, n_waves_c = 0, n_items_dt = 0, n_items_b = 0;
   // graph of one step: its kernels read every pointer from the device
   // descriptors, so it stays valid while only the descriptors change
@@ -941,12 +990,25 @@ int balanced_starts(const std::vector<double>& cost, int waves, std::vector<int>
   return waves;
 }
 
+// The per-order reconstruction launches: TENO_BATCH_CASE of every pair.
+#define TENO_BATCH_CASES \
+  TENO_BATCH_CASE(32)    \
+  TENO_BATCH_CASE(33)    \
+  TENO_BATCH_CASE(42)    \
+  TENO_BATCH_CASE(43)    \
+  TENO_BATCH_CASE(52)    \
+  TENO_BATCH_CASE(53)    \
+  TENO_BATCH_CASE(62)    \
+  TENO_BATCH_CASE(63)
+
 int batch_plan(teno_batch* b) {
   b->drop_graph();
   b->free_plan();
   const int n = b->n;
   const teno_batch_tuning& T = b->tune;
-  const int waves = T.waves_per_cu * b->n_cu;  // 0: one wavefront per item
+  const int waves = T.waves_per_cu * b->n_cu;  // 0: one wavefront (or workgroup) per item
+  b->bmax.assign(n, 0);
+  b->nbuf.assign(n, 1);
   // mesh order for the work list
   std::vector<int> morder(n);
   for (int m = 0; m < n; ++m) morder[m] = m;
@@ -970,22 +1032,55 @@ int batch_plan(teno_batch* b) {
   for (int pq : pqs) {
     std::vector<double> cost;
     const int item0 = (int)items.size();
-    int lds_stride = 0;
+    // the buffers of a launch's items have one layout, the largest block's
+    int bmax = 0, nbuf = 2, order = 0;
+    size_t lds = 0;
     for (int m : morder) {
       const teno_solver* s = b->sv[m];
-      const int mpq = s->d.order * 10 + s->d.nq;
-      if (pq != 0 && mpq != pq) continue;
-      lds_stride = std::max(lds_stride, stage_int4(s->d.rows4, s->ustride));
-      for (int t = 0; t < s->n_tiles; ++t) {
+      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
+      bmax = std::max(bmax, s->bmax);
+      order = s->d.order;
+      for (int t = 0; t < s->n_blocks; ++t) {
         items.push_back(make_int2(m, t));
-        cost.push_back((double)s->d.Jp + 4.0 * s->d.rows4 * 4);
+        cost.push_back(s->bwaves * ((double)s->d.Jp + 4.0 * s->d.rows4 * 4));
       }
     }
-    std::vector<int> st;
-    const int nw = balanced_starts(cost, waves, st);
-    for (int& x : st) x += item0;
-    b->rplan.push_back({pq, item0, (int)starts_all.size(), nw, lds_stride});
-    starts_all.insert(starts_all.end(), st.begin(), st.end());
+    const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);
+    if (pq != 0) {
+      const Dims& d = b->sv[items[item0].x]->d;
+      if (group_lds_bytes(d.nu, bmax, 2) > lds_budget(tiles)) nbuf = 1;
+      lds = recon_lds(d, tiles, bmax, nbuf, false);
+    }
+    for (int m : morder) {
+      const teno_solver* s = b->sv[m];
+      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
+      b->bmax[m] = pq != 0 ? bmax : s->bmax;
+      b->nbuf[m] = pq != 0 ? nbuf : s->nbuf;
+      if (pq == 0) lds = std::max(lds, recon_lds(s));
+    }
+    const int n_items = (int)items.size() - item0;
+    if (waves == 0) {
+      // every order: one item per workgroup; one order: as many workgroups as
+      // the chip holds, the items dealt out in turn
+      int groups = n_items;
+      switch (pq) {
+#define TENO_BATCH_CASE(PQ)                                                              \
+  case PQ:                                                                               \
+    groups = std::min(n_items, resident_groups(k_batch_reconstruct<PQ>, 64 * tiles, lds, \
+                                               b->device));                              \
+    break;
+        TENO_BATCH_CASES
+#undef TENO_BATCH_CASE
+        default: break;
+      }
+      b->rplan.push_back({pq, item0, n_items, -1, groups, lds});
+    } else {
+      std::vector<int> st;
+      const int ng = balanced_starts(cost, std::max(1, waves / tiles), st);
+      for (int& x : st) x += item0;
+      b->rplan.push_back({pq, item0, n_items, (int)starts_all.size(), ng, lds});
+      starts_all.insert(starts_all.end(), st.begin(), st.end());
+    }
   }
   // face items (64-face chunks), cell items (64-cell chunks) and dt items
   // (256-cell blocks)
@@ -1071,11 +1166,9 @@ int batch_descriptors(teno_batch* b, double* const* U, const double* dt, hipStre
     for (int k = 0; k < 3; ++k) {
       ReconArgs& a = d.r[k];
       a.U = in[k];
-      a.slot = s->slot;
-      a.tmem = s->tmem;
-      a.ustride = s->ustride;
-      a.lds_stride = stage_int4(s->d.rows4, s->ustride);
-      a.M = s->M;
+      a.b = block_args(s);
+      a.b.bmax = b->bmax[m];
+      a.b.nbuf = b->nbuf[m];
       a.fp = s->fp;
       a.flags = nullptr;
       a.user_of = s->user_of;
@@ -1144,34 +1237,22 @@ int batch_descriptors(teno_batch* b, double* const* U, const double* dt, hipStre
 
 void batch_launch_recon(teno_batch* b, int k, hipStream_t st) {
   for (const auto& L : b->rplan) {
-    // one wavefront per item: the loop-free kernel over this launch's items,
-    // in blocks of kReconBlockWaves wavefronts; the persistent kernel in
-    // blocks of four
-    const bool one = b->tune.waves_per_cu == 0;
-    const int bw = one ? kReconBlockWaves : 4;
-    const int blocks = (L.n_waves + bw - 1) / bw;
-    const int* ws = b->start_r + L.wave0;
-    const size_t lds = (size_t)bw * L.lds_stride * sizeof(int4);
-    const int2* its = b->items_r + L.item0;
+    // ranges index the whole work list, items dealt out in turn this launch's
+    const bool dealt = L.start0 < 0;
+    const int* start = dealt ? nullptr : b->start_r + L.start0;
+    const int2* its = dealt ? b->items_r + L.item0 : b->items_r;
     switch (L.pq) {
-#define TENO_BATCH_CASE(PQ)                                                                  \
-  case PQ:                                                                                   \
-    if (one)                                                                                 \
-      hipLaunchKernelGGL((k_batch_reconstruct_one<PQ>), dim3(blocks), dim3(64 * bw), lds, st, \
-                         b->meshes, its, L.n_waves, k, L.lds_stride);                        \
-    else                                                                                     \
-      hipLaunchKernelGGL((k_batch_reconstruct<PQ>), dim3(blocks), dim3(256), lds, st,        \
-                         b->meshes, b->items_r, ws, L.n_waves, k, L.lds_stride);             \
+      case 0:
+        hipLaunchKernelGGL(k_batch_reconstruct_all, dim3(L.n_groups), dim3(64 * kMaxBlockTiles),
+                           L.lds, st, b->meshes, its, start, k);
+        break;
+#define TENO_BATCH_CASE(PQ)                                                             \
+  case PQ:                                                                              \
+    hipLaunchKernelGGL((k_batch_reconstruct<PQ>), dim3(L.n_groups),                     \
+                       dim3(64 * block_tiles(PQ / 10)), L.lds, st, b->meshes, its, start, \
+                       L.n_items, k);                                                   \
     break;
-      TENO_BATCH_CASE(0)
-      TENO_BATCH_CASE(32)
-      TENO_BATCH_CASE(33)
-      TENO_BATCH_CASE(42)
-      TENO_BATCH_CASE(43)
-      TENO_BATCH_CASE(52)
-      TENO_BATCH_CASE(53)
-      TENO_BATCH_CASE(62)
-      TENO_BATCH_CASE(63)
+        TENO_BATCH_CASES
 #undef TENO_BATCH_CASE
       default: break;
     }
