@@ -54,15 +54,14 @@ Dims dims_for(int order, int nq_req, bool dense) {
 // simple parallel-for over [0, n) with std::thread
 // ---------------------------------------------------------------------------
 template <class F>
-static void parallel_for(int n, int threads, F&& f) {
+static void parallel_for(int n, int threads, F&& f, int chunk = 64) {
   if (threads <= 0) threads = (int)std::max(1u, std::thread::hardware_concurrency());
-  threads = std::min(threads, std::max(1, n / 64));
+  threads = std::min(threads, std::max(1, n / chunk));
   if (threads <= 1) {
     for (int i = 0; i < n; ++i) f(i);
     return;
   }
   std::atomic<int> next{0};
-  const int chunk = 64;
   std::vector<std::thread> pool;
   for (int t = 0; t < threads; ++t)
     pool.emplace_back([&]() {
@@ -547,7 +546,7 @@ static void shift_moments(int r, Ext x, Ext y, const Ext (&mu)[6][6], Ext (&out)
 
 // X = (A^T A)^-1 of the m x n row-major A: Cholesky, or the triangular factor
 // of a Householder QR where the normal matrix breaks down.
-void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& X) {
+static void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& X) {
   std::vector<Ext> L((size_t)n * n, 0);
   bool ok = true;
   for (int j = 0; j < n && ok; ++j)
@@ -699,7 +698,7 @@ static void pack_blocks(Mesh& m) {
       int cur = top.load();
       while ((int)u.size() > cur && !top.compare_exchange_weak(cur, (int)u.size())) {
       }
-    });
+    }, 1);
     m.bmax = top.load();
     if (group_lds_bytes(nu, m.bmax, m.nbuf) <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || W == 1)
       break;
@@ -896,7 +895,7 @@ static void pack_blocks(Mesh& m) {
         quad0 += sym_quads(n);
       }
     }
-  });
+  }, 1);
 }
 
 int mesh_setup(Mesh& m, const teno_params& p) {
