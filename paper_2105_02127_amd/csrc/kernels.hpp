@@ -1677,8 +1677,10 @@ __device__ __forceinline__ void boundary_state(int kind, const double* __restric
   }
 }
 
-template <int NQ, bool BND = false>
-__device__ __forceinline__ void face_flux(const FaceFluxArgs& a, int f, int b = -1) {
+// Phi of face f.  KIND 0: as if no face lay on the boundary; 1: f is boundary
+// face b; 2: what the face's record says.
+template <int NQ, int KIND>
+__device__ __forceinline__ void face_phi(const FaceFluxArgs& a, int f, int b, double (&out)[4]) {
   const int4 fc = a.fcell[f];
   const double2 nrm = a.fgeo[2 * (size_t)f], len = a.fgeo[2 * (size_t)f + 1];
   const int eL = fc.z & 3, eR = (fc.z >> 2) & 3;
@@ -1690,7 +1692,7 @@ __device__ __forceinline__ void face_flux(const FaceFluxArgs& a, int f, int b = 
     const double2 l0 = fp2[oL], l1 = fp2[oL + 1];
     const double uL[4] = {l0.x, l0.y, l1.x, l1.y};
     double uR[4];
-    if constexpr (BND) {
+    if constexpr (KIND == 1) {
       boundary_state(a.bkind[b], a.bstate, b, uL, nrm.x, nrm.y, uR);
     } else {
       const size_t oR = ((size_t)(eR * NQ + NQ - 1 - k) * a.n_pad + fc.y) * 2;
@@ -1699,15 +1701,25 @@ __device__ __forceinline__ void face_flux(const FaceFluxArgs& a, int f, int b = 
       uR[1] = r0.y;
       uR[2] = r1.x;
       uR[3] = r1.y;
+      if constexpr (KIND == 2)
+        if (fc.w >= 0) boundary_state(a.bkind[fc.w], a.bstate, fc.w, uL, nrm.x, nrm.y, uR);
     }
     double F[4];
     hll(uL, uR, nrm.x, nrm.y, a.gamma, F);
 #pragma unroll
     for (int c = 0; c < 4; ++c) phi[c] = phi[c] + FaceRule<NQ>::w[k] * F[c];
   }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) out[c] = phi[c] * len.x;
+}
+
+template <int NQ, bool BND = false>
+__device__ __forceinline__ void face_flux(const FaceFluxArgs& a, int f, int b = -1) {
+  double p[4];
+  face_phi<NQ, BND ? 1 : 0>(a, f, b, p);
   double2* out = reinterpret_cast<double2*>(a.phi) + 2 * (size_t)f;
-  out[0] = make_double2(phi[0] * len.x, phi[1] * len.x);
-  out[1] = make_double2(phi[2] * len.x, phi[3] * len.x);
+  out[0] = make_double2(p[0], p[1]);
+  out[1] = make_double2(p[2], p[3]);
 }
 
 // Every face, boundary faces included as if their outer side were the cell
@@ -1840,6 +1852,52 @@ __global__ __launch_bounds__(256) void k_cell_update_dt(CellUpdateArgs a,
   const double m = block_min(lim, sh);
   if (threadIdx.x == 0) partial[blockIdx.x] = m;
 }
+
+// Flux, gather and update in one launch, four lanes per cell: lane e < 3 forms
+// the Phi of the cell's local edge e as the face's own lane would, and the four
+// lanes add them in edge order, so the results are those of the separate kernels
+// bit for bit.  Every face is formed twice (both its cells), which a small mesh
+// does not notice: it waits for launches.  DT: also the block's minimum of the
+// next step's limit, as k_cell_update_dt.
+template <int NQ, bool RK, bool DT>
+__global__ __launch_bounds__(256) void k_cell_flux_update(FaceFluxArgs fa, CellUpdateArgs a,
+                                                          const double* __restrict__ geo,
+                                                          double* __restrict__ partial) {
+  const int t = xcd_remap(blockIdx.x, gridDim.x) * 64 + (threadIdx.x >> 2), e = threadIdx.x & 3;
+  const bool live = t < a.n_cell;
+  const int4 cf = a.cfaces[live ? t : 0];
+  double p[4] = {0.0, 0.0, 0.0, 0.0};
+  if (live && e < 3) face_phi<NQ, 2>(fa, e == 0 ? cf.x : (e == 1 ? cf.y : cf.z), -1, p);
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  static_for<0, 3>([&](auto k) {
+    static_for<0, 4>([&](auto c) {
+      const double x = quad_bcast<k>(p[c]);
+      acc[c] = (cf.w >> k) & 1 ? acc[c] + x : acc[c] - x;
+    });
+  });
+  const double own = e == 0 ? acc[0] : (e == 1 ? acc[1] : (e == 2 ? acc[2] : acc[3]));
+  double u = 0.0;
+  if (live) {
+    const double ia = -1.0 / a.vol[t];
+    const double R = own * ia;
+    const size_t o = 4 * (size_t)t + e;
+    u = R;
+    if (RK) u = a.ca * a.Un[o] + a.cb * a.Uk[o] + a.cc * (*a.dt * R);
+    a.out[o] = u;
+  }
+  if constexpr (DT) {
+    __shared__ double sh[4];
+    double w[4];
+    static_for<0, 4>([&](auto c) { w[c] = quad_bcast<c>(u); });
+    const double m = block_min(live ? dt_limit_of(w, geo, t, fa.gamma) : INFINITY, sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = m;
+  }
+}
+// Taken up to 65,536 / nq cells.  Linear residuals (fused against separate, us),
+// two points per face: 11.8 against 15.3 at 2,048 cells, 14.8 / 15.2 at 32,768,
+// 24.7 / 22.9 at 65,522; three: 17.7 / 19.0 at 2,048, 20.6 / 21.5 at 14,450,
+// 25.8 / 24.7 at 32,768.
+constexpr bool fuse_update(int n_cell, int nq) { return n_cell <= 65536 / nq; }
 
 __global__ __launch_bounds__(256) void k_dt_partial(const double* __restrict__ U,
                                                     const double* __restrict__ geo, int n,

@@ -302,6 +302,23 @@ int launch_flux(teno_solver* s, const double* Un, const double* Uk, double* out,
   int rc = TENO_OK;
   auto go = [&](auto NQ) {
     rc = timed(s, 1, st, [&]() {
+      constexpr int nq = decltype(NQ)::value;
+      if (fuse_update(s->n_cell, nq)) {
+        const int blocks = (s->n_cell + 63) / 64;
+        const double* geo = s->geo;
+        if (rk && next_dt) {
+          hipLaunchKernelGGL((k_cell_flux_update<nq, true, true>), dim3(blocks), dim3(256), 0, st, f,
+                             c, geo, s->dtpart);
+          hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(256), 0, st, (const double*)s->dtpart, blocks,
+                             next_cfl, next_dt);
+        } else if (rk)
+          hipLaunchKernelGGL((k_cell_flux_update<nq, true, false>), dim3(blocks), dim3(256), 0, st, f,
+                             c, geo, s->dtpart);
+        else
+          hipLaunchKernelGGL((k_cell_flux_update<nq, false, false>), dim3(blocks), dim3(256), 0, st,
+                             f, c, geo, s->dtpart);
+        return;
+      }
       hipLaunchKernelGGL((k_face_flux<decltype(NQ)::value>), dim3(fblocks), dim3(256), 0, st, f);
       if (s->n_bface > 0)
         hipLaunchKernelGGL((k_boundary_flux<decltype(NQ)::value>), dim3((s->n_bface + 255) / 256),
@@ -613,7 +630,7 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
   A(s->T0, nc * 4);
   A(s->T1, nc * 4);
   A(s->T2, nc * 4);
-  A(s->dtpart, (size_t)s->n_dtblk);
+  A(s->dtpart, (size_t)(m.nc + 63) / 64);  // (the fused update's blocks have 64 cells)
   A(s->diag, 1);
   if (rc) {
     delete s;

@@ -56,3 +56,29 @@ def test_block_layouts(oracle_mod, order, n, aspect, variant, characteristic):
         fu = np.empty_like(f)
         fu[..., lm.perm] = f
         check_flags(fu, want["flags"], want["diag"]["tie_mask"])
+
+
+@pytest.mark.parametrize("order,n", [(3, 9), (3, 127), (3, 128), (3, 129), (5, 104), (5, 105)])
+def test_step_equals_batched_step(order, n):
+    """Small meshes form fluxes and update in one launch (up to 32,768 cells with
+    two points per face, 21,845 with three), batches in two: the same bits, and
+    the next step's dt that of the new state."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_02127_amd import teno
+    from paper_2105_02127_amd.batch import Batch
+    print(f"[case] step order={order} n={n}", flush=True)
+    m = inputs.jittered_periodic_mesh(n, 43)
+    lm = teno.Mesh(m.xy, m.tri).setup(order=order, fallback=1)
+    sv = teno.Solver(lm)
+    U = torch.as_tensor(inputs.make_state(m, "random_lines")[lm.perm], device="cuda")
+    b = Batch([sv])
+    b.set_tuning(order_mode=1, waves_per_cu=0, item_order=0, use_graph=0)
+    dt = b.max_dt([U], 0.4)
+    w, d = U.clone(), dt.clone()
+    sv.rk_step_dt(w, d, 0.4)
+    b.rk_step([U], dt)
+    torch.cuda.synchronize()
+    assert torch.equal(w, U)
+    assert torch.equal(d, sv.max_dt(w, 0.4))
