@@ -504,6 +504,34 @@ struct Flux3Args {
   int n_face, n_pad;
 };
 
+// F . n at point k of face record fc
+template <int NPT>
+__device__ __forceinline__ void point_flux3(const Flux3Args& a, const int4& fc, const double n[3],
+                                            int k, double (&F)[5]) {
+  const int eL = fc.z & 3, eR = fc.z >> 2;
+  double uL[5], uR[5];
+  const double* pl = a.fp + ((size_t)(eL * NPT + k) * a.n_pad + fc.x) * kVars3;
+#pragma unroll
+  for (int c = 0; c < 5; ++c) uL[c] = pl[c];
+  if (fc.y >= 0) {
+    const int kr = (fc.w >> (3 * k)) & 7;
+    const double* pr = a.fp + ((size_t)(eR * NPT + kr) * a.n_pad + fc.y) * kVars3;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) uR[c] = pr[c];
+  } else {
+    // outer state of the boundary face: transmissive copies the inner
+    // state, reflective reverses its normal momentum
+#pragma unroll
+    for (int c = 0; c < 5; ++c) uR[c] = uL[c];
+    if (a.bkind[-1 - fc.y] == TENO_BC_REFLECTIVE) {
+      const double mn = uL[1] * n[0] + uL[2] * n[1] + uL[3] * n[2];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) uR[1 + d] = uL[1 + d] - 2.0 * mn * n[d];
+    }
+  }
+  hll3(uL, uR, n, a.gamma, F);
+}
+
 template <int NPT>
 __global__ __launch_bounds__(256) void k_face_flux3(Flux3Args a) {
   const int f = xcd_remap3(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
@@ -511,32 +539,11 @@ __global__ __launch_bounds__(256) void k_face_flux3(Flux3Args a) {
   const int4 fc = a.fcell[f];
   const double4 gg = a.fgeo[f];
   const double n[3] = {gg.x, gg.y, gg.z};
-  const int eL = fc.z & 3, eR = fc.z >> 2;
   double phi[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int k = 0; k < NPT; ++k) {
-    double uL[5], uR[5];
-    const double* pl = a.fp + ((size_t)(eL * NPT + k) * a.n_pad + fc.x) * kVars3;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) uL[c] = pl[c];
-    if (fc.y >= 0) {
-      const int kr = (fc.w >> (3 * k)) & 7;
-      const double* pr = a.fp + ((size_t)(eR * NPT + kr) * a.n_pad + fc.y) * kVars3;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) uR[c] = pr[c];
-    } else {
-      // outer state of the boundary face: transmissive copies the inner
-      // state, reflective reverses its normal momentum
-#pragma unroll
-      for (int c = 0; c < 5; ++c) uR[c] = uL[c];
-      if (a.bkind[-1 - fc.y] == TENO_BC_REFLECTIVE) {
-        const double mn = uL[1] * n[0] + uL[2] * n[1] + uL[3] * n[2];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) uR[1 + d] = uL[1 + d] - 2.0 * mn * n[d];
-      }
-    }
     double F[5];
-    hll3(uL, uR, n, a.gamma, F);
+    point_flux3<NPT>(a, fc, n, k, F);
 #pragma unroll
     for (int c = 0; c < 5; ++c) phi[c] = fma(a.w[k], F[c], phi[c]);
   }
@@ -584,6 +591,60 @@ __global__ __launch_bounds__(256) void k_cell_update3(Update3Args a) {
     for (int c = 0; c < 5; ++c) o[c] = acc[c] * ia;
   }
 }
+
+// Flux, gather and update in one launch, 32 lanes per cell: eight per face, one
+// per point, then twenty lanes add a variable of a face over its points in point
+// order and five add a variable over the faces in face order, as the separate
+// kernels do (the products that those keep apart by a trip through memory go
+// through LDS here).  A small mesh waits for launches and for one lane's chain of
+// six or seven Riemann problems; forming every face twice costs it nothing.
+template <int NPT>
+__global__ __launch_bounds__(256) void k_cell_flux_update3(Flux3Args f, Update3Args a) {
+  __shared__ double sF[256 * 5], sP[8 * 20];
+  const int l = threadIdx.x & 31, w = threadIdx.x >> 5;
+  const int t = xcd_remap3(blockIdx.x, gridDim.x) * 8 + w;
+  const bool live = t < a.n_cell;
+  const int4 cf = a.cfaces[live ? t : 0];
+  auto face = [&](int e) { return e == 0 ? cf.x : (e == 1 ? cf.y : (e == 2 ? cf.z : cf.w)); };
+  if (live && (l & 7) < NPT) {
+    const int id = face(l >> 3);
+    const int4 fc = f.fcell[id];
+    const double4 gg = f.fgeo[id];
+    const double n[3] = {gg.x, gg.y, gg.z};
+    double F[5];
+    point_flux3<NPT>(f, fc, n, l & 7, F);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) sF[threadIdx.x * 5 + c] = F[c];
+  }
+  __syncthreads();
+  if (live && l < 20) {
+    const int e = l / 5, c = l - 5 * e;
+    double phi = 0.0;
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) phi = fma(f.w[k], sF[(32 * w + 8 * e + k) * 5 + c], phi);
+    sP[20 * w + l] = f.fgeo[face(e)].w * phi;
+  }
+  __syncthreads();
+  if (live && l < 5) {
+    const int side = a.cside[t];
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double p = sP[20 * w + 5 * e + l];
+      acc = (side >> e) & 1 ? acc + p : acc - p;
+    }
+    const double ia = -1.0 / a.vol[t];
+    const size_t o = (size_t)t * 5 + l;
+    if (a.rk)
+      a.out[o] = a.ca * a.Un[o] + a.cb * a.Uk[o] + a.cc * (*a.dt * (acc * ia));
+    else
+      a.out[o] = acc * ia;
+  }
+}
+// Flux and update against the two launches (us): 10.9 / 14.8 at 10,368 cells with
+// six points per face and 11.2 / 15.9 with seven, 17.9 / 17.4 at 24,576 with seven,
+// 29 / 20 at 48,000.
+constexpr int kFuseCells3 = 16384;
 
 __device__ __forceinline__ double block_min3(double x, double* sh) {
 #pragma unroll

@@ -187,6 +187,14 @@ int launch_flux3(teno3_solver* s, const double* Un, const double* Uk, double* ou
   c.rk = rk ? 1 : 0;
   const int fb = (s->n_face + 255) / 256, cb = (s->n_cell + 255) / 256;
   return timed3(s, 1, st, [&]() {
+    if (s->n_cell <= kFuseCells3) {
+      const int fused = (s->n_cell + 7) / 8;
+      if (s->d.npt == 6)
+        hipLaunchKernelGGL(k_cell_flux_update3<6>, dim3(fused), dim3(256), 0, st, f, c);
+      else
+        hipLaunchKernelGGL(k_cell_flux_update3<7>, dim3(fused), dim3(256), 0, st, f, c);
+      return;
+    }
     if (s->d.npt == 6)
       hipLaunchKernelGGL(k_face_flux3<6>, dim3(fb), dim3(256), 0, st, f);
     else

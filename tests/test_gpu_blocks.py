@@ -82,3 +82,27 @@ def test_step_equals_batched_step(order, n):
     torch.cuda.synchronize()
     assert torch.equal(w, U)
     assert torch.equal(d, sv.max_dt(w, 0.4))
+
+
+@pytest.mark.parametrize("order,n", [(3, 13), (5, 13), (3, 14)])
+def test_tetrahedral_residual_on_both_update_paths(order, n):
+    """Tetrahedral meshes of up to 16,384 cells form fluxes and update in one
+    launch, larger ones in two: residuals at sampled cells within 1e-12 of the
+    flux scale, and conservation over the periodic mesh, on both sides (13,182
+    cells, no multiple of a block's eight, and 16,464)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from oracle import tet
+    from paper_2105_02127_amd import inputs3, teno3
+    from test_gpu_tet import Case3
+    m = inputs3.jittered_periodic_cube(n, 47)
+    U = inputs3.random_planes3(m)
+    c = Case3(teno3, tet, torch, m, U, order, f"update paths n={n}", oracle_all=False, fallback=1)
+    R = c.user(c.sv.residual(c.Ud))
+    cells = np.linspace(0, m.n_cell - 1, 60).astype(np.int32)
+    want, _ = c.om.residual_cells(U, cells)
+    scale = c.flux_scale()
+    assert np.abs(R[cells] - want).max() <= 1e-12 * scale
+    vol, _, _ = c.om.geometry()
+    assert np.abs((vol[:, None] * R).sum(0)).max() <= 1e-12 * scale * vol.sum()
