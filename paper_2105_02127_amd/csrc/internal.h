@@ -9,15 +9,9 @@
 
 namespace teno {
 
-// Cells per wavefront tile of the reconstruction kernel (16 or 8): the 64
-// lanes of a wavefront give each cell 64 / kTile lanes.  Host packing and
-// device kernels must agree, so both compilers see the same macro.
-#ifndef TENO_TILE
-#define TENO_TILE 16
-#endif
-constexpr int kTile = TENO_TILE;
-constexpr int kLanesPerCell = 64 / kTile;
-static_assert(kTile == 16 || kTile == 8, "tile must hold 16 or 8 cells");
+// Cells per wavefront tile of the reconstruction kernels: four of the 64 lanes
+// per cell.
+constexpr int kTile = 16;
 
 // Sizes of one order (Sec. 2.2 eq. 03 with N_k counting the constant term;
 // N_s = 2 N_k cells including the target, so 2 N_k - 1 least-squares rows).
@@ -167,31 +161,16 @@ struct Mesh {
 constexpr int small_row(int k, int s) { return kSmallRows * k + s; }
 constexpr int large_row(int s) { return 3 * kSmallRows + s; }
 
-// Stored operator entries of one stencil (M^T: nrow rows of L
-// coefficients), in one of two block layouts (offsets in doubles within the
-// block of a tile of kTile cells):
-//  * rows by lane (dense meshes, odd L: the small stencils and the large one
-//    at orders 3 and 4): the rows come in groups of four; lane g of a cell
-//    owns row 4j + g of group j and reads its L entries from L planes, each
-//    holding entry l of the group's rows for every cell (cell-major,
-//    row-minor).  The last group may hold fewer rows.  Nothing is padded,
-//    and a wavefront's load of one plane covers 16 cells x 4 rows
-//    contiguously.
+// Operator entries of one stencil (M^T: nrow rows of L coefficients), kept on
+// the host for teno_mesh_lsq_operator, in one of two block layouts (offsets in
+// doubles within the block of a tile of kTile cells):
+//  * rows by lane (dense meshes, odd L): groups of four rows, each as L planes
+//    of [cell][row];
 //  * entry pairs (even L, or any L on meshes that are not dense): M^T row by
-//    row as 16-byte pairs, [pair][cell][2], odd rows padded with a zero to
-//    even length; lane g of a cell reads pairs g, g + 4, ... of each row.
-// Meshes reconstructed in conservative variables are dense; the
-// characteristic-variable kernel holds more values across its streams and
-// measured faster on entry pairs.  TENO_DENSE=0 makes no mesh dense.
-#ifndef TENO_DENSE
-#define TENO_DENSE 1
-#endif
-#ifndef TENO_LARGE_LANES
-#define TENO_LARGE_LANES 1
-#endif
-constexpr bool lane_rows(int L, bool dense) { return TENO_DENSE && dense && (L & 1) && kTile == 16; }
-// the large stencil's block (its rows are longer than the small ones')
-constexpr bool large_lane_rows(int L, bool dense) { return TENO_LARGE_LANES && lane_rows(L, dense); }
+//    row as pairs, [pair][cell][2], odd rows padded with a zero.
+// Meshes reconstructed in conservative variables are dense.
+constexpr bool lane_rows(int L, bool dense) { return dense && (L & 1); }
+constexpr bool large_lane_rows(int L, bool dense) { return lane_rows(L, dense); }
 constexpr int stored_row(int L) { return L + (L & 1); }
 constexpr int block_entries(int nrow, int L, bool dense) {
   return lane_rows(L, dense) ? nrow * L : nrow * stored_row(L);
@@ -210,7 +189,7 @@ constexpr int large_block_offset(int nrow, int L, bool dense, int c, int s, int 
   return block_offset(nrow, L, large_lane_rows(L, dense), c, s, l);
 }
 
-// The operator stream of a tile: the three small stencils' blocks, then the
+// The operators of a tile: the three small stencils' blocks, then the
 // large stencil's, Jp * kTile doubles in all.  Block k (3 = large) starts at
 // block_start(k, dense) * kTile.
 constexpr int block_start(int k, bool dense) { return small_block(dense) * k; }

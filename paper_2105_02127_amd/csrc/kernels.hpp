@@ -1,7 +1,7 @@
 // HIP kernels of the TENO residual for gfx950 (MI355X), FP64.
 //
-//   k_reconstruct  blocks of four wavefronts, one tile of 16 cells each, four
-//                  lanes per cell.  Least-squares phase (Sec. 2.2 eqs. 08-10)
+//   k_reconstruct  blocks of four or eight wavefronts, one tile of 16 cells
+//                  each, four lanes per cell.  Least-squares phase (Sec. 2.2 eqs. 08-10)
 //                  without stored operators (below).  Selection phase: lane g
 //                  holds the full coefficient vectors of variable g, forms the
 //                  smoothness indicators (Sec. 2.3), the strong scale
@@ -14,6 +14,7 @@
 //  k_cell_update   one lane per cell: gather of its three face fluxes into
 //                  the residual (Sec. 2.1), optional SSP-RK3 stage combine
 //                  (a gather in a fixed order: no atomics, deterministic).
+//  k_cell_flux_update  both in one launch, for small meshes.
 //  k_dt_*          constant-CFL step: per-block minima, then one block.
 //  k_adj_*         adjoint of the residual with the selection frozen.
 //
@@ -933,7 +934,7 @@ __device__ __forceinline__ bool quad_all(bool ok, int lane) {
 }
 
 // Characteristic projection of lane variable v (Sec. 2.3): row v of L
-// (char_lrow) and row v of R (char_rrow), where R's columns are the right
+// (char_lrow_lane) and row v of R (char_rrow), where R's columns are the right
 // eigenvectors of the Euler flux Jacobian in direction (nx, ny) at the cell
 // mean u (quad lanes 0..3), for the speeds u.n - c, u.n (entropy), u.n
 // (shear), u.n + c, and L = R^-1 in closed form (b1 = (gamma-1)/c^2,
@@ -982,24 +983,6 @@ __device__ __forceinline__ CharState char_expand(CharCore K, double g) {
   S.b1 = (g - 1.0) * K.ic * K.ic;
   S.b2 = 0.5 * S.q2 * S.b1;
   return S;
-}
-
-__device__ __forceinline__ void char_lrow(const CharState& S, double nx, double ny, bool ok, int v,
-                                          double (&lrow)[4]) {
-  if (!ok) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) lrow[j] = (j == v) ? 1.0 : 0.0;
-    return;
-  }
-  const double un = S.ux * nx + S.uy * ny, ut = S.uy * nx - S.ux * ny;
-  const double b1 = S.b1, b2 = S.b2, ic = S.ic;
-  const double L[4][4] = {
-      {0.5 * (b2 + un * ic), -0.5 * (b1 * S.ux + nx * ic), -0.5 * (b1 * S.uy + ny * ic), 0.5 * b1},
-      {1.0 - b2, b1 * S.ux, b1 * S.uy, -b1},
-      {-ut, -ny, nx, 0.0},
-      {0.5 * (b2 - un * ic), -0.5 * (b1 * S.ux - nx * ic), -0.5 * (b1 * S.uy - ny * ic), 0.5 * b1}};
-#pragma unroll
-  for (int j = 0; j < 4; ++j) lrow[j] = pick4(L[0][j], L[1][j], L[2][j], L[3][j], v);
 }
 
 __device__ __forceinline__ void char_rrow(const CharState& S, double nx, double ny, bool ok, int v,
@@ -2047,15 +2030,6 @@ struct AdjReconArgs {
   int ustride;
   int n_cell, n_tiles, n_pad;
 };
-
-__device__ __forceinline__ unsigned quad_bcast_u(unsigned x, int k) {
-  switch (k) {
-    case 0: return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x00, 0xF, 0xF, false);
-    case 1: return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x55, 0xF, 0xF, false);
-    case 2: return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0xAA, 0xF, 0xF, false);
-    default: return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0xFF, 0xF, 0xF, false);
-  }
-}
 
 // Rows of one stencil: adjoints of its differences from z (the lane's own
 // variable), added to acc; returns the lane's sums over its rows in dq.

@@ -3,7 +3,7 @@
 // The target cell is mapped onto the reference triangle (0,0),(1,0),(0,1)
 // (Sec. 2.2 eq. 02), so the smoothness form and the face-point basis values
 // are the same for every cell of a given order; only the least-squares
-// operators differ per cell.  Both tables are exact rational expressions
+// matrices differ per cell.  Both tables are exact rational expressions
 // evaluated here at compile time.
 #pragma once
 
@@ -197,7 +197,6 @@ struct OrderT {
   static constexpr int NL = (R + 1) * (R + 2) - 1;
   static constexpr int NQ = (P + 1) / 2;
   static constexpr int ROWS = 33 + NL;
-  static constexpr int ROWS4 = (ROWS + 3) / 4;
   static constexpr int J = 165 + NU * NL;         // operator entries
 };
 
