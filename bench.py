@@ -38,18 +38,21 @@ def kernel_source_hash() -> str:
 
 def algorithmic_bytes_stage(order: int) -> int:
     """Bytes one cell must move per RK stage, the fused minimum of the
-    method: its least-squares operators (3 small 5 x 11 + the large
-    nu x nl, FP64), its stencil indices (33 + nl int32), its state, U^n and
-    U^(k+1) (32 B each), and its share of the face geometry (1.5 faces x
-    (normal, |A|, two cell ids) + its face list and |V|: 68 B).  Stencil
-    gathers served from cache and intermediates are not counted: 2,100 /
-    3,060 / 4,980 / 8,340 B at orders 3-6."""
+    method: the packed inverses of its normal matrices (3 small 15 + the
+    large nu (nu + 1) / 2, FP64), its own geometry record (nu + 1 doubles),
+    frame map and stencil centres (64 B), its row slots (33 + nl of 10 bits,
+    three to a word), its state, U^n and U^(k+1) (32 B each), and its share
+    of the face geometry (1.5 faces x (normal, |A|, two cell ids) + its face
+    list and |V|: 68 B).  Records and states of other members, served from
+    LDS and caches, and intermediates are not counted: 816 / 1,100 / 1,632 /
+    2,536 B at orders 3-6 (stored least-squares operators: 2,100 / 3,060 /
+    4,980 / 8,340 B)."""
     r = order - 1
     nu = (r + 1) * (r + 2) // 2 - 1
     nl = (r + 1) * (r + 2) - 1
-    ops = 8 * (3 * 5 * 11 + nu * nl)
-    idx = 4 * (33 + nl)
-    return ops + idx + 3 * 32 + 68
+    ops = 8 * (3 * 15 + nu * (nu + 1) // 2)
+    idx = 4 * ((33 + nl + 2) // 3)
+    return ops + 8 * (nu + 1) + 64 + idx + 3 * 32 + 68
 
 
 def traffic_from_profiles(workload: str):

@@ -280,7 +280,8 @@ typedef struct teno_batch_tuning {
                             order (dispatch per work item); 1: one launch per
                             order present, each with that order's registers */
   int32_t waves_per_cu;  /* persistent wavefronts per compute unit, 1..32;   */
-                         /* 0: one wavefront per work item (no persistence)  */
+                         /* 0: as many as the device holds, items dealt out  */
+                         /* in turn (order_mode 0: one workgroup per item)   */
   int32_t item_order;    /* 0: mesh order; 1: largest order first            */
   int32_t use_graph;     /* 1: capture one step as a HIP graph and replay it  */
 } teno_batch_tuning;
@@ -288,7 +289,7 @@ typedef struct teno_batch_tuning {
 /* Groups solvers created on the same device (meshes of any size and order,
  * each set up with its own parameters) so that one SSP-RK3 step of all of
  * them runs as persistent launches over a shared work list: per stage one
- * reconstruction launch (or one per order, see tuning) over (mesh, tile)
+ * reconstruction launch (or one per order, see tuning) over (mesh, block)
  * items and one flux/update launch over (mesh, 64-cell) items.  The solvers
  * must outlive the batch; their workspaces are reused.  Meshes with boundary
  * faces take their conditions and prescribed states from their solvers.
