@@ -576,7 +576,7 @@ def main():
                             "reconstruction") if diag["fallbacks"] else None,
                    "stage": "reconstruct + HLL flux + gather + RK update; dt once per step, "
                             "formed by the last stage's update"},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "fp64 issue", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS if achieved else None,
                      "traffic": traffic,
                      "kernel": "k_reconstruct",
