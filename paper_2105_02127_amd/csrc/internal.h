@@ -57,11 +57,25 @@ constexpr double kHermite = 0.4;  // the frame has unit variance over a stencil
 constexpr int rec_units(int nu) { return ((nu + 2) / 2) | 1; }  // nu + 1 doubles
 // LDS of one staged block: states (32 B each), records.
 constexpr int block_lds_bytes(int nu, int members) { return members * (16 * rec_units(nu) + 32); }
-// A workgroup holds two of them (one when they do not fit), and two lists of
-// member ids (padded to whole wavefront loads).
+// A workgroup holds two of them (one when they do not fit), and as many lists of
+// member ids (padded to whole wavefront loads).  In characteristic variables a
+// wavefront's Gram matrices (4 stencils x 10 entries per cell) take the place of
+// its block's members once these are read, and at order 3 they are the longer of
+// the two: the buffers lie buffer_stride apart, and the lists behind them.  Host
+// and kernels form every offset from these functions.
+constexpr int kCharGramDoubles = kTile * 4 * 10;
+constexpr int gram_bytes(int waves) { return waves * kCharGramDoubles * (int)sizeof(double); }
 constexpr int ids_bytes(int members) { return (members + 63) / 64 * 256; }
-constexpr int group_lds_bytes(int nu, int members, int buffers) {
-  return buffers * (block_lds_bytes(nu, members) + ids_bytes(members));
+constexpr int buffer_stride(int nu, int members, int waves, bool characteristic) {
+  const int staged = block_lds_bytes(nu, members), gram = characteristic ? gram_bytes(waves) : 0;
+  return staged > gram ? staged : gram;
+}
+constexpr int buffer_offset(int stride, int buffers, int k) { return (buffers == 2 ? k & 1 : 0) * stride; }
+constexpr int ids_offset(int stride, int members, int buffers, int k) {
+  return buffers * stride + (buffers == 2 ? k & 1 : 0) * ids_bytes(members);
+}
+constexpr int group_lds_bytes(int stride, int members, int buffers) {
+  return buffers * (stride + ids_bytes(members));
 }
 constexpr int kLdsPerCu = 160 * 1024;
 // Tiles (wavefronts) per block: workgroups of four, two or more to a CU, at

@@ -283,19 +283,20 @@ struct BlockArgs {
   int mstride;                         // members of the mesh's largest block
   int bmax;                            // of all the launch's meshes: lays out the LDS
   int nbuf;                            // staged blocks in LDS (2 or 1)
+  int stride;                          // bytes from one to the next (buffer_stride)
 };
 
 // Arguments in constant memory (a kernel's own, or a batch's descriptors):
 // fields are loaded through the scalar cache where they are used.
 #define TENO_CONST const __attribute__((address_space(4)))
 
-// LDS of a reconstruction workgroup: nbuf staged blocks (states at 0, records
-// at 32 bmax), then nbuf lists of member ids.
-__device__ __forceinline__ unsigned buf_offset(TENO_CONST BlockArgs& b, int nu, int k) {
-  return (b.nbuf == 2 ? k & 1 : 0) * block_lds_bytes(nu, b.bmax);
+// LDS of a reconstruction workgroup: nbuf staged blocks, stride apart (states at
+// 0, records at 32 bmax), then nbuf lists of member ids.
+__device__ __forceinline__ unsigned buf_offset(TENO_CONST BlockArgs& b, int k) {
+  return buffer_offset(b.stride, b.nbuf, k);
 }
-__device__ __forceinline__ unsigned ids_offset(TENO_CONST BlockArgs& b, int nu, int k) {
-  return b.nbuf * block_lds_bytes(nu, b.bmax) + (b.nbuf == 2 ? k & 1 : 0) * ids_bytes(b.bmax);
+__device__ __forceinline__ unsigned list_offset(TENO_CONST BlockArgs& b, int k) {
+  return ids_offset(b.stride, b.bmax, b.nbuf, k);
 }
 
 // Copies from memory straight to LDS (no registers): lane l's 16 (or 4) bytes
@@ -1028,8 +1029,6 @@ __device__ __forceinline__ double quad_dot(const double (&row)[4], double x) {
 // select differently project the coefficients and map back.  The Gram
 // matrices live in the block's staging LDS (16 cells x
 // 4 stencils x 10 entries), which the least-squares phase no longer needs.
-constexpr int kCharGramDoubles = kTile * 4 * 10;
-
 __device__ __forceinline__ int gram_off(int i, int j) {  // i <= j
   return i * 4 - (i * (i - 1)) / 2 + (j - i);
 }
@@ -1409,7 +1408,7 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
     copy_records<NU>(a.b, blk, lds0 + 32 * a.b.bmax, nthr);
     if (k0 + step < k1) {
       TENO_CONST ReconArgs& n = items.args(k0 + step);
-      copy_ids(n.b, items.block(k0 + step), lds0 + ids_offset(n.b, NU, 1), nthr);
+      copy_ids(n.b, items.block(k0 + step), lds0 + list_offset(n.b, 1), nthr);
     }
     tile_n = tile_of(a, blk);
     ta.load(a.b, max(tile_n, 0), threadIdx.x & 63);
@@ -1431,8 +1430,8 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
       if (k + step < k1) {
         TENO_CONST ReconArgs& n = items.args(k + step);
         const int nb = items.block(k + step);
-        const unsigned st = lds0 + buf_offset(n.b, NU, it + 1);
-        const int* ids = reinterpret_cast<const int*>(lds + ids_offset(n.b, NU, it + 1));
+        const unsigned st = lds0 + buf_offset(n.b, it + 1);
+        const int* ids = reinterpret_cast<const int*>(lds + list_offset(n.b, it + 1));
         copy_states(n.U, ids, scalar_load(n.b.boff, nb + 1) - scalar_load(n.b.boff, nb), st, nthr);
         copy_records<NU>(n.b, nb, st + 32 * n.b.bmax, nthr);
       }
@@ -1441,10 +1440,10 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
       stage_next();
       if (k + 2 * step < k1) {
         TENO_CONST ReconArgs& n = items.args(k + 2 * step);
-        copy_ids(n.b, items.block(k + 2 * step), lds0 + ids_offset(n.b, NU, it), nthr);
+        copy_ids(n.b, items.block(k + 2 * step), lds0 + list_offset(n.b, it), nthr);
       }
     }
-    const char* buf = lds + buf_offset(a.b, NU, it);
+    const char* buf = lds + buf_offset(a.b, it);
     const int own_slot = min(wave, a.b.bwaves - 1) * kTile + c;
     const int cell = ta.cell;
     const bool live = on && cell >= 0;
@@ -1506,7 +1505,7 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
     if (a.b.nbuf == 1 && k + step < k1) {  // the next block in the same LDS
       TENO_CONST ReconArgs& n = items.args(k + step);
       __syncthreads();
-      copy_ids(n.b, items.block(k + step), lds0 + ids_offset(n.b, NU, 0), nthr);
+      copy_ids(n.b, items.block(k + step), lds0 + list_offset(n.b, 0), nthr);
       lds_copy_wait();
       __syncthreads();
       if constexpr (!CH) {

@@ -700,7 +700,8 @@ static void pack_blocks(Mesh& m) {
       }
     }, 1);
     m.bmax = top.load();
-    if (group_lds_bytes(nu, m.bmax, m.nbuf) <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || W == 1)
+    const int stride = buffer_stride(nu, m.bmax, W, m.prm.characteristic != 0);
+    if (group_lds_bytes(stride, m.bmax, m.nbuf) <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || W == 1)
       break;
     // two buffers do not fit: one, in workgroups of four or fewer
     if (m.nbuf == 2 && W == 4) {

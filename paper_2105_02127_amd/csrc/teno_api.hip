@@ -188,20 +188,21 @@ static void set_tie_window(ReconArgs& a) {
   }
 }
 
+// Layout of the staged blocks of a launch whose largest block has bmax members.
+static void set_layout(BlockArgs& b, const Dims& d, int waves, int bmax, int nbuf, bool characteristic) {
+  b.bmax = bmax;
+  b.nbuf = nbuf;
+  b.stride = buffer_stride(d.nu, bmax, waves, characteristic);
+}
 static BlockArgs block_args(const teno_solver* s) {
-  return {s->boff, s->bmem, s->brec, s->bslot, s->N, s->jac, s->centre, s->pack, s->bwaves, s->bmax, s->bmax, s->nbuf};
+  BlockArgs b{s->boff, s->bmem, s->brec, s->bslot, s->N, s->jac, s->centre, s->pack, s->bwaves, s->bmax, 0, 0, 0};
+  set_layout(b, s->d, s->bwaves, s->bmax, s->nbuf, s->prm.characteristic != 0);
+  return b;
 }
 
-// Dynamic LDS of one reconstruction workgroup; in characteristic variables the
-// buffer of the current block also holds its Gram matrices.
-static size_t recon_lds(const Dims& d, int bwaves, int bmax, int nbuf, bool characteristic) {
-  size_t n = (size_t)group_lds_bytes(d.nu, bmax, nbuf);
-  if (characteristic) {
-    const size_t buf = (size_t)block_lds_bytes(d.nu, bmax);
-    const size_t gram = (size_t)bwaves * kCharGramDoubles * sizeof(double);
-    if (gram > buf) n += nbuf * (gram - buf);
-  }
-  return n;
+// Dynamic LDS of one reconstruction workgroup.
+static size_t recon_lds(const Dims& d, int waves, int bmax, int nbuf, bool characteristic) {
+  return (size_t)group_lds_bytes(buffer_stride(d.nu, bmax, waves, characteristic), bmax, nbuf);
 }
 static size_t recon_lds(const teno_solver* s) {
   return recon_lds(s->d, s->bwaves, s->bmax, s->nbuf, s->prm.characteristic != 0);
@@ -1065,7 +1066,7 @@ int batch_plan(teno_batch* b) {
     const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);
     if (pq != 0) {
       const Dims& d = b->sv[items[item0].x]->d;
-      if (group_lds_bytes(d.nu, bmax, 2) > lds_budget(tiles)) nbuf = 1;
+      if (recon_lds(d, tiles, bmax, 2, false) > (size_t)lds_budget(tiles)) nbuf = 1;
       lds = recon_lds(d, tiles, bmax, nbuf, false);
     }
     for (int m : morder) {
@@ -1184,8 +1185,7 @@ int batch_descriptors(teno_batch* b, double* const* U, const double* dt, hipStre
       ReconArgs& a = d.r[k];
       a.U = in[k];
       a.b = block_args(s);
-      a.b.bmax = b->bmax[m];
-      a.b.nbuf = b->nbuf[m];
+      set_layout(a.b, s->d, s->bwaves, b->bmax[m], b->nbuf[m], false);
       a.fp = s->fp;
       a.flags = nullptr;
       a.user_of = s->user_of;

@@ -1,0 +1,62 @@
+"""Host checks (no GPU) of what set-up packs for the triangle kernels' blocks,
+through the driver tests/host/blocks2d.cpp."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2105_02127_amd import inputs
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    tmp = str(tmp_path_factory.mktemp("blocks2d"))
+    exe = os.path.join(tmp, "blocks2d")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-pthread", "-ffp-contract=off",
+                    os.path.join(ROOT, "tests", "host", "blocks2d.cpp"),
+                    os.path.join(ROOT, "paper_2105_02127_amd", "csrc", "setup.cpp"), "-o", exe],
+                   check=True, capture_output=True)
+    return tmp, exe
+
+
+def _write(tmp, tag, m):
+    with open(os.path.join(tmp, tag + ".txt"), "w") as fh:
+        fh.write(f"{m.xy.shape[0]} {m.tri.shape[0]} {m.period[0]} {m.period[1]}\n")
+    np.ascontiguousarray(m.xy, np.float64).tofile(os.path.join(tmp, tag + ".xy"))
+    np.ascontiguousarray(m.tri, np.int32).tofile(os.path.join(tmp, tag + ".tri"))
+
+
+def _run(exe, *args):
+    r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-500:] + r.stderr[-2000:]
+    return r.stdout
+
+
+def _mesh(driver, m, order, variant=0, characteristic=0):
+    tmp, exe = driver
+    _write(tmp, "m", m)
+    w = _run(exe, "mesh", tmp, "m", order, variant, characteristic).split()
+    return dict(zip(w[::2], map(int, w[1::2])))
+
+
+def test_block_layouts_do_not_overlap(driver):
+    # every order, wavefront count, member count, one and two buffers; in
+    # characteristic variables the Gram matrices lie over the members just read,
+    # and at order 3 (about 200 members per block) they are the longer of the two
+    assert "ok" in _run(driver[1], "layout")
+
+
+@pytest.mark.parametrize("order", [3, 4, 5, 6])
+@pytest.mark.parametrize("kind", ["periodic", "box", "strip"])
+def test_characteristic_block_layouts_of_meshes(driver, order, kind):
+    m = {"periodic": lambda: inputs.jittered_periodic_mesh(30, 2),
+         "box": lambda: inputs.jittered_box_mesh(31, 23, 3),
+         "strip": lambda: inputs.jittered_box_mesh(400, 12, 4, lx=400.0, ly=12.0)}[kind]()
+    s = _mesh(driver, m, order, characteristic=1)
+    assert s["lds"] <= 160 * 1024

@@ -106,3 +106,17 @@ def test_tetrahedral_residual_on_both_update_paths(order, n):
     assert np.abs(R[cells] - want).max() <= 1e-12 * scale
     vol, _, _ = c.om.geometry()
     assert np.abs((vol[:, None] * R).sum(0)).max() <= 1e-12 * scale * vol.sum()
+
+
+@pytest.mark.parametrize("order,variant", [(3, 0), (3, 1), (3, 2), (4, 0), (4, 2)])
+def test_characteristic_past_the_first_blocks(oracle_mod, order, variant):
+    """576,738 cells: about twelve blocks per resident workgroup, so that the
+    Gram matrices of one block lie beside the staged members and the ids of the
+    next ones."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_02127_amd import teno
+    from test_gpu_parity import _sampled
+    _sampled(teno, oracle_mod, torch, 6, n_sample=160, characteristic=1, variant=variant,
+             order=order)
