@@ -100,6 +100,18 @@ constexpr int kSlotBits = 10;
 constexpr int row_groups(int nrow) { return (nrow + 3) / 4; }
 constexpr int lane_groups(int nl) { return 3 * row_groups(kSmallRows) + row_groups(nl); }
 constexpr int slot_words(int nl) { return (lane_groups(nl) + 2) / 3; }
+// Cells of which a stencil's normal matrix would cost digits (setup.cpp,
+// normal_bound) are solved with the operators of all four stencils instead, four
+// to a wavefront: lane h of a cell's sixteen owns rows 16j + h of each stencil.
+// M^T in the basis of the reference triangle, per four cells [chunk][64 lanes], a
+// chunk per group of rows and coefficient, stencil by stencil.  Rare: none on a
+// jittered periodic mesh.
+constexpr int kKeptCells = 4;
+constexpr int kept_row_groups(int nrow) { return (nrow + 15) / 16; }
+constexpr int kept_groups(int nl) { return 3 * kept_row_groups(kSmallRows) + kept_row_groups(nl); }
+constexpr int kept_chunks(int nl, int nu) {
+  return 3 * kept_row_groups(kSmallRows) * kSmallCoef + kept_row_groups(nl) * nu;
+}
 constexpr int adj_words(int nl) { return (lane_groups(nl) + 1) / 2; }  // 16 bits each
 
 void set_error(const std::string& msg);
@@ -161,13 +173,18 @@ struct Mesh {
   std::vector<double> jac;         // [n_pad][4]: a third of the map's columns, block frame
   std::vector<float> centre;       // [n_pad][4][2]: centre of each stencil's basis, block
                                    // frame, relative to the cell
+  // cells solved with operators (-1 in pack)
+  std::vector<int32_t> kept;       // [kKeptCells n] internal cell, -1: none
+  std::vector<int32_t> kept_rows;  // [n][kept_groups][64] member of each row (no row: the cell)
+  std::vector<double> kept_ops;    // [n][kept_chunks][64]
   // adjoint accumulation order, by lane and row group as bslot, 16 bits each,
   // [n_tiles][adj_words][64]: slot in the tile's list | round << 9, where
   // round = how many earlier lanes of the row group name the same member
   std::vector<uint32_t> aslot;
   // reverse member lists (adjoint gather): the tile member slots naming cell j
   std::vector<int32_t> rev_ptr; // [n_cell + 1]
-  std::vector<int32_t> rev_ent; // tile * ustride + slot, by tile
+  std::vector<int32_t> rev_ent; // tile * ustride + slot, by tile; then the rows of kept
+                                // cells, n_tiles * ustride + position in kept_rows
 };
 
 // Stencil row order of a cell: rows 0..32 hold the three small stencils

@@ -259,7 +259,8 @@ __device__ __forceinline__ void hll_vjp(const double uL[4], const double uR[4], 
 // binomial rule as monomials), about the mean of each stencil's members; N is
 // formed and inverted in extended precision.  Against 128 bits the face values
 // are closer than the stored operators' (rms error 0.44, 0.13, 0.07, 0.02 of
-// theirs at orders 3-6 on jittered meshes).
+// theirs at orders 3-6 on jittered meshes).  Set-up bounds every stencil's error
+// and leaves cells where it would exceed an operator's to k_reconstruct_kept.
 //
 // A block of wavefronts (16 cells each, four lanes per cell) stages the distinct
 // members of all its stencils in LDS: about 190 records and states for four
@@ -278,7 +279,7 @@ struct BlockArgs {
   const double2* __restrict__ N;       // [n_tiles][normal_quads][64]
   const double2* __restrict__ jac;     // [n_pad][2]
   const float2* __restrict__ centre;   // [n_pad][4] centre of each stencil's basis
-  const int* __restrict__ pack;        // [n_pad] cell of each packed position, -1: none
+  const int* __restrict__ pack;        // [n_pad] cell of each packed position, -1: none or kept
   int bwaves;                          // wavefronts (tiles) per block
   int mstride;                         // members of the mesh's largest block
   int bmax;                            // of all the launch's meshes: lays out the LDS
@@ -1374,6 +1375,60 @@ struct TileAhead {
   }
 };
 
+// Selection and face states of one cell per quad from its stencils' coefficients,
+// in conservative variables.
+template <int P, int NQ, bool CW>
+__device__ __forceinline__ void select_and_store(TENO_CONST ReconArgs& a, bool frozen,
+                                                 const double (&as)[3][5],
+                                                 double (&aK)[OrderT<P>::NU], double u0, int cell,
+                                                 bool live, int g, int v, int lane) {
+  using O = OrderT<P>;
+  constexpr int NU = O::NU, NP = 3 * NQ;
+  const unsigned nib_in = (frozen && live) ? ((a.flags[cell] >> (4 * v)) & 0xFu) : 8u;
+  int ties = 0;
+  unsigned nib = 0u;
+  if constexpr (CW)
+    cweno_combine<P>(a, as, aK);
+  else
+    nib = teno_select<P>(a, frozen, nib_in, as, aK, ties);
+  // ---- face Gauss points (variable v of this cell) ----
+  double val[NP];
+  static_for<0, NP>([&](auto q) {
+    double s = u0;
+    static_for<0, NU>([&](auto l) { s = fma(aK[l], FaceBasis<O::R, NQ>::P.v[q][l], s); });
+    val[q] = s;
+  });
+  // ---- non-physical states (all four lanes of a cell agree) ----
+  if (!frozen) {
+    QuadPhysical phys;
+    phys.init(v, a.gamma);
+    const bool avg_ok = quad_all(phys(u0), lane);
+    bool ok = true;
+    static_for<0, NP>([&](auto q) { ok = phys(val[q]) && ok; });
+    const bool fp_ok = quad_all(ok, lane);
+    if (live && g == 0 && !(avg_ok && fp_ok)) {  // one lane per cell
+      atomicAdd(&a.diag->nonphysical, 1ull);
+      atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
+    }
+    if (!fp_ok && avg_ok && a.fallback) {
+      static_for<0, NP>([&](auto q) { val[q] = u0; });
+      nib = 0u;
+      if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
+    }
+    if (live && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
+  }
+  if (live)
+    static_for<0, NP>([&](auto q) {
+      (a.fp + (size_t)q * a.n_pad * 4)[4u * cell + v] = val[q];
+    });
+  if (!frozen && a.flags) {
+    unsigned f = nib << (4 * v);
+    f |= __shfl_xor(f, 1);
+    f |= __shfl_xor(f, 2);
+    if (live && g == 0) a.flags[cell] = (uint16_t)f;
+  }
+}
+
 // Reconstruction of the blocks of a work list by one workgroup: items
 // [k0, k1) in steps, item k = (arguments, block) from items(k).  Two blocks are
 // staged in LDS: while one is computed, the next one's records and states are
@@ -1387,7 +1442,6 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
                                                  char* lds) {
   using O = OrderT<P>;
   constexpr int NU = O::NU, NL = O::NL, R = O::R;
-  constexpr int NP = 3 * NQ;
   constexpr int GS = row_groups(kSmallRows), QS = sym_quads(kSmallCoef);
   if (k0 >= k1) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1527,49 +1581,7 @@ __device__ __forceinline__ void reconstruct_loop(const Items& items, int k0, int
       }
       continue;
     }
-    const unsigned nib_in = (frozen && live) ? ((a.flags[cell] >> (4 * v)) & 0xFu) : 8u;
-    int ties = 0;
-    unsigned nib = 0u;
-    if constexpr (CW)
-      cweno_combine<P>(a, as, aK);
-    else
-      nib = teno_select<P>(a, frozen, nib_in, as, aK, ties);
-    // ---- face Gauss points (variable v of this cell) ----
-    double val[NP];
-    static_for<0, NP>([&](auto q) {
-      double s = u0;
-      static_for<0, NU>([&](auto l) { s = fma(aK[l], FaceBasis<O::R, NQ>::P.v[q][l], s); });
-      val[q] = s;
-    });
-    // ---- non-physical states (all four lanes of a cell agree) ----
-    if (!frozen) {
-      QuadPhysical phys;
-      phys.init(v, a.gamma);
-      const bool avg_ok = quad_all(phys(u0), lane);
-      bool ok = true;
-      static_for<0, NP>([&](auto q) { ok = phys(val[q]) && ok; });
-      const bool fp_ok = quad_all(ok, lane);
-      if (live && g == 0 && !(avg_ok && fp_ok)) {  // one lane per cell
-        atomicAdd(&a.diag->nonphysical, 1ull);
-        atomicMin(&a.diag->first_bad, (long long)a.user_of[cell]);
-      }
-      if (!fp_ok && avg_ok && a.fallback) {
-        static_for<0, NP>([&](auto q) { val[q] = u0; });
-        nib = 0u;
-        if (live && g == 0) atomicAdd(&a.diag->fallbacks, 1ull);
-      }
-      if (live && ties) atomicAdd(&a.diag->near_ties, (unsigned long long)ties);
-    }
-    if (live)
-      static_for<0, NP>([&](auto q) {
-        (a.fp + (size_t)q * a.n_pad * 4)[4u * cell + v] = val[q];
-      });
-    if (!frozen && a.flags) {
-      unsigned f = nib << (4 * v);
-      f |= __shfl_xor(f, 1);
-      f |= __shfl_xor(f, 2);
-      if (live && g == 0) a.flags[cell] = (uint16_t)f;
-    }
+    select_and_store<P, NQ, CW>(a, frozen, as, aK, u0, cell, live, g, v, lane);
   }
 }
 
@@ -1615,6 +1627,81 @@ __global__ __launch_bounds__(64 * block_tiles(P))
 __attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct_char(ReconArgs a,
                                                                               int n_blocks) {
   reconstruct_mesh<P, NQ, CW, true>(n_blocks);
+}
+
+// Cells solved with operators (internal.h), in sets of four.
+struct KeptArgs {
+  const int* __restrict__ cell;    // [4 n] -1: none
+  const int* __restrict__ rows;    // [n][kept_groups][64]
+  const double* __restrict__ ops;  // [n][kept_chunks][64]
+  int n;
+};
+
+// Sum over a cell's sixteen lanes of variable g, from sums x[i] of variable i ^ g:
+// the same bits in its four quads.
+__device__ __forceinline__ double kept_sum(const double (&x)[4]) {
+  double s = quad_sum(x);
+  s += quad_perm_dpp<0x128>(s);  // row_ror:8
+  s += quad_perm_dpp<0x124>(s);  // row_ror:4
+  return s;
+}
+
+// Their reconstruction, one wavefront per set, operators and members' states from
+// memory: sixteen lanes per cell, so that all loads of a wavefront are in flight at
+// once (few cells: what counts is the chain of loads, not their number).  The
+// selection is that of the other cells, done alike by the four quads of a cell, of
+// which the first writes.  5 to 8 us after the main launch (8,192 cells of a graded
+// sector, 1-5% of them kept, orders 3-6); four lanes per cell took 8 to 27.
+template <int N, int NR>
+__device__ __forceinline__ void operator_sums(const double* __restrict__ U,
+                                              const int* __restrict__ rows,
+                                              const double* __restrict__ M, int lane, int g,
+                                              const double (&u0)[4], double* c) {
+  double acc[N][4];
+  static_for<0, kept_row_groups(NR)>([&](auto j) {
+    const double* u = U + (size_t)rows[j * 64 + lane] * 4;
+    double d[4];
+    static_for<0, 4>([&](auto i) { d[i] = u[g ^ i] - u0[i]; });
+    static_for<0, N>([&](auto l) {
+      const double x = M[(j * N + l) * 64 + lane];
+      static_for<0, 4>([&](auto i) { acc[l][i] = j == 0 ? x * d[i] : fma(x, d[i], acc[l][i]); });
+    });
+  });
+  static_for<0, N>([&](auto l) { c[l] = kept_sum(acc[l]); });
+}
+
+template <int P, int NQ, bool CW, bool CH>
+__device__ __forceinline__ void reconstruct_kept(TENO_CONST ReconArgs& a, const KeptArgs& k, int set,
+                                                 double* gram) {
+  using O = OrderT<P>;
+  constexpr int NU = O::NU, NL = O::NL;
+  constexpr int GS = kept_row_groups(kSmallRows), CS = GS * kSmallCoef;
+  const int lane = threadIdx.x & 63, c = lane >> 2, g = lane & 3;
+  const int at = k.cell[set * kKeptCells + (lane >> 4)];
+  const int cell = max(at, 0);
+  const bool live = at >= 0 && (lane & 15) < 4;
+  const double* __restrict__ U = a.U;
+  const int* __restrict__ rows = k.rows + (size_t)set * (kept_groups(NL) * 64);
+  const double* __restrict__ M = k.ops + (size_t)set * (kept_chunks(NL, NU) * 64);
+  double u0[4], aK[NU], as[3][5];
+  static_for<0, 4>([&](auto i) { u0[i] = U[(size_t)cell * 4 + (g ^ i)]; });
+  static_for<0, 3>([&](auto q) {
+    operator_sums<kSmallCoef, kSmallRows>(U, rows + GS * q * 64, M + CS * q * 64, lane, g, u0, as[q]);
+  });
+  operator_sums<NU, NL>(U, rows + 3 * GS * 64, M + 3 * CS * 64, lane, g, u0, aK);
+  if constexpr (CH && CW)
+    char_edges_cweno_gram<P, NQ>(a, as, aK, u0[0], cell, live, g, g, c, lane, gram);
+  else if constexpr (CH)
+    char_edges_gram<P, NQ>(a, as, aK, u0[0], cell, live, g, g, c, lane, gram);
+  else
+    select_and_store<P, NQ, CW>(a, a.frozen != 0, as, aK, u0[0], cell, live, g, g, lane);
+}
+
+template <int P, int NQ, bool CW, bool CH>
+__global__ __launch_bounds__(64) void k_reconstruct_kept(ReconArgs, KeptArgs k) {
+  __shared__ double gram[CH ? kCharGramDoubles : 1];
+  reconstruct_kept<P, NQ, CW, CH>(
+      *(TENO_CONST ReconArgs*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr(), k, blockIdx.x, gram);
 }
 
 // ---------------------------------------------------------------------------
@@ -2024,7 +2111,7 @@ struct AdjReconArgs {
   const uint16_t* __restrict__ flags;
   BlockArgs b;
   const unsigned* __restrict__ aslot;  // [n_tiles][adj_words][64]: slot | round << 9
-  double* __restrict__ tbar;      // [n_tiles][ustride][4]
+  double* __restrict__ tbar;      // [n_tiles][ustride][4], then [kept rows][4]
   double* __restrict__ own;       // [n_pad][4]
   int ustride;
   int n_cell, n_tiles, n_pad;
@@ -2181,9 +2268,64 @@ __attribute__((amdgpu_waves_per_eu(adj_waves(P)))) void k_adj_recon(AdjReconArgs
   for (int i = lane; i < 4 * a.ustride; i += 64) tb[i] = acc[i];
 }
 
+// The same for the cells solved with operators, one wavefront per set of them.
+// What a row adds to its member goes to a place of its own in tbar (after the
+// tiles' sums), which the member's reverse list names.
+template <int N, int NR>
+__device__ __forceinline__ void adj_operator(const double* __restrict__ M, int lane, int g,
+                                             const double* ab, double* __restrict__ out,
+                                             double (&dq)[4]) {
+  static_for<0, kept_row_groups(NR)>([&](auto j) {
+    double d[4] = {0.0, 0.0, 0.0, 0.0};
+    static_for<0, N>([&](auto l) {
+      const double x = M[(j * N + l) * 64 + lane];
+      static_for<0, 4>([&](auto i) { d[i] = fma(x, quad_xor<i>(ab[l]), d[i]); });
+    });
+    if (16 * j + (lane & 15) < NR) static_for<0, 4>([&](auto i) {
+      dq[i] += d[i];
+      out[(j * 64 + lane) * 4 + (g ^ i)] = d[i];
+    });
+  });
+}
+
+template <int P, int NQ>
+__global__ __launch_bounds__(64) void k_adj_recon_kept(AdjReconArgs a, KeptArgs k) {
+  using O = OrderT<P>;
+  constexpr int NU = O::NU, NL = O::NL;
+  constexpr int GS = kept_row_groups(kSmallRows), CS = GS * kSmallCoef;
+  const int lane = threadIdx.x, v = lane & 3, set = blockIdx.x;
+  const int cell = k.cell[set * kKeptCells + (lane >> 4)];
+  const bool live = cell >= 0;
+  const int cl = live ? cell : 0;
+  const unsigned nib = live ? ((a.flags[cl] >> (4 * v)) & 0xFu) : 0u;
+  double gsum = 0.0, ab[NU];
+  static_for<0, NU>([&](auto l) { ab[l] = 0.0; });
+  static_for<0, 3 * NQ>([&](auto q) {
+    const double gq = live ? a.fpbar[((size_t)q * a.n_pad + cl) * 4 + v] : 0.0;
+    gsum += gq;
+    static_for<0, NU>([&](auto l) { ab[l] = fma(FaceBasis<O::R, NQ>::P.v[q][l], gq, ab[l]); });
+  });
+  const bool keepK = nib & 8u;
+  const int cnt = (int)(nib & 1u) + (int)((nib >> 1) & 1u) + (int)((nib >> 2) & 1u);
+  const double* __restrict__ M = k.ops + (size_t)set * (kept_chunks(NL, NU) * 64);
+  double* __restrict__ out =
+      a.tbar + ((size_t)a.n_tiles * a.ustride + (size_t)set * (kept_groups(NL) * 64)) * 4;
+  double dq[4] = {0.0, 0.0, 0.0, 0.0};
+  static_for<0, 3>([&](auto q) {
+    const double w = !keepK && ((nib >> q) & 1u) ? 1.0 / (double)cnt : 0.0;
+    double r[kSmallCoef];
+    static_for<0, kSmallCoef>([&](auto l) { r[l] = w * ab[l]; });
+    adj_operator<kSmallCoef, kSmallRows>(M + CS * q * 64, lane, v, r, out + GS * q * 256, dq);
+  });
+  static_for<0, NU>([&](auto l) { ab[l] = keepK ? ab[l] : 0.0; });
+  adj_operator<NU, NL>(M + 3 * CS * 64, lane, v, ab, out + 3 * GS * 256, dq);
+  const double dsum = kept_sum(dq);
+  if (live && (lane & 15) < 4) a.own[(size_t)cell * 4 + v] = gsum - dsum;
+}
+
 // Phase 3 (four lanes per cell, lane q = variable q): U_bar[j] = own[j] +
-// the tile sums of every tile member slot naming j (reverse list rev_ptr[j]
-// .. rev_ptr[j+1]-1, by tile), in list order: no atomics.  Then out = U_bar
+// the tile sums of every tile member slot naming j and the rows of kept cells
+// that do (reverse list rev_ptr[j] .. rev_ptr[j+1]-1), in list order: no atomics.  Then out = U_bar
 // + beta * extra (extra nullable).
 __global__ __launch_bounds__(256) void k_adj_gather(const double* __restrict__ own,
                                                     const double* __restrict__ tbar,
@@ -2230,6 +2372,7 @@ __global__ __launch_bounds__(256) void k_lincomb(double* out, double a1, const d
 // One mesh of a batch: the arguments of its three RK stages.
 struct BatchMeshDev {
   ReconArgs r[3];          // reconstruction input of stage k
+  KeptArgs kept;           // cells solved with operators
   FaceFluxArgs ff;         // face fluxes (the same buffers every stage)
   CellUpdateArgs cu[3];    // gather and update of stage k
   const double* U;         // cell averages at the start of the step
@@ -2297,6 +2440,26 @@ void k_batch_reconstruct_all(const BatchMeshDev* __restrict__ meshes,
       case 63: reconstruct_loop<6, 3, false, false>(it, i, i + 1, 1, lds); break;
       default: break;
     }
+  }
+}
+
+// Cells solved with operators, over (mesh, set of them) items of every order.
+__global__ __launch_bounds__(64) void k_batch_reconstruct_kept(
+    const BatchMeshDev* __restrict__ meshes, const int2* __restrict__ items, int stage_k) {
+  const int2 it = items[blockIdx.x];
+  const int m = __builtin_amdgcn_readfirstlane(it.x);
+  TENO_CONST ReconArgs& a = *(TENO_CONST ReconArgs*)(uintptr_t)&meshes[m].r[stage_k];
+  const KeptArgs k = meshes[m].kept;
+  switch (meshes[m].pq) {
+    case 32: reconstruct_kept<3, 2, false, false>(a, k, it.y, nullptr); break;
+    case 33: reconstruct_kept<3, 3, false, false>(a, k, it.y, nullptr); break;
+    case 42: reconstruct_kept<4, 2, false, false>(a, k, it.y, nullptr); break;
+    case 43: reconstruct_kept<4, 3, false, false>(a, k, it.y, nullptr); break;
+    case 52: reconstruct_kept<5, 2, false, false>(a, k, it.y, nullptr); break;
+    case 53: reconstruct_kept<5, 3, false, false>(a, k, it.y, nullptr); break;
+    case 62: reconstruct_kept<6, 2, false, false>(a, k, it.y, nullptr); break;
+    case 63: reconstruct_kept<6, 3, false, false>(a, k, it.y, nullptr); break;
+    default: break;
   }
 }
 

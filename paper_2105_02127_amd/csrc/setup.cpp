@@ -378,42 +378,45 @@ static Basis basis_of(int r) {
 }
 
 // Radon's seven-point rule (degree 5) on a triangle, barycentric form.
-struct Radon {
-  double l[7][3], w[7];
-  Radon() {
-    const double s15 = std::sqrt(15.0);
-    const double a1 = (6.0 - s15) / 21.0, a2 = (6.0 + s15) / 21.0;
-    const double w1 = (155.0 - s15) / 1200.0, w2 = (155.0 + s15) / 1200.0;
-    double pts[7][3] = {{1.0 / 3, 1.0 / 3, 1.0 / 3},
-                        {a1, a1, 1 - 2 * a1}, {a1, 1 - 2 * a1, a1}, {1 - 2 * a1, a1, a1},
-                        {a2, a2, 1 - 2 * a2}, {a2, 1 - 2 * a2, a2}, {1 - 2 * a2, a2, a2}};
-    double ww[7] = {9.0 / 40.0, w1, w1, w1, w2, w2, w2};
+template <class T>
+struct RadonRule {
+  T l[7][3], w[7];
+  RadonRule() {
+    const T s15 = std::sqrt((T)15);
+    const T a1 = (6 - s15) / 21, a2 = (6 + s15) / 21;
+    const T w1 = (155 - s15) / 1200, w2 = (155 + s15) / 1200;
+    T pts[7][3] = {{(T)1 / 3, (T)1 / 3, (T)1 / 3},
+                   {a1, a1, 1 - 2 * a1}, {a1, 1 - 2 * a1, a1}, {1 - 2 * a1, a1, a1},
+                   {a2, a2, 1 - 2 * a2}, {a2, 1 - 2 * a2, a2}, {1 - 2 * a2, a2, a2}};
+    T ww[7] = {(T)9 / 40, w1, w1, w1, w2, w2, w2};
     std::memcpy(l, pts, sizeof(l));
     std::memcpy(w, ww, sizeof(w));
   }
 };
+typedef RadonRule<double> Radon;
 
 // Householder QR of the m x n row-major matrix A, then
 //   Op[l][s] = (R^{-1} Q_1^T)[l][s] * scale[s].
-// Returns min|R_jj|/max|R_jj| (0 on breakdown).
-double pinv_scaled(int m, int n, std::vector<double>& A, const double* scale, double* Op) {
+// Returns min|R_jj|/max|R_jj| (0 on breakdown: not above `tiny`).
+template <class T>
+T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
   // A row-major [m][n]; Householder vectors stored in place below the diagonal
-  std::vector<double> vj(m), beta(n);
+  std::vector<T> vj(m), beta(n);
   for (int j = 0; j < n; ++j) {
-    double nrm2 = 0.0;
+    T nrm2 = 0.0;
     for (int i = j; i < m; ++i) nrm2 += A[(size_t)i * n + j] * A[(size_t)i * n + j];
-    double nrm = std::sqrt(nrm2);
-    if (nrm == 0.0) return 0.0;
-    double x0 = A[(size_t)j * n + j];
-    double alpha = x0 > 0.0 ? -nrm : nrm;
+    T nrm = std::sqrt(nrm2);
+    if (nrm == 0.0) return 0;
+    T x0 = A[(size_t)j * n + j];
+    T alpha = x0 > 0.0 ? -nrm : nrm;
     // v = x - alpha e_1, scaled to v_j = 1
-    double v0 = x0 - alpha;
+    T v0 = x0 - alpha;
     for (int i = j + 1; i < m; ++i) A[(size_t)i * n + j] /= v0;
-    double vv = 1.0;
+    T vv = 1.0;
     for (int i = j + 1; i < m; ++i) vv += A[(size_t)i * n + j] * A[(size_t)i * n + j];
     beta[j] = 2.0 / vv;
     for (int c = j + 1; c < n; ++c) {
-      double s = A[(size_t)j * n + c];
+      T s = A[(size_t)j * n + c];
       for (int i = j + 1; i < m; ++i) s += A[(size_t)i * n + j] * A[(size_t)i * n + c];
       s *= beta[j];
       A[(size_t)j * n + c] -= s;
@@ -421,35 +424,39 @@ double pinv_scaled(int m, int n, std::vector<double>& A, const double* scale, do
     }
     A[(size_t)j * n + j] = alpha;
   }
-  double rmax = 0.0, rmin = INFINITY;
+  T rmax = 0, rmin = INFINITY;
   for (int j = 0; j < n; ++j) {
-    double d = std::fabs(A[(size_t)j * n + j]);
+    T d = std::fabs(A[(size_t)j * n + j]);
     rmax = std::max(rmax, d);
     rmin = std::min(rmin, d);
   }
-  if (!(rmin > 1e-13 * rmax)) return 0.0;
+  if (!(rmin > tiny * rmax)) return 0;
   // Q_1 (m x n): apply H_{n-1} ... H_0 to the first n columns of I
-  std::vector<double> Q((size_t)m * n, 0.0);
+  std::vector<T> Q((size_t)m * n, 0.0);
   for (int j = 0; j < n; ++j) Q[(size_t)j * n + j] = 1.0;
   for (int j = n - 1; j >= 0; --j)
     for (int c = 0; c < n; ++c) {
-      double s = Q[(size_t)j * n + c];
+      T s = Q[(size_t)j * n + c];
       for (int i = j + 1; i < m; ++i) s += A[(size_t)i * n + j] * Q[(size_t)i * n + c];
       s *= beta[j];
       Q[(size_t)j * n + c] -= s;
       for (int i = j + 1; i < m; ++i) Q[(size_t)i * n + c] -= s * A[(size_t)i * n + j];
     }
   // Op[:, s] = R^{-1} Q_1[s, :]^T * scale[s]
-  std::vector<double> x(n);
+  std::vector<T> x(n);
   for (int s = 0; s < m; ++s) {
     for (int l = n - 1; l >= 0; --l) {
-      double acc = Q[(size_t)s * n + l];
+      T acc = Q[(size_t)s * n + l];
       for (int c = l + 1; c < n; ++c) acc -= A[(size_t)l * n + c] * x[c];
       x[l] = acc / A[(size_t)l * n + l];
     }
     for (int l = 0; l < n; ++l) Op[(size_t)l * m + s] = x[l] * scale[s];
   }
   return rmin / rmax;
+}
+
+double pinv_scaled(int m, int n, std::vector<double>& A, const double* scale, double* Op) {
+  return pinv_scaled<double>(m, n, A, scale, Op, 1e-13);
 }
 
 // Rows of the constrained system of one stencil of (user) cell i.
@@ -514,12 +521,15 @@ static uint32_t spread16(uint32_t x) {
 // displacements of its stencils (also on stretched and sheared meshes), the
 // polynomials are Hermite's, and each stencil's are centred on its members'
 // mean (one-sided small stencils, stencils at a wall).  The matrices are formed
-// and inverted in extended precision and stored in FP64.  Against quad
-// precision the face values of random data come out closer than with the
+// and inverted in extended precision and stored in FP64.  On jittered meshes
+// the face values of random data come out closer to 128 bits than with the
 // stored operators of the reference triangle's monomials (rms, orders 3-6:
 // x 0.3-0.02), and the rounding noise of their sums is x 0.7-1.9 of a
 // plain product M d (orders 3-6, boxes included; monomials about the target
-// would give x 2-55).
+// would give x 2-55).  On graded meshes a few stencils, one-sided ones above
+// all, would lose digits that their operators keep (to 2.6e-7 against 1e-10 on
+// a sector of 4 rad with radii 1 : e^6): normal_bound finds those, and their
+// cells keep their operators.
 typedef long double Ext;
 
 // E[H_a(x + X) H_b(y + Y)] for 0 <= a + b <= r from the central moments
@@ -600,6 +610,210 @@ static void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& 
       X[(size_t)i * n + j] = X[(size_t)j * n + i] = s;
     }
 }
+
+// Functions of the least-squares bases at nine points of a cell's edges (Gauss,
+// three per edge): in X = 3 xi - 1, Y = 3 eta - 1 (v), and in xi, eta (w), less
+// their means.
+struct FacePoints {
+  double v[9][20], w[9][20];
+  FacePoints(const Basis& B, const RadonRule<Ext>& rule) {
+    for (int l = 0; l < B.n; ++l) {
+      auto f = [&](Ext x, Ext y) {
+        Ext p = 1;
+        for (int i = 0; i < B.ea[l]; ++i) p *= x;
+        for (int i = 0; i < B.eb[l]; ++i) p *= y;
+        return p;
+      };
+      Ext mean = 0;
+      for (int g = 0; g < 7; ++g) mean += rule.w[g] * f(3 * rule.l[g][1] - 1, 3 * rule.l[g][2] - 1);
+      for (int q = 0; q < 9; ++q) {
+        const double t = 0.5 + (q % 3 - 1) * 0.5 * std::sqrt(0.6);
+        const double xi = q < 3 ? t : (q < 6 ? 1.0 - t : 0.0), eta = q < 3 ? 0.0 : (q < 6 ? t : 1.0 - t);
+        v[q][l] = (double)(f(3 * (Ext)xi - 1, 3 * (Ext)eta - 1) - mean);
+        w[q][l] = (double)f(xi, eta) - B.mean[l];
+      }
+    }
+  }
+};
+
+// What a normal matrix may cost.  Where the weights |V|^2 of a stencil's members
+// span orders of magnitude (a one-sided stencil of a graded mesh, completed with
+// far larger cells), or its members lie near a curve of the basis' degree, N has
+// lost the digits that its operator still has: the sums of the large members'
+// rows round at a size that the weak directions of N multiply.  A first-order
+// bound of that, for differences of size one: the rounded row sums (magnitudes of
+// the rows in `rows`) through |N|, the shift and expansion of the Hermite
+// functions and the map to the reference triangle, all with absolute values, at
+// the points of the cell's edges.  Rounding is random where the bound adds
+// magnitudes: errors against 128 bits reach it at most (jittered, stretched and
+// graded meshes, orders 3-6).
+static double normal_bound(int r, int n, const std::vector<Ext>& N, const double* rows, double cx,
+                           double cy, const double* J, const FacePoints& at) {
+  // magnitudes of the coefficients of x^(n-2k) in H_n, [n][k]
+  constexpr double h = kHermite;
+  static const double expand[6][3] = {{1}, {1}, {1, h}, {1, 3 * h}, {1, 6 * h, 3 * h * h}, {1, 10 * h, 15 * h * h}};
+  auto mono = [](int d, int k) { return d * (d + 1) / 2 - 1 + k; };
+  double c[20], t[20];
+  for (int i = 0; i < n; ++i) {
+    c[i] = 0.0;
+    for (int j = 0; j < n; ++j) c[i] += std::fabs((double)N[(size_t)i * n + j]) * rows[j];
+  }
+  cx = std::fabs(cx);
+  cy = std::fabs(cy);
+  for (int b = 0; b < r; ++b)
+    for (int i = 0; i < r - b; ++i)
+      for (int a = r - b - 1; a >= i; --a)
+        if (a + b >= 1) c[mono(a + b, b)] += cx * c[mono(a + b + 1, b)];
+  for (int a = 0; a < r; ++a)
+    for (int i = 0; i < r - a; ++i)
+      for (int b = r - a - 1; b >= i; --b)
+        if (a + b >= 1) c[mono(a + b, b)] += cy * c[mono(a + b + 1, b + 1)];
+  for (int axis = 0; axis < 2; ++axis)
+    for (int o = 0; o < r; ++o)
+      for (int e = 0; e <= r - o; ++e)  // e: the exponent that H_e expands
+        for (int k = 1; o + e >= 1 && o + e + 2 * k <= r; ++k) {
+          const int d = o + e + 2 * k;
+          c[mono(o + e, axis ? e : o)] += expand[e + 2 * k][k] * c[mono(d, axis ? e + 2 * k : o)];
+        }
+  double sum[20];
+  const double j0 = std::fabs(J[0]), j1 = std::fabs(J[1]), j2 = std::fabs(J[2]), j3 = std::fabs(J[3]);
+  for (int d = 1; d <= r; ++d) {  // sum of c_k (j0 X + j1 Y)^(d-k) (j2 X + j3 Y)^k
+    for (int q = 0; q <= d; ++q) t[q] = 0.0;
+    for (int k = 0; k <= d; ++k) {
+      double p[7] = {c[mono(d, k)]};
+      for (int i = 0; i < d; ++i) {
+        const double u = i < d - k ? j0 : j2, v = i < d - k ? j1 : j3;
+        for (int q = i + 1; q >= 0; --q) p[q] = (q <= i ? u * p[q] : 0.0) + (q > 0 ? v * p[q - 1] : 0.0);
+      }
+      for (int q = 0; q <= d; ++q) t[q] += p[q];
+    }
+    for (int q = 0; q <= d; ++q) sum[mono(d, q)] = t[q];
+  }
+  double worst = 0.0;
+  for (int q = 0; q < 9; ++q) {
+    double x = 0.0;
+    for (int l = 0; l < n; ++l) x += sum[l] * std::fabs(at.v[q][l]);
+    worst = std::max(worst, x);
+  }
+  return worst * 1.1e-16;
+}
+
+// M of one stencil (Op[l][s], l < B.n) of user cell i in extended precision, in
+// the basis X = 3 xi - 1, Y = 3 eta - 1 less its means; false on breakdown.
+// Solved in monomials of coordinates that give the members' centroids mean zero
+// and unit variance, then expanded.
+static bool extended_operator(const Mesh& m, const Basis& B, const RadonRule<Ext>& rule, int i,
+                              const int32_t* mem, int nrow, std::vector<Ext>& Op) {
+  const int n = B.n;
+  const double* X0 = &m.X[6 * (size_t)i];
+  const Ext j00 = (Ext)X0[2] - X0[0], j01 = (Ext)X0[4] - X0[0];
+  const Ext j10 = (Ext)X0[3] - X0[1], j11 = (Ext)X0[5] - X0[1];
+  const Ext det = j00 * j11 - j01 * j10;
+  std::vector<Ext> q((size_t)nrow * 6), A((size_t)nrow * n), vol(nrow);  // q: vertices (X, Y)
+  Ext mx = 0, my = 0, sxx = 0, sxy = 0, syy = 0;
+  auto centroid = [&](int s, int a) { return (q[6 * s + a] + q[6 * s + 2 + a] + q[6 * s + 4 + a]) / 3; };
+  for (int s = 0; s < nrow; ++s) {
+    const int j = mem[s];
+    double dx = m.cen[2 * (size_t)j] - m.cen[2 * (size_t)i];
+    double dy = m.cen[2 * (size_t)j + 1] - m.cen[2 * (size_t)i + 1], kx, ky;
+    wrap_delta(m, dx, dy, kx, ky);
+    const double* Xj = &m.X[6 * (size_t)j];
+    for (int v = 0; v < 3; ++v) {
+      const Ext px = (Ext)Xj[2 * v] - (Ext)m.P[0] * kx - X0[0];
+      const Ext py = (Ext)Xj[2 * v + 1] - (Ext)m.P[1] * ky - X0[1];
+      q[6 * s + 2 * v] = 3 * (j11 * px - j01 * py) / det - 1;
+      q[6 * s + 2 * v + 1] = 3 * (j00 * py - j10 * px) / det - 1;
+    }
+    const Ext* t = &q[6 * s];
+    vol[s] = ((t[2] - t[0]) * (t[5] - t[1]) - (t[4] - t[0]) * (t[3] - t[1])) / 18;
+    mx += centroid(s, 0) / nrow;
+    my += centroid(s, 1) / nrow;
+  }
+  for (int s = 0; s < nrow; ++s) {
+    const Ext x = centroid(s, 0) - mx, y = centroid(s, 1) - my;
+    sxx += x * x / nrow;
+    sxy += x * y / nrow;
+    syy += y * y / nrow;
+  }
+  // x = ax (X - mx), y = bx (X - mx) + by (Y - my)
+  const Ext l11 = std::sqrt(sxx), l21 = sxy / l11;
+  Ext l22 = syy - l21 * l21;
+  l22 = l22 > 1e-24L * syy ? std::sqrt(l22) : std::sqrt(syy);
+  const Ext ax = 1 / l11, bx = -l21 / (l11 * l22), by = 1 / l22;
+  auto averages = [&](const Ext* t, Ext* out) {
+    for (int l = 0; l < n; ++l) out[l] = 0;
+    for (int g = 0; g < 7; ++g) {
+      Ext X = -mx, Y = -my, px[6], py[6];
+      for (int v = 0; v < 3; ++v) {
+        X += rule.l[g][v] * t[2 * v];
+        Y += rule.l[g][v] * t[2 * v + 1];
+      }
+      px[0] = py[0] = 1;
+      for (int e = 1; e < 6; ++e) {
+        px[e] = px[e - 1] * (ax * X);
+        py[e] = py[e - 1] * (bx * X + by * Y);
+      }
+      for (int l = 0; l < n; ++l) out[l] += rule.w[g] * px[B.ea[l]] * py[B.eb[l]];
+    }
+  };
+  const Ext ref[6] = {-1, -1, 2, -1, -1, 2};
+  Ext mean[20], av[20];
+  averages(ref, mean);
+  for (int s = 0; s < nrow; ++s) {
+    averages(&q[6 * s], av);
+    for (int l = 0; l < n; ++l) A[(size_t)s * n + l] = vol[s] * (av[l] - mean[l]);
+  }
+  std::vector<Ext> c((size_t)n * nrow, 0);
+  if (!(pinv_scaled<Ext>(nrow, n, A, vol.data(), c.data(), 0.0L) > 0)) return false;
+  // each function's polynomial in X, Y: p[a][b] of X^a Y^b
+  Op.assign((size_t)n * nrow, 0);
+  for (int l = 0; l < n; ++l) {
+    Ext p[6][6] = {{1}};
+    const int deg = B.ea[l] + B.eb[l];
+    for (int e = 0; e < deg; ++e) {
+      const Ext u = e < B.ea[l] ? ax : bx, v = e < B.ea[l] ? 0 : by, w = -u * mx - v * my;
+      for (int a = e + 1; a >= 0; --a)
+        for (int b = e + 1 - a; b >= 0; --b)
+          p[a][b] = w * p[a][b] + (a > 0 ? u * p[a - 1][b] : 0) + (b > 0 ? v * p[a][b - 1] : 0);
+    }
+    for (int k = 0; k < n; ++k)
+      if (B.ea[k] + B.eb[k] <= deg)
+        for (int s = 0; s < nrow; ++s) Op[(size_t)k * nrow + s] += p[B.ea[k]][B.eb[k]] * c[(size_t)l * nrow + s];
+  }
+  return true;
+}
+
+// ... and what the stored operator costs that is formed in FP64 in the reference
+// triangle's monomials (lsq_rows, pinv_scaled), for the same differences: its error
+// against `op` and the rounding of its sums.
+static double operator_error(const Mesh& m, const Basis& B, const Radon& rule, int i, const int32_t* mem,
+                             int nrow, const std::vector<Ext>& op, const FacePoints& at) {
+  const int n = B.n;
+  std::vector<double> A, vol, dbl((size_t)n * nrow);
+  lsq_rows(m, B, rule, i, mem, nrow, A, vol);
+  if (pinv_scaled(nrow, n, A, vol.data(), dbl.data()) == 0.0) return 0.0;
+  double worst = 0.0;
+  for (int q = 0; q < 9; ++q) {
+    double t = 0.0;
+    for (int s = 0; s < nrow; ++s) {
+      Ext x = 0, e = 0;
+      for (int l = 0; l < n; ++l) {
+        x += op[(size_t)l * nrow + s] * at.v[q][l];
+        e += (Ext)dbl[(size_t)l * nrow + s] * at.w[q][l];
+      }
+      t += std::fabs((double)(e - x)) + 1.1e-16 * std::fabs((double)x);
+    }
+    worst = std::max(worst, t);
+  }
+  return worst;
+}
+
+// A cell is solved with operators where the bound of a stencil is above both a
+// floor (values of size one) and a multiple of that.  Errors are 0.1-0.2 of the
+// bound where it is large (small stencils; 0.05-0.1 the large one) and 0.2-0.7 of
+// operator_error: these ratios are where the two meet.
+constexpr double kBoundFloor = 2e-13;
+constexpr double bound_ratio(bool big) { return big ? 20.0 : 10.0; }
 
 // A stencil member as a block sees it: the cell and its periodic image.
 struct Image {
@@ -720,20 +934,17 @@ static void pack_blocks(Mesh& m) {
   m.N.resize((size_t)m.n_tiles * nq4 * 128);
   m.jac.resize((size_t)m.n_pad * 4);
   m.centre.assign((size_t)m.n_pad * 8, 0.0f);
-  // Radon's rule of degree 5, exact for every moment needed
-  Ext rl[7][3], rw[7];
-  {
-    const Ext s15 = std::sqrt((Ext)15);
-    const Ext a1 = (6 - s15) / 21, a2 = (6 + s15) / 21;
-    rw[0] = (Ext)9 / 40;
-    rl[0][0] = rl[0][1] = rl[0][2] = (Ext)1 / 3;
-    for (int h = 0; h < 2; ++h)
-      for (int k = 0; k < 3; ++k) {
-        const Ext a = h ? a2 : a1;
-        for (int j = 0; j < 3; ++j) rl[1 + 3 * h + k][j] = j == k ? 1 - 2 * a : a;
-        rw[1 + 3 * h + k] = (h ? 155 + s15 : 155 - s15) / 1200;
-      }
-  }
+  // exact for every moment needed (degree 5)
+  const RadonRule<Ext> rule;
+  const Radon rule64;
+  const Basis Bs = basis_of(2), Bl = basis_of(r);
+  const FacePoints at_small(Bs, rule), at_large(Bl, rule);
+  std::vector<uint8_t> keep(m.n_pad, 0);  // solved with operators, by packed position
+  auto users = [&](int cell, int k, int32_t* mem) {  // members of stencil k, user ids
+    const int nrow = k == 3 ? d.nl : kSmallRows;
+    for (int s = 0; s < nrow; ++s)
+      mem[s] = m.perm[m.idx[packed_idx_index(m, cell, k == 3 ? large_row(s) : small_row(k, s))]];
+  };
   parallel_for(n_blocks, m.prm.n_threads, [&](int b) {
     const std::vector<Image>& u = lists[b];
     const int cells = m.bwaves * kTile;
@@ -783,8 +994,8 @@ static void pack_blocks(Mesh& m) {
       for (int g = 0; g < 7; ++g) {
         Ext x = 0, y = 0;
         for (int v = 0; v < 3; ++v) {
-          x += rl[g][v] * q[v][0];
-          y += rl[g][v] * q[v][1];
+          x += rule.l[g][v] * q[v][0];
+          y += rule.l[g][v] * q[v][1];
         }
         hx[g][0] = hy[g][0] = 1;
         hx[g][1] = x;
@@ -798,7 +1009,7 @@ static void pack_blocks(Mesh& m) {
       for (int deg = 2; deg <= r; ++deg)
         for (int e = deg; e >= 0; --e, ++l) {
           Ext s = 0;
-          for (int g = 0; g < 7; ++g) s += rw[g] * hx[g][e] * hy[g][deg - e];
+          for (int g = 0; g < 7; ++g) s += rule.w[g] * hx[g][e] * hy[g][deg - e];
           R[l] = (double)s;
         }
       m.bmem[(size_t)b * m.bmax + k] = u[k].id;
@@ -814,7 +1025,8 @@ static void pack_blocks(Mesh& m) {
       for (int deg = 2; deg <= r; ++deg)
         for (int e = deg; e >= 0; --e, ++l) mu[e][deg - e] = R[l];
     };
-    std::vector<Ext> A, X;
+    std::vector<Ext> A, X, op;
+    int32_t mem[64];
     for (int c = 0; c < cells; ++c) {
       const int t = t0 + c, tile = t / kTile, tc = t % kTile;
       if (tile >= m.n_tiles) break;
@@ -876,6 +1088,7 @@ static void pack_blocks(Mesh& m) {
         m.centre[((size_t)t * 4 + k) * 2] = fx;
         m.centre[((size_t)t * 4 + k) * 2 + 1] = fy;
         shift_moments(rk, -(Ext)fx, -(Ext)fy, mu0, own);
+        double size[20] = {};
         for (int s = 0; s < nrow; ++s) {
           Ext mu[6][6], sh[6][6];
           moments(slots[s], mu);
@@ -884,10 +1097,22 @@ static void pack_blocks(Mesh& m) {
           const Ext w = std::sqrt((Ext)R[2]);
           int l = 0;
           for (int deg = 1; deg <= rk; ++deg)
-            for (int e = deg; e >= 0; --e, ++l)
+            for (int e = deg; e >= 0; --e, ++l) {
               A[(size_t)s * n + l] = w * (sh[e][deg - e] - own[e][deg - e]);
+              size[l] += R[2] * (std::fabs((double)sh[e][deg - e]) + std::fabs((double)own[e][deg - e]));
+            }
         }
         normal_inverse(nrow, n, A, X);
+        const Basis& B = big ? Bl : Bs;
+        const double bound = normal_bound(rk, n, X, size, fx, fy, J, big ? at_large : at_small);
+        if (!(bound <= kBoundFloor) && !keep[t]) {
+          const int user = m.perm[m.pack[t]];
+          users(m.pack[t], k, mem);
+          if (extended_operator(m, B, rule, user, mem, nrow, op) &&
+              !(bound <= bound_ratio(big) * operator_error(m, B, rule64, user, mem, nrow, op,
+                                                      big ? at_large : at_small)))
+            keep[t] = 1;
+        }
         int j = 0;
         for (int i = 0; i < n; ++i)
           for (int q = i; q < n; ++q, ++j)
@@ -897,6 +1122,44 @@ static void pack_blocks(Mesh& m) {
       }
     }
   }, 1);
+  // ---- cells solved with operators ----
+  std::vector<int32_t> at;  // packed position of each
+  for (int t = 0; t < nc; ++t)
+    if (keep[t]) at.push_back(t);
+  const int n_kept = (int)(at.size() + kKeptCells - 1) / kKeptCells;
+  const int groups = kept_groups(d.nl), chunks = kept_chunks(d.nl, nu);
+  m.kept.assign((size_t)n_kept * kKeptCells, -1);
+  m.kept_rows.assign((size_t)n_kept * groups * 64, 0);
+  m.kept_ops.assign((size_t)n_kept * chunks * 64, 0.0);
+  parallel_for((int)at.size(), m.prm.n_threads, [&](int i) {
+    const int cell = m.pack[at[i]], set = i / kKeptCells, lane = i % kKeptCells * 16;
+    int32_t* rows = &m.kept_rows[(size_t)set * groups * 64 + lane];
+    double* out = &m.kept_ops[(size_t)set * chunks * 64 + lane];
+    std::vector<Ext> op[4];
+    int32_t mem[64];
+    for (int k = 0; k < 4; ++k) {
+      users(cell, k, mem);
+      if (!extended_operator(m, k == 3 ? Bl : Bs, rule, m.perm[cell], mem, k == 3 ? d.nl : kSmallRows, op[k])) {
+        keep[at[i]] = 0;  // (set-up has refused meshes where this could be)
+        return;
+      }
+    }
+    m.kept[i] = cell;
+    int grp = 0, chunk = 0;
+    for (int k = 0; k < 4; ++k) {
+      const int nrow = k == 3 ? d.nl : kSmallRows, n = k == 3 ? nu : kSmallCoef;
+      for (int s = 0; s < kept_row_groups(nrow) * 16; ++s) {
+        rows[(size_t)(grp + s / 16) * 64 + s % 16] =
+            s < nrow ? m.idx[packed_idx_index(m, cell, k == 3 ? large_row(s) : small_row(k, s))] : cell;
+        for (int l = 0; l < n && s < nrow; ++l)
+          out[((size_t)chunk + (s / 16) * n + l) * 64 + s % 16] = (double)op[k][(size_t)l * nrow + s];
+      }
+      grp += kept_row_groups(nrow);
+      chunk += kept_row_groups(nrow) * n;
+    }
+  }, 1);
+  for (int t : at)
+    if (keep[t]) m.pack[t] = -1;
 }
 
 int mesh_setup(Mesh& m, const teno_params& p) {
@@ -1112,8 +1375,9 @@ int mesh_setup(Mesh& m, const teno_params& p) {
     m.aslot.assign((size_t)m.n_tiles * nw * 64, 0);
     parallel_for(m.n_tiles, p.n_threads, [&](int tile) {
       std::vector<int32_t>& u = lists[tile];
-      for (int t = tile * kTile; t < std::min(nc, (tile + 1) * kTile); ++t)
-        for (int r = 0; r < d.rows; ++r) u.push_back(m.idx[packed_idx_index(m, m.pack[t], r)]);
+      for (int t = tile * kTile; t < (tile + 1) * kTile; ++t)
+        for (int r = 0; r < d.rows && m.pack[t] >= 0; ++r)
+          u.push_back(m.idx[packed_idx_index(m, m.pack[t], r)]);
       std::sort(u.begin(), u.end());
       u.erase(std::unique(u.begin(), u.end()), u.end());
       int cur = umax.load();
@@ -1133,7 +1397,7 @@ int mesh_setup(Mesh& m, const teno_params& p) {
           std::fill(seen.begin(), seen.end(), 0);
           for (int lane = 0; lane < 64; ++lane) {
             const int t = tile * kTile + lane / 4, row = 4 * j + lane % 4;
-            if (t >= nc || row >= nrow) continue;
+            if (m.pack[t] < 0 || row >= nrow) continue;
             const int id = m.idx[packed_idx_index(m, m.pack[t], r0 + row)];
             const int s = (int)(std::lower_bound(u.begin(), u.end(), id) - u.begin());
             as[(size_t)(grp / 2) * 64 + lane] |= (uint32_t)((s & 511) | seen[s]++ << 9) << (16 * (grp % 2));
@@ -1159,6 +1423,17 @@ int mesh_setup(Mesh& m, const teno_params& p) {
   m.rev_ptr.assign(nc + 1, 0);
   for (int tile = 0; tile < m.n_tiles; ++tile)
     for (int k = 0; k < m.tcount[tile]; ++k) m.rev_ptr[m.tmem[(size_t)tile * m.ustride + k] + 1]++;
+  // a kept cell's rows, one entry each
+  auto kept_row = [&](size_t e) {  // whether entry e of kept_rows is a row
+    const int lane = e % 64, grp = (int)(e / 64 % kept_groups(d.nl));
+    const int gs = kept_row_groups(kSmallRows), j = grp < 3 * gs ? grp % gs : grp - 3 * gs;
+    return m.kept[e / 64 / kept_groups(d.nl) * kKeptCells + lane / 16] >= 0 &&
+           16 * j + lane % 16 < (grp < 3 * gs ? kSmallRows : d.nl);
+  };
+  for (size_t e = 0; e < m.kept_rows.size(); ++e)
+    if (kept_row(e)) m.rev_ptr[m.kept_rows[e] + 1]++;
+  if ((int64_t)m.n_tiles * m.ustride + (int64_t)m.kept_rows.size() > INT32_MAX)
+    return fail(TENO_EARG, "mesh too large: adjoint entries exceed 32-bit indices");
   for (int t = 0; t < nc; ++t) m.rev_ptr[t + 1] += m.rev_ptr[t];
   m.rev_ent.assign(std::max<int32_t>(1, m.rev_ptr[nc]), 0);
   {
@@ -1168,6 +1443,8 @@ int mesh_setup(Mesh& m, const teno_params& p) {
         const int j = m.tmem[(size_t)tile * m.ustride + k];
         m.rev_ent[fill[j]++] = tile * m.ustride + k;
       }
+    for (size_t e = 0; e < m.kept_rows.size(); ++e)
+      if (kept_row(e)) m.rev_ent[fill[m.kept_rows[e]]++] = m.n_tiles * m.ustride + (int32_t)e;
   }
   m.ready = true;
   return TENO_OK;

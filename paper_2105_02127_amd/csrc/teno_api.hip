@@ -78,6 +78,10 @@ struct teno_solver {
   double2* N = nullptr;
   double2* jac = nullptr;
   float2* centre = nullptr;
+  int* kept = nullptr;      // cells solved with operators
+  int* kept_rows = nullptr;
+  double* kept_ops = nullptr;
+  int n_kept = 0;
   int bwaves = 0, bmax = 0, nbuf = 2, n_blocks = 0;
   int recon_groups = 1;     // reconstruction workgroups that the chip holds at once
   unsigned* aslot = nullptr;    // adjoint: tile member slot and accumulation round per row
@@ -200,6 +204,8 @@ static BlockArgs block_args(const teno_solver* s) {
   return b;
 }
 
+static KeptArgs kept_args(const teno_solver* s) { return {s->kept, s->kept_rows, s->kept_ops, s->n_kept}; }
+
 // Dynamic LDS of one reconstruction workgroup.
 static size_t recon_lds(const Dims& d, int waves, int bmax, int nbuf, bool characteristic) {
   return (size_t)group_lds_bytes(buffer_stride(d.nu, bmax, waves, characteristic), bmax, nbuf);
@@ -217,16 +223,17 @@ static int resident_groups(K kernel, int threads, size_t lds, int device) {
   return std::max(1, cus) * std::max(1, per);
 }
 
-// f(kernel) with the reconstruction kernel of a solver's order and scheme.
+// f(kernel, kept) with the reconstruction kernel of a solver's order and scheme and
+// that of its cells solved with operators.
 template <class F>
 static void recon_kernel(const teno_solver* s, F&& f) {
   const bool cw = s->prm.variant == 2, ch = s->prm.characteristic != 0;
   dispatch(s->d.order, s->d.nq, [&](auto P, auto NQ) {
     constexpr int p = decltype(P)::value, nq = decltype(NQ)::value;
-    if (ch && cw) f(k_reconstruct_char<p, nq, true>);
-    else if (ch) f(k_reconstruct_char<p, nq, false>);
-    else if (cw) f(k_reconstruct<p, nq, true>);
-    else f(k_reconstruct<p, nq, false>);
+    if (ch && cw) f(k_reconstruct_char<p, nq, true>, k_reconstruct_kept<p, nq, true, true>);
+    else if (ch) f(k_reconstruct_char<p, nq, false>, k_reconstruct_kept<p, nq, false, true>);
+    else if (cw) f(k_reconstruct<p, nq, true>, k_reconstruct_kept<p, nq, true, false>);
+    else f(k_reconstruct<p, nq, false>, k_reconstruct_kept<p, nq, false, false>);
   });
 }
 
@@ -261,10 +268,12 @@ int launch_reconstruct(teno_solver* s, const double* U, uint16_t* flags, bool fr
   a.cw_dK = 1.0 - 1.0 / s->prm.dk_prime;
   a.cw_ds = (1.0 - a.cw_dK) / 3.0;
   int rc = TENO_OK;
-  recon_kernel(s, [&](auto kernel) {
+  recon_kernel(s, [&](auto kernel, auto kept) {
     rc = timed(s, 0, st, [&]() {
       hipLaunchKernelGGL(kernel, dim3(std::min(s->n_blocks, s->recon_groups)),
                          dim3(64 * s->bwaves), recon_lds(s), st, a, s->n_blocks);
+      if (s->n_kept > 0)
+        hipLaunchKernelGGL(kept, dim3(s->n_kept), dim3(64), 0, st, a, kept_args(s));
     });
   });
   return rc;
@@ -397,6 +406,9 @@ int launch_vjp(teno_solver* s, const double* U, const uint16_t* flags, const dou
                          (size_t)16 * rec_units(s->d.nu) * s->bmax +
                              (size_t)s->bwaves * s->ustride * 4 * sizeof(double),
                          st, ra);
+      if (s->n_kept > 0)
+        hipLaunchKernelGGL((k_adj_recon_kept<decltype(P)::value, decltype(NQ)::value>),
+                           dim3(s->n_kept), dim3(64), 0, st, ra, kept_args(s));
       hipLaunchKernelGGL(k_adj_gather, dim3(qblocks), dim3(256), 0, st, s->own, s->tbar,
                          s->rev_ptr, s->rev_ent, s->n_cell, extra, beta, out);
     });
@@ -606,6 +618,12 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
   A(s->N, m.N.size() / 2);
   A(s->jac, m.jac.size() / 2);
   A(s->centre, m.centre.size() / 2);
+  s->n_kept = (int)m.kept.size() / kKeptCells;
+  if (s->n_kept > 0) {
+    A(s->kept, m.kept.size());
+    A(s->kept_rows, m.kept_rows.size());
+    A(s->kept_ops, m.kept_ops.size());
+  }
   A(s->aslot, m.aslot.size());
   A(s->nbinfo, np);
   s->n_face = m.nf;
@@ -624,7 +642,7 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
   A(s->rev_ent, std::max<size_t>(1, m.rev_ent.size()));
   A(s->fp, (size_t)3 * m.d.nq * np * 4);
   A(s->fpbar, (size_t)3 * m.d.nq * np * 4);
-  A(s->tbar, (size_t)m.n_tiles * m.ustride * 4);
+  A(s->tbar, ((size_t)m.n_tiles * m.ustride + m.kept_rows.size()) * 4);
   A(s->own, np * 4);
   A(s->W1, nc * 4);
   A(s->W2, nc * 4);
@@ -649,6 +667,9 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
              {s->N, m.N.data(), m.N.size() * sizeof(double)},
              {s->jac, m.jac.data(), m.jac.size() * sizeof(double)},
              {s->centre, m.centre.data(), m.centre.size() * sizeof(float)},
+             {s->kept, m.kept.data(), m.kept.size() * sizeof(int32_t)},
+             {s->kept_rows, m.kept_rows.data(), m.kept_rows.size() * sizeof(int32_t)},
+             {s->kept_ops, m.kept_ops.data(), m.kept_ops.size() * sizeof(double)},
              {s->aslot, m.aslot.data(), m.aslot.size() * sizeof(uint32_t)},
              {s->nbinfo, m.nbinfo.data(), m.nbinfo.size() * sizeof(int32_t)},
              {s->bkind, m.bkind.data(), m.bkind.size() * sizeof(int32_t)},
@@ -670,7 +691,7 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
       return hip_fail(e, "hipMemcpy upload");
     }
   }
-  recon_kernel(s, [&](auto kernel) {
+  recon_kernel(s, [&](auto kernel, auto) {
     s->recon_groups = resident_groups(kernel, 64 * s->bwaves, recon_lds(s), device);
   });
   hipLaunchKernelGGL(k_diag_reset, dim3(1), dim3(64), 0, 0, s->diag);
@@ -923,6 +944,7 @@ struct teno_batch {
   BatchMeshDev* meshes = nullptr;
   int2* items_r = nullptr;     // reconstruction items, all orders
   int* start_r = nullptr;      // wave starts per launch, concatenated
+  int2* items_k = nullptr;     // sets of cells solved with operators
   int2* items_f = nullptr;     // face items (64-face chunks)
   int* start_f = nullptr;
   int2* items_c = nullptr;     // cell items (64-cell chunks)
@@ -939,7 +961,7 @@ struct teno_batch {
   };
   std::vector<RLaunch> rplan;
   std::vector<int> bmax, nbuf;  // per mesh: LDS layout of its launch (the largest block)
-  int n_waves_f = 0, n_waves_c = 0, n_items_dt = 0, n_items_b = 0;
+  int n_waves_f = 0, n_waves_c = 0, n_items_dt = 0, n_items_b = 0, n_items_k = 0;
   // graph of one step: its kernels read every pointer from the device
   // descriptors, so it stays valid while only the descriptors change
   hipGraph_t graph = nullptr;
@@ -1120,6 +1142,10 @@ int batch_plan(teno_batch* b) {
   for (int m : morder)
     for (int u = 0; u < (b->sv[m]->n_bface + 63) / 64; ++u) bitems.push_back(make_int2(m, u));
   b->n_items_b = (int)bitems.size();
+  std::vector<int2> kitems;
+  for (int m : morder)
+    for (int u = 0; u < b->sv[m]->n_kept; ++u) kitems.push_back(make_int2(m, u));
+  b->n_items_k = (int)kitems.size();
   for (int m = 0; m < n; ++m) {
     dstart[m] = (int)ditems.size();
     for (int u = 0; u < (b->sv[m]->n_cell + 255) / 256; ++u) ditems.push_back(make_int2(m, u));
@@ -1144,6 +1170,7 @@ int batch_plan(teno_batch* b) {
   A(b->start_dt, dstart.size());
   A(b->partial, ditems.size());
   A(b->items_b, bitems.size());
+  A(b->items_k, kitems.size());
   if (rc) return rc;
   struct Up {
     void* d;
@@ -1157,7 +1184,8 @@ int batch_plan(teno_batch* b) {
              {b->start_c, cstart.data(), cstart.size() * sizeof(int)},
              {b->items_dt, ditems.data(), ditems.size() * sizeof(int2)},
              {b->start_dt, dstart.data(), dstart.size() * sizeof(int)},
-             {b->items_b, bitems.data(), bitems.size() * sizeof(int2)}};
+             {b->items_b, bitems.data(), bitems.size() * sizeof(int2)},
+             {b->items_k, kitems.data(), kitems.size() * sizeof(int2)}};
   for (auto& u : ups) {
     if (u.bytes == 0) continue;
     hipError_t e = hipMemcpy(u.d, u.h, u.bytes, hipMemcpyHostToDevice);
@@ -1228,6 +1256,7 @@ int batch_descriptors(teno_batch* b, double* const* U, const double* dt, hipStre
     f.gamma = s->prm.gamma;
     f.n_face = s->n_face;
     f.n_pad = s->n_pad;
+    d.kept = kept_args(s);
     d.U = U[m];
     d.geo = s->geo;
     d.dt = dt ? const_cast<double*>(dt) + m : nullptr;
@@ -1274,6 +1303,9 @@ void batch_launch_recon(teno_batch* b, int k, hipStream_t st) {
       default: break;
     }
   }
+  if (b->n_items_k > 0)
+    hipLaunchKernelGGL(k_batch_reconstruct_kept, dim3(b->n_items_k), dim3(64), 0, st, b->meshes,
+                       b->items_k, k);
 }
 
 void batch_launch_step(teno_batch* b, hipStream_t st) {

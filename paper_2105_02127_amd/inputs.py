@@ -134,6 +134,24 @@ def jittered_box_mesh(nx: int, ny: int, seed: int, lx: float = 1.0, ly: float = 
                     seed=seed, rng=rng, box=(x0, y0, lx, ly))
 
 
+def graded_sector_mesh(n: int, seed: int, angle: float, growth: float,
+                       jitter: float = 0.2) -> MeshData:
+    """N x N x 2 jittered triangulation of a sector of `angle` radians with open
+    sides, radii 1 to e^growth in geometric steps: cells of about one shape whose
+    size grows with the radius."""
+    rng = np.random.default_rng(seed)
+    ii, jj = np.meshgrid(np.arange(n + 1.0), np.arange(n + 1.0), indexing="ij")
+    d = rng.uniform(-jitter, jitter, size=(2, n - 1, n - 1))
+    ii[1:-1, 1:-1] += d[0]
+    jj[1:-1, 1:-1] += d[1]
+    r, t = np.exp(growth * ii / n), angle * jj / n
+    xy = np.stack([r * np.cos(t), r * np.sin(t)], axis=-1).reshape(-1, 2)
+    a = (np.arange(n)[:, None] * (n + 1) + np.arange(n)).ravel()
+    tri = np.stack([np.stack([a, a + n + 1, a + n + 2], 1), np.stack([a, a + n + 2, a + 1], 1)], 1)
+    return MeshData(n=n, xy=np.ascontiguousarray(xy), tri=np.ascontiguousarray(
+        tri.reshape(-1, 3).astype(np.int32)), period=(0.0, 0.0), seed=seed, rng=rng)
+
+
 def unwrapped_vertices(mesh: MeshData) -> np.ndarray:
     """[n_cell, 3, 2] vertex coordinates with v1, v2 moved to the periodic
     image nearest to v0 (on the periodic axes)."""

@@ -60,3 +60,31 @@ def test_characteristic_block_layouts_of_meshes(driver, order, kind):
          "strip": lambda: inputs.jittered_box_mesh(400, 12, 4, lx=400.0, ly=12.0)}[kind]()
     s = _mesh(driver, m, order, characteristic=1)
     assert s["lds"] <= 160 * 1024
+
+
+# (angle, growth): radii 1 : e^growth over a sector of that angle; 0: a jittered
+# periodic mesh; -1: a box stretched eightfold
+@pytest.mark.parametrize("order", [3, 4, 5, 6])
+@pytest.mark.parametrize("angle,growth", [(4.0, 6.0), (4.0, 4.0), (1.5, 8.0), (1.5, 4.0), (0, 0), (-1, 0)])
+def test_least_squares_of_the_block_data(driver, order, angle, growth):
+    """Coefficients from the records, slots and normal inverses, or the operators of
+    kept cells, in the kernels' arithmetic, against 128 bits.  The bar: set-up
+    keeps the operators of a cell unless the bound of each stencil's normal matrix
+    is below 2e-13 or below 10 (large: 20) times what an operator formed in FP64
+    costs; errors are a fifth (a tenth) of the bound at most, so each stencil's
+    face values are within 2e-13 plus twice the operator's worst.  Over a mesh the
+    worst face value stays below the operators' worst."""
+    if angle > 0:
+        m = inputs.graded_sector_mesh(64, 3, angle, growth)
+    elif angle == 0:
+        m = inputs.jittered_periodic_mesh(32, 3)
+    else:
+        m = inputs.jittered_box_mesh(32, 32, 3, lx=1.0, ly=0.125)
+    tmp, exe = driver
+    _write(tmp, "s", m)
+    out = _run(exe, "solve", tmp, "s", order, 11 if angle > 0 else 3)
+    print(out)
+    for line in out.splitlines():
+        w = line.split()
+        assert float(w[-1]) <= 1.0, out
+        assert float(w[6]) <= float(w[8]), out

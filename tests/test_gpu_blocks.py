@@ -13,7 +13,8 @@ import numpy as np
 import pytest
 
 from paper_2105_02127_amd import inputs
-from parity_check import assert_states, check_flags
+from parity_check import assert_adjoint, assert_states, check_flags
+from test_blocks_host import _run, _write, driver  # noqa: F401  (the host driver's fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -120,3 +121,123 @@ def test_characteristic_past_the_first_blocks(oracle_mod, order, variant):
     from test_gpu_parity import _sampled
     _sampled(teno, oracle_mod, torch, 6, n_sample=160, characteristic=1, variant=variant,
              order=order)
+
+
+def _graded(order, angle, growth, **kw):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_02127_amd import teno
+    print(f"[case] graded order={order} {angle} rad e^{growth} {kw}", flush=True)
+    m = inputs.graded_sector_mesh(40, 3, angle, growth)
+    U = inputs.conservative(1.0 + 0.3 * m.rng.uniform(-1, 1, m.n_cell), 0.3, 0.2, 1.0)
+    lm = teno.Mesh(m.xy, m.tri, period=m.period).setup(order=order, **kw)
+    return torch, m, U, lm, teno.Solver(lm)
+
+
+@pytest.mark.parametrize("order", [3, 4, 5, 6])
+@pytest.mark.parametrize("angle,growth", [(1.5, 4.0), (1.5, 8.0), (4.0, 4.0)])
+def test_graded_mesh_large_stencils(driver, order, angle, growth):  # noqa: F811
+    """Graded meshes, where set-up keeps the operators of some stencils: face
+    states of the linear scheme against 128 bits.  The operators' own rounding of
+    the differences (0.6, 41 rows of entries up to about 50 with basis values up to
+    32) allows 1e-11 of the state; the normal matrices' bound, 1e-12, adds less."""
+    torch, m, U, lm, sv = _graded(order, angle, growth, variant=1)
+    tmp, exe = driver
+    _write(tmp, "g", m)
+    np.ascontiguousarray(U).tofile(tmp + "/g.u")
+    _run(exe, "faces", tmp, "g", order, 13)
+    cells = np.fromfile(tmp + "/g.cells", np.int32)
+    want = np.fromfile(tmp + "/g.faces").reshape(len(cells), -1, 4)
+    fs = sv.reconstruct(torch.as_tensor(U[lm.perm], device="cuda"))
+    got = np.empty((m.n_cell, fs.shape[0], 4))
+    got[lm.perm] = fs.permute(1, 0, 2).cpu().numpy()
+    scale = max(np.abs(want).max(), 1.0)
+    assert np.abs(got[cells] - want).max() <= 1e-11 * scale
+
+
+@pytest.mark.parametrize("variant,characteristic", [(0, 0), (2, 0), (0, 1), (2, 1)])
+def test_graded_mesh_small_stencils(oracle_mod, variant, characteristic):
+    """The same at order 3, where the oracle's operators keep 1e-13 on such a mesh:
+    selections and combinations of the small stencils, and the adjoint."""
+    torch, m, U, lm, sv = _graded(3, 1.5, 4.0, variant=variant, characteristic=characteristic,
+                                  fallback=1)
+    om = oracle_mod.OracleMesh(m.xy, m.tri, period=m.period)
+    om.setup(oracle_mod.params(order=3, variant=variant, characteristic=characteristic, fallback=1))
+    want = om.residual(U, want_fp=True)
+    flags = sv.empty_flags()
+    Ud = torch.as_tensor(U[lm.perm], device="cuda")
+    fs = sv.reconstruct(Ud, flags=flags)
+    got = np.empty((m.n_cell, fs.shape[0], 4))
+    got[lm.perm] = fs.permute(1, 0, 2).cpu().numpy()
+    assert_states(got, want["fp"].reshape(m.n_cell, -1, 4), what="face states")
+    if variant == 2:
+        return
+    f = flags.cpu().numpy().view(np.uint16)
+    fu = np.empty_like(f)
+    fu[..., lm.perm] = f
+    check_flags(fu, want["flags"], want["diag"]["tie_mask"])
+    if characteristic:
+        return
+    lam = m.rng.normal(size=U.shape)
+    g = sv.vjp_residual(Ud, flags, torch.as_tensor(lam[lm.perm], device="cuda"))
+    gu = np.empty_like(U)
+    gu[lm.perm] = g.cpu().numpy()
+    assert_adjoint(gu, om.vjp(U, fu, lam), om.vjp_scale(U, fu, lam), what="graded vjp")
+
+
+@pytest.mark.parametrize("order", [3, 5, 6])
+def test_graded_mesh_adjoint_is_the_transpose(order):
+    """<lam, dR v> by central differences of the linear scheme's residual against
+    <vjp, v>.  The oracle's own central difference at order 6 on this mesh is 7e-6
+    off at a step of 1e-4 and 7e-8 at 1e-5 (the one-sided large stencils raise the
+    perturbation a hundredfold, and the error falls with its square), 5e-10 at
+    1e-6, where rounding adds 1e-9: step 1e-6, bar 1e-7."""
+    torch, m, U, lm, sv = _graded(order, 1.5, 8.0, variant=1)
+    U = inputs.conservative(1.0 + 0.02 * m.rng.uniform(-1, 1, m.n_cell), 0.3, 0.2, 1.0)
+    Ud = torch.as_tensor(U[lm.perm], device="cuda")
+    flags = sv.empty_flags()
+    sv.reconstruct(Ud, flags=flags)
+    vol = torch.as_tensor(np.ascontiguousarray(_areas(m)[lm.perm]), device="cuda")[:, None]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    lam = vol * torch.randn(U.shape, generator=g, dtype=torch.float64, device="cuda")
+    v = torch.randn(U.shape, generator=g, dtype=torch.float64, device="cuda")
+    e = 1e-6
+    dR = (sv.residual(Ud + e * v) - sv.residual(Ud - e * v)) / (2 * e)
+    a, b = (lam * dR), sv.vjp_residual(Ud, flags, lam) * v
+    assert abs(a.sum().item() - b.sum().item()) <= 1e-7 * a.abs().sum().item()
+
+
+@pytest.mark.parametrize("order_mode", [0, 1])
+def test_graded_meshes_in_a_batch(order_mode):
+    """Batched steps of graded meshes of two orders and a jittered one: the bits of
+    stepping them alone."""
+    from paper_2105_02127_amd.batch import Batch
+    from paper_2105_02127_amd import teno
+    torch, m, U, lm, sv = _graded(4, 1.5, 8.0, fallback=1)
+    svs, Us = [sv], [U[lm.perm]]
+    lm = teno.Mesh(m.xy, m.tri, period=m.period).setup(order=5, fallback=1)
+    svs.append(teno.Solver(lm))
+    Us.append(U[lm.perm])
+    p = inputs.jittered_periodic_mesh(20, 3)
+    lm = teno.Mesh(p.xy, p.tri).setup(order=3, fallback=1)
+    svs.append(teno.Solver(lm))
+    Us.append(inputs.random_lines(p)[lm.perm])
+    Us = [torch.as_tensor(u, device="cuda") for u in Us]
+    alone = [u.clone() for u in Us]
+    b = Batch(svs)
+    b.set_tuning(order_mode=order_mode, waves_per_cu=0, item_order=0, use_graph=1)
+    dt = b.max_dt(Us, 0.4)
+    for _ in range(3):
+        b.rk_step(Us, dt)
+        for k, (s, u) in enumerate(zip(svs, alone)):
+            s.rk_step(u, dt[k:k + 1].clone())
+        torch.cuda.synchronize()
+        for u, w in zip(Us, alone):
+            assert torch.equal(u, w)
+
+
+def _areas(m):
+    x = m.xy[m.tri]
+    d1, d2 = x[:, 1] - x[:, 0], x[:, 2] - x[:, 0]
+    return 0.5 * np.abs(d1[:, 0] * d2[:, 1] - d1[:, 1] * d2[:, 0])
