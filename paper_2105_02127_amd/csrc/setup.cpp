@@ -813,7 +813,7 @@ static double operator_error(const Mesh& m, const Basis& B, const Radon& rule, i
 // bound where it is large (small stencils; 0.05-0.1 the large one) and 0.2-0.7 of
 // operator_error: these ratios are where the two meet.
 constexpr double kBoundFloor = 2e-13;
-constexpr double bound_ratio(bool big) { return big ? 20.0 : 10.0; }
+constexpr double bound_ratio(bool big) { return big ? 30.0 : 10.0; }
 
 // A stencil member as a block sees it: the cell and its periodic image.
 struct Image {

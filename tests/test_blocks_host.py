@@ -70,7 +70,7 @@ def test_least_squares_of_the_block_data(driver, order, angle, growth):
     """Coefficients from the records, slots and normal inverses, or the operators of
     kept cells, in the kernels' arithmetic, against 128 bits.  The bar: set-up
     keeps the operators of a cell unless the bound of each stencil's normal matrix
-    is below 2e-13 or below 10 (large: 20) times what an operator formed in FP64
+    is below 2e-13 or below 10 (large: 30) times what an operator formed in FP64
     costs; errors are a fifth (a tenth) of the bound at most, so each stencil's
     face values are within 2e-13 plus twice the operator's worst.  Over a mesh the
     worst face value stays below the operators' worst."""
