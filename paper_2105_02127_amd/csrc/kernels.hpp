@@ -1629,6 +1629,122 @@ __attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct_char(Rec
   reconstruct_mesh<P, NQ, CW, true>(n_blocks);
 }
 
+// ---------------------------------------------------------------------------
+// Small meshes: one workgroup of four wavefronts per tile, a wavefront per stencil
+// (0..2 small, 3 large) over the tile's staged block, whose coefficients the first
+// one then selects from.  The same sums in the same order as above, so the same
+// bits, from a quarter of the chain: where blocks of 64 or 128 cells leave compute
+// units empty, a tile waits for its rows and not for its share of the chip.
+// 2,048 cells, orders 3-6: 6.6, 6.9, 9.5, 14.1 us against 9.3, 10.2, 13.4, 20.6 us.
+// ---------------------------------------------------------------------------
+// Tiles up to which it is taken.  Small against blocks (us): order 3 14.2 / 14.4 at
+// 2,048 tiles, 18.2 / 18.0 at 2,813; in characteristic variables, whose selection
+// is most of the work, 40.3 / 44.5 at 4,050 and 56.1 / 57.4 at 6,050 (CWENO 44.1 /
+// 42.5 at 4,050).  Order 4 8.3 / 10.9 at 512, 13.6 / 11.4 at 1,013; order 5 11.2 /
+// 14.6 and 21.1 / 15.4; order 6 16.0 / 21.7 and 30.5 / 22.8: two or three workgroups
+// fit a compute unit there.
+constexpr int small_tiles(int order, bool characteristic_teno) {
+  return order > 3 ? 512 : (characteristic_teno ? 4096 : 2048);
+}
+// LDS: the staged block; over it, once read, the coefficients [15 + NU][64] and in
+// characteristic variables the Gram matrices.
+constexpr int small_lds_bytes(int nu, int members, bool characteristic) {
+  const int staged = block_lds_bytes(nu, members);
+  const int coef = (3 * kSmallCoef + nu) * 512 + (characteristic ? gram_bytes(1) : 0);
+  return staged > coef ? staged : coef;
+}
+
+// wavefronts per SIMD: as many workgroups on a CU
+constexpr int small_waves(int p) { return p == 3 ? 4 : 2; }
+
+template <int P, int NQ, bool CW, bool CH>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(small_waves(P)))) void k_reconstruct_small(ReconArgs) {
+  using O = OrderT<P>;
+  constexpr int NU = O::NU, NL = O::NL, R = O::R;
+  constexpr int GS = row_groups(kSmallRows), QS = sym_quads(kSmallCoef);
+  typedef RowSlots<GS, kSlotBits> Small;
+  static_assert(Small::NW == 1 && Small::PER == GS, "a word of slots per small stencil");
+  extern __shared__ int4 lds4[];
+  char* lds = reinterpret_cast<char*>(lds4);
+  TENO_CONST ReconArgs& a = *(TENO_CONST ReconArgs*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, c = lane >> 2, g = lane & 3;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x), blk = tile / a.b.bwaves;
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  copy_states(a.U, a.b.bmem + (size_t)blk * a.b.mstride, a.b.mstride, lds0, 256);
+  copy_records<NU>(a.b, blk, lds0 + 32 * a.b.bmax, 256);
+  const int cell = a.b.pack[tile * kTile + c];
+  const bool live = cell >= 0, frozen = a.frozen != 0;
+  const bool small = CW || frozen || a.variant != 1;
+  const unsigned* __restrict__ words = a.b.bslot + (size_t)tile * (slot_words(NL) * 64);
+  const double2* __restrict__ np = a.b.N + (size_t)tile * (normal_quads(NU) * 64);
+  const double2* __restrict__ jc = a.b.jac + (size_t)tile * (2 * kTile);
+  const float2 ce = (a.b.centre + (size_t)tile * (4 * kTile))[4 * c + wave];
+  const double2 ja = jc[2 * c], jb = jc[2 * c + 1];
+  CellView cv;
+  cv.us = reinterpret_cast<const double*>(lds);
+  cv.geo = reinterpret_cast<const double*>(lds + 32 * a.b.bmax);
+  cv.g = g;
+  const int own_slot = (tile - blk * a.b.bwaves) * kTile + c;
+  const double* own = cv.geo + own_slot * (2 * rec_units(NU));
+  auto staged = [&]() {
+    lds_copy_wait();
+    __syncthreads();
+    cv.x = own[0];
+    cv.y = own[1];
+    static_for<0, 4>([&](auto i) { cv.u0[i] = cv.us[own_slot * 4 + (g ^ i)]; });
+  };
+  double* ex = reinterpret_cast<double*>(lds) + lane;
+  if (wave == 3) {
+    double r[NU], aK[NU];
+    RowSlots<row_groups(NL), kSlotBits> slots;
+    static_for<0, slots.NW>([&](auto k) { slots.w[k] = words[(3 + k) * 64 + lane]; });
+    NormalMatrix<NU, TileAhead<P>::CH> nl;
+    nl.template load<0>(np + 3 * QS * 64, lane);
+    staged();
+    const bool shift = __any(ce.x != 0.0f || ce.y != 0.0f);
+    stencil_sums<R, NL, 0, NU, split_degree(P)>(cv, slots, own, ce.x, ce.y, shift, r);
+    nl.apply(np + 3 * QS * 64, lane, r, aK);
+    hermite_to_monomials<R>(aK, ce.x, ce.y, shift);
+    Frame<R> fr;
+    fr.init(ja, jb);
+    fr.template to_basis<R>(aK);
+    __syncthreads();  // every wavefront is done with the staged members
+    static_for<0, NU>([&](auto l) { ex[(3 * kSmallCoef + l) * 64] = aK[l]; });
+  } else {
+    double r[kSmallCoef], as[kSmallCoef];
+    Small slots;
+    slots.w[0] = words[wave * 64 + lane];
+    NormalMatrix<kSmallCoef> ns;
+    ns.template load<0>(np + QS * wave * 64, lane);
+    staged();
+    static_for<0, kSmallCoef>([&](auto l) { as[l] = 0.0; });
+    if (small) {
+      stencil_sums<2, kSmallRows, 0, NU, 2>(cv, slots, own, ce.x, ce.y, true, r);
+      ns.apply(np, lane, r, as);
+      hermite_to_monomials<2>(as, ce.x, ce.y, true);
+      Frame<2> fr;
+      fr.init(ja, jb);
+      fr.template to_basis<2>(as);
+    }
+    __syncthreads();
+    static_for<0, kSmallCoef>([&](auto l) { ex[(wave * kSmallCoef + l) * 64] = as[l]; });
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  double as[3][5], aK[NU];
+  static_for<0, 3>([&](auto q) { static_for<0, 5>([&](auto l) { as[q][l] = ex[(5 * q + l) * 64]; }); });
+  static_for<0, NU>([&](auto l) { aK[l] = ex[(3 * kSmallCoef + l) * 64]; });
+  double* gram = reinterpret_cast<double*>(lds) + (3 * kSmallCoef + NU) * 64;
+  if constexpr (CH && CW)
+    char_edges_cweno_gram<P, NQ>(a, as, aK, cv.u0[0], cell, live, g, g, c, lane, gram);
+  else if constexpr (CH)
+    char_edges_gram<P, NQ>(a, as, aK, cv.u0[0], cell, live, g, g, c, lane, gram);
+  else
+    select_and_store<P, NQ, CW>(a, frozen, as, aK, cv.u0[0], cell, live, g, g, lane);
+}
+
 // Cells solved with operators (internal.h), in sets of four.
 struct KeptArgs {
   const int* __restrict__ cell;    // [4 n] -1: none

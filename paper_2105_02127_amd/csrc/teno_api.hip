@@ -223,17 +223,21 @@ static int resident_groups(K kernel, int threads, size_t lds, int device) {
   return std::max(1, cus) * std::max(1, per);
 }
 
-// f(kernel, kept) with the reconstruction kernel of a solver's order and scheme and
-// that of its cells solved with operators.
+// f(kernel, small, kept) with the reconstruction kernels of a solver's order and
+// scheme: of blocks, of a small mesh's tiles, and of cells solved with operators.
 template <class F>
 static void recon_kernel(const teno_solver* s, F&& f) {
   const bool cw = s->prm.variant == 2, ch = s->prm.characteristic != 0;
   dispatch(s->d.order, s->d.nq, [&](auto P, auto NQ) {
     constexpr int p = decltype(P)::value, nq = decltype(NQ)::value;
-    if (ch && cw) f(k_reconstruct_char<p, nq, true>, k_reconstruct_kept<p, nq, true, true>);
-    else if (ch) f(k_reconstruct_char<p, nq, false>, k_reconstruct_kept<p, nq, false, true>);
-    else if (cw) f(k_reconstruct<p, nq, true>, k_reconstruct_kept<p, nq, true, false>);
-    else f(k_reconstruct<p, nq, false>, k_reconstruct_kept<p, nq, false, false>);
+    if (ch && cw) f(k_reconstruct_char<p, nq, true>, k_reconstruct_small<p, nq, true, true>,
+                    k_reconstruct_kept<p, nq, true, true>);
+    else if (ch) f(k_reconstruct_char<p, nq, false>, k_reconstruct_small<p, nq, false, true>,
+                    k_reconstruct_kept<p, nq, false, true>);
+    else if (cw) f(k_reconstruct<p, nq, true>, k_reconstruct_small<p, nq, true, false>,
+                    k_reconstruct_kept<p, nq, true, false>);
+    else f(k_reconstruct<p, nq, false>, k_reconstruct_small<p, nq, false, false>,
+                    k_reconstruct_kept<p, nq, false, false>);
   });
 }
 
@@ -268,9 +272,14 @@ int launch_reconstruct(teno_solver* s, const double* U, uint16_t* flags, bool fr
   a.cw_dK = 1.0 - 1.0 / s->prm.dk_prime;
   a.cw_ds = (1.0 - a.cw_dK) / 3.0;
   int rc = TENO_OK;
-  recon_kernel(s, [&](auto kernel, auto kept) {
+  recon_kernel(s, [&](auto kernel, auto small, auto kept) {
     rc = timed(s, 0, st, [&]() {
-      hipLaunchKernelGGL(kernel, dim3(std::min(s->n_blocks, s->recon_groups)),
+      if (s->n_tiles <= small_tiles(s->d.order, s->prm.characteristic && s->prm.variant != 2))
+        hipLaunchKernelGGL(small, dim3(s->n_tiles), dim3(256),
+                           (size_t)small_lds_bytes(s->d.nu, s->bmax, s->prm.characteristic != 0),
+                           st, a);
+      else
+        hipLaunchKernelGGL(kernel, dim3(std::min(s->n_blocks, s->recon_groups)),
                          dim3(64 * s->bwaves), recon_lds(s), st, a, s->n_blocks);
       if (s->n_kept > 0)
         hipLaunchKernelGGL(kept, dim3(s->n_kept), dim3(64), 0, st, a, kept_args(s));
@@ -691,7 +700,7 @@ int teno_solver_create(const teno_mesh* mesh, int32_t device, teno_solver** out)
       return hip_fail(e, "hipMemcpy upload");
     }
   }
-  recon_kernel(s, [&](auto kernel, auto) {
+  recon_kernel(s, [&](auto kernel, auto, auto) {
     s->recon_groups = resident_groups(kernel, 64 * s->bwaves, recon_lds(s), device);
   });
   hipLaunchKernelGGL(k_diag_reset, dim3(1), dim3(64), 0, 0, s->diag);
@@ -955,7 +964,8 @@ struct teno_batch {
   double* partial = nullptr;
   // launch plan: per reconstruction launch (pq, item offset, wave offset, waves)
   struct RLaunch {
-    int pq, item0, n_items;   // items [item0, item0 + n_items)
+    int pq, tiles;            // wavefronts per workgroup
+    int item0, n_items;       // items [item0, item0 + n_items)
     int start0, n_groups;     // n_groups workgroups; their ranges, or -1: dealt out in turn
     size_t lds;               // LDS per workgroup
   };
@@ -1060,32 +1070,32 @@ int batch_plan(teno_batch* b) {
   std::vector<int2> items;
   std::vector<int> starts_all;
   b->rplan.clear();
-  std::vector<int> pqs;
-  if (T.order_mode == 1) {
-    for (int m : morder) {
-      int pq = b->sv[m]->d.order * 10 + b->sv[m]->d.nq;
-      if (std::find(pqs.begin(), pqs.end(), pq) == pqs.end()) pqs.push_back(pq);
-    }
-  } else {
-    pqs.push_back(0);
-  }
-  for (int pq : pqs) {
+  std::vector<std::pair<int, int>> kinds;  // order * 10 + face points (0: any), wavefronts
+  // (with one launch per order, a launch of its own for each block size too: no
+  // wavefront of a workgroup is without a tile)
+  auto kind = [&](const teno_solver* s) {
+    return T.order_mode == 1 ? std::make_pair(s->d.order * 10 + s->d.nq, s->bwaves)
+                             : std::make_pair(0, kMaxBlockTiles);
+  };
+  for (int m : morder)
+    if (std::find(kinds.begin(), kinds.end(), kind(b->sv[m])) == kinds.end())
+      kinds.push_back(kind(b->sv[m]));
+  for (const auto& of : kinds) {
+    const int pq = of.first, tiles = of.second;
     std::vector<double> cost;
     const int item0 = (int)items.size();
     // the buffers of a launch's items have one layout, the largest block's
-    int bmax = 0, nbuf = 2, order = 0;
+    int bmax = 0, nbuf = 2;
     size_t lds = 0;
     for (int m : morder) {
       const teno_solver* s = b->sv[m];
-      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
+      if (kind(s) != of) continue;
       bmax = std::max(bmax, s->bmax);
-      order = s->d.order;
       for (int t = 0; t < s->n_blocks; ++t) {
         items.push_back(make_int2(m, t));
         cost.push_back(s->bwaves * ((double)s->d.Jp + 4.0 * s->d.rows4 * 4));
       }
     }
-    const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);
     if (pq != 0) {
       const Dims& d = b->sv[items[item0].x]->d;
       if (recon_lds(d, tiles, bmax, 2, false) > (size_t)lds_budget(tiles)) nbuf = 1;
@@ -1093,7 +1103,7 @@ int batch_plan(teno_batch* b) {
     }
     for (int m : morder) {
       const teno_solver* s = b->sv[m];
-      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
+      if (kind(s) != of) continue;
       b->bmax[m] = pq != 0 ? bmax : s->bmax;
       b->nbuf[m] = pq != 0 ? nbuf : s->nbuf;
       if (pq == 0) lds = std::max(lds, recon_lds(s));
@@ -1113,12 +1123,12 @@ int batch_plan(teno_batch* b) {
 #undef TENO_BATCH_CASE
         default: break;
       }
-      b->rplan.push_back({pq, item0, n_items, -1, groups, lds});
+      b->rplan.push_back({pq, tiles, item0, n_items, -1, groups, lds});
     } else {
       std::vector<int> st;
       const int ng = balanced_starts(cost, std::max(1, waves / tiles), st);
       for (int& x : st) x += item0;
-      b->rplan.push_back({pq, item0, n_items, (int)starts_all.size(), ng, lds});
+      b->rplan.push_back({pq, tiles, item0, n_items, (int)starts_all.size(), ng, lds});
       starts_all.insert(starts_all.end(), st.begin(), st.end());
     }
   }
@@ -1289,13 +1299,13 @@ void batch_launch_recon(teno_batch* b, int k, hipStream_t st) {
     const int2* its = dealt ? b->items_r + L.item0 : b->items_r;
     switch (L.pq) {
       case 0:
-        hipLaunchKernelGGL(k_batch_reconstruct_all, dim3(L.n_groups), dim3(64 * kMaxBlockTiles),
+        hipLaunchKernelGGL(k_batch_reconstruct_all, dim3(L.n_groups), dim3(64 * L.tiles),
                            L.lds, st, b->meshes, its, start, k);
         break;
 #define TENO_BATCH_CASE(PQ)                                                             \
   case PQ:                                                                              \
     hipLaunchKernelGGL((k_batch_reconstruct<PQ>), dim3(L.n_groups),                     \
-                       dim3(64 * block_tiles(PQ / 10)), L.lds, st, b->meshes, its, start, \
+                       dim3(64 * L.tiles), L.lds, st, b->meshes, its, start, \
                        L.n_items, k);                                                   \
     break;
         TENO_BATCH_CASES

@@ -19,6 +19,38 @@ from test_blocks_host import _run, _write, driver  # noqa: F401  (the host drive
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("order,n", [(3, 5), (4, 64), (4, 65), (5, 64), (5, 65), (6, 64), (6, 65),
+                                     (6, 90), (6, 91)])
+def test_small_mesh_reconstruction_equals_blocks(order, n):
+    """Small meshes are reconstructed a tile per workgroup, a wavefront per stencil
+    (up to 512 tiles of 16 cells; order 3 above), batches always by blocks (of four
+    tiles up to 1,024 tiles, of eight at orders 5 and 6 above): the same bits, by
+    the schemes' selection and by the flags of the first step frozen."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_02127_amd import teno
+    from paper_2105_02127_amd.batch import Batch
+    print(f"[case] small order={order} n={n}", flush=True)
+    m = (inputs.jittered_periodic_mesh(n, 43) if n > 5 else
+         inputs.jittered_box_mesh(11, n, 43))       # 110 cells: a part of a block
+    lm = teno.Mesh(m.xy, m.tri, period=m.period).setup(order=order, fallback=1)
+    sv = teno.Solver(lm)
+    U = torch.as_tensor(inputs.random_lines(m)[lm.perm], device="cuda")
+    b = Batch([sv])
+    b.set_tuning(order_mode=1, waves_per_cu=0, item_order=0, use_graph=0)
+    dt = b.max_dt([U], 0.4)
+    w = U.clone()
+    flags = sv.empty_flags(3)
+    sv.rk_step(w, dt.clone(), flags3=flags)
+    b.rk_step([U], dt)
+    torch.cuda.synchronize()
+    assert torch.equal(w, U)
+    f = sv.empty_flags()
+    R = sv.residual(w, flags=f)
+    assert torch.equal(sv.residual_frozen(w, f), R)
+
+
 @pytest.mark.parametrize("order,n,aspect,variant,characteristic", [
     (3, 60, 32, 0, 0),   # four wavefronts, two blocks of 471 members
     (4, 60, 16, 0, 0),   # four, one block
