@@ -192,16 +192,8 @@ static void set_tie_window(ReconArgs& a) {
   }
 }
 
-// Layout of the staged blocks of a launch whose largest block has bmax members.
-static void set_layout(BlockArgs& b, const Dims& d, int waves, int bmax, int nbuf, bool characteristic) {
-  b.bmax = bmax;
-  b.nbuf = nbuf;
-  b.stride = buffer_stride(d.nu, bmax, waves, characteristic);
-}
 static BlockArgs block_args(const teno_solver* s) {
-  BlockArgs b{s->boff, s->bmem, s->brec, s->bslot, s->N, s->jac, s->centre, s->pack, s->bwaves, s->bmax, 0, 0, 0};
-  set_layout(b, s->d, s->bwaves, s->bmax, s->nbuf, s->prm.characteristic != 0);
-  return b;
+  return {s->boff, s->bmem, s->brec, s->bslot, s->N, s->jac, s->centre, s->pack, s->bwaves, s->bmax, s->bmax, s->nbuf};
 }
 
 static KeptArgs kept_args(const teno_solver* s) { return {s->kept, s->kept_rows, s->kept_ops, s->n_kept}; }
@@ -1223,7 +1215,8 @@ int batch_descriptors(teno_batch* b, double* const* U, const double* dt, hipStre
       ReconArgs& a = d.r[k];
       a.U = in[k];
       a.b = block_args(s);
-      set_layout(a.b, s->d, s->bwaves, b->bmax[m], b->nbuf[m], false);
+      a.b.bmax = b->bmax[m];
+      a.b.nbuf = b->nbuf[m];
       a.fp = s->fp;
       a.flags = nullptr;
       a.user_of = s->user_of;
