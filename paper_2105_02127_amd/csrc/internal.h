@@ -78,15 +78,11 @@ constexpr int group_lds_bytes(int stride, int members, int buffers) {
   return buffers * (stride + ids_bytes(members));
 }
 constexpr int kLdsPerCu = 160 * 1024;
-// Tiles (wavefronts) per block at most: workgroups of four, two or more to a CU, at
+// Tiles (wavefronts) per block: workgroups of four, two or more to a CU, at
 // orders 3 and 4; at orders 5 and 6, whose records are longer and whose
 // registers allow two wavefronts per SIMD, one of eight, whose cells share more
 // members.
 constexpr int block_tiles(int order) { return order >= 5 ? 8 : 4; }
-// ... of a mesh of n tiles: four also at orders 5 and 6 where eight would leave CUs
-// empty.  15.3 against 20.2 us at order 5 and 22.9 against 33.7 at order 6 (1,013
-// tiles); from 2,048 tiles on eight are as fast or faster (22.0 against 22.4).
-constexpr int mesh_block_tiles(int order, int n) { return n <= 1024 ? 4 : block_tiles(order); }
 constexpr int kMaxBlockTiles = 8;
 // LDS a workgroup of w tiles may take to keep eight wavefronts on a CU
 constexpr int lds_budget(int w) { return w >= 8 ? kLdsPerCu : kLdsPerCu / 8 * w; }

@@ -1644,16 +1644,16 @@ __attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct_char(Rec
 // one then selects from.  The same sums in the same order as above, so the same
 // bits, from a quarter of the chain: where blocks of 64 or 128 cells leave compute
 // units empty, a tile waits for its rows and not for its share of the chip.
-// 2,048 cells, orders 3-6: 6.6, 6.9, 9.5, 14.1 us against 9.3, 10.2, 13.4, 20.6 us.
+// 2,048 cells, orders 3-6: 6.8, 6.8, 10.0, 14.6 us against 8.7, 9.5, 16.9, 24.3 us.
 // ---------------------------------------------------------------------------
-// Tiles up to which it is taken.  Small against blocks (us): order 3 14.2 / 14.4 at
-// 2,048 tiles, 18.2 / 18.0 at 2,813; in characteristic variables, whose selection
-// is most of the work, 40.3 / 44.5 at 4,050 and 56.1 / 57.4 at 6,050 (CWENO 44.1 /
-// 42.5 at 4,050).  Order 4 8.3 / 10.9 at 512, 13.6 / 11.4 at 1,013; order 5 11.2 /
-// 14.6 and 21.1 / 15.4; order 6 16.0 / 21.7 and 30.5 / 22.8: two or three workgroups
-// fit a compute unit there.
+// Tiles up to which it is taken.  Small against blocks (us): order 3 8.4 / 9.9 at
+// 1,013 tiles, 14.4 / 13.2 at 2,048; in characteristic variables, whose selection is
+// most of the work, 24.2 / 25.0 at 2,048 and 40.6 / 41.9 at 4,050 (CWENO 25.0 / 22.5
+// at 2,048).  Order 4 8.2 / 10.2 at 512, 13.7 / 10.6 at 1,013; order 5 11.6 / 17.2
+// and 22.3 / 17.7; order 6 16.5 / 24.9 and 31.7 / 25.5: two or three workgroups fit
+// a compute unit there.
 constexpr int small_tiles(int order, bool characteristic_teno) {
-  return order > 3 ? 512 : (characteristic_teno ? 4096 : 2048);
+  return order > 3 ? 512 : (characteristic_teno ? 4096 : 1024);
 }
 // LDS: the staged block; over it, once read, the coefficients [15 + NU][64] and in
 // characteristic variables the Gram matrices.

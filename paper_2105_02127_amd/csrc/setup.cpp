@@ -873,7 +873,7 @@ static void pack_blocks(Mesh& m) {
   std::vector<std::vector<Image>> lists;
   int n_blocks = 0;
   // as many tiles per block as the LDS allows
-  for (m.bwaves = mesh_block_tiles(d.order, m.n_tiles), m.nbuf = 2;;) {
+  for (m.bwaves = block_tiles(d.order), m.nbuf = 2;;) {
     const int W = m.bwaves, cells = W * kTile;
     n_blocks = (m.n_tiles + W - 1) / W;
     for (int t = 0; t < nc; ++t) m.pack[t] = t;

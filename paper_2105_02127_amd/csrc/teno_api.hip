@@ -956,8 +956,7 @@ struct teno_batch {
   double* partial = nullptr;
   // launch plan: per reconstruction launch (pq, item offset, wave offset, waves)
   struct RLaunch {
-    int pq, tiles;            // wavefronts per workgroup
-    int item0, n_items;       // items [item0, item0 + n_items)
+    int pq, item0, n_items;   // items [item0, item0 + n_items)
     int start0, n_groups;     // n_groups workgroups; their ranges, or -1: dealt out in turn
     size_t lds;               // LDS per workgroup
   };
@@ -1062,32 +1061,32 @@ int batch_plan(teno_batch* b) {
   std::vector<int2> items;
   std::vector<int> starts_all;
   b->rplan.clear();
-  std::vector<std::pair<int, int>> kinds;  // order * 10 + face points (0: any), wavefronts
-  // (with one launch per order, a launch of its own for each block size too: no
-  // wavefront of a workgroup is without a tile)
-  auto kind = [&](const teno_solver* s) {
-    return T.order_mode == 1 ? std::make_pair(s->d.order * 10 + s->d.nq, s->bwaves)
-                             : std::make_pair(0, kMaxBlockTiles);
-  };
-  for (int m : morder)
-    if (std::find(kinds.begin(), kinds.end(), kind(b->sv[m])) == kinds.end())
-      kinds.push_back(kind(b->sv[m]));
-  for (const auto& of : kinds) {
-    const int pq = of.first, tiles = of.second;
+  std::vector<int> pqs;
+  if (T.order_mode == 1) {
+    for (int m : morder) {
+      int pq = b->sv[m]->d.order * 10 + b->sv[m]->d.nq;
+      if (std::find(pqs.begin(), pqs.end(), pq) == pqs.end()) pqs.push_back(pq);
+    }
+  } else {
+    pqs.push_back(0);
+  }
+  for (int pq : pqs) {
     std::vector<double> cost;
     const int item0 = (int)items.size();
     // the buffers of a launch's items have one layout, the largest block's
-    int bmax = 0, nbuf = 2;
+    int bmax = 0, nbuf = 2, order = 0;
     size_t lds = 0;
     for (int m : morder) {
       const teno_solver* s = b->sv[m];
-      if (kind(s) != of) continue;
+      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
       bmax = std::max(bmax, s->bmax);
+      order = s->d.order;
       for (int t = 0; t < s->n_blocks; ++t) {
         items.push_back(make_int2(m, t));
         cost.push_back(s->bwaves * ((double)s->d.Jp + 4.0 * s->d.rows4 * 4));
       }
     }
+    const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);
     if (pq != 0) {
       const Dims& d = b->sv[items[item0].x]->d;
       if (recon_lds(d, tiles, bmax, 2, false) > (size_t)lds_budget(tiles)) nbuf = 1;
@@ -1095,7 +1094,7 @@ int batch_plan(teno_batch* b) {
     }
     for (int m : morder) {
       const teno_solver* s = b->sv[m];
-      if (kind(s) != of) continue;
+      if (pq != 0 && s->d.order * 10 + s->d.nq != pq) continue;
       b->bmax[m] = pq != 0 ? bmax : s->bmax;
       b->nbuf[m] = pq != 0 ? nbuf : s->nbuf;
       if (pq == 0) lds = std::max(lds, recon_lds(s));
@@ -1115,12 +1114,12 @@ int batch_plan(teno_batch* b) {
 #undef TENO_BATCH_CASE
         default: break;
       }
-      b->rplan.push_back({pq, tiles, item0, n_items, -1, groups, lds});
+      b->rplan.push_back({pq, item0, n_items, -1, groups, lds});
     } else {
       std::vector<int> st;
       const int ng = balanced_starts(cost, std::max(1, waves / tiles), st);
       for (int& x : st) x += item0;
-      b->rplan.push_back({pq, tiles, item0, n_items, (int)starts_all.size(), ng, lds});
+      b->rplan.push_back({pq, item0, n_items, (int)starts_all.size(), ng, lds});
       starts_all.insert(starts_all.end(), st.begin(), st.end());
     }
   }
@@ -1292,13 +1291,13 @@ void batch_launch_recon(teno_batch* b, int k, hipStream_t st) {
     const int2* its = dealt ? b->items_r + L.item0 : b->items_r;
     switch (L.pq) {
       case 0:
-        hipLaunchKernelGGL(k_batch_reconstruct_all, dim3(L.n_groups), dim3(64 * L.tiles),
+        hipLaunchKernelGGL(k_batch_reconstruct_all, dim3(L.n_groups), dim3(64 * kMaxBlockTiles),
                            L.lds, st, b->meshes, its, start, k);
         break;
 #define TENO_BATCH_CASE(PQ)                                                             \
   case PQ:                                                                              \
     hipLaunchKernelGGL((k_batch_reconstruct<PQ>), dim3(L.n_groups),                     \
-                       dim3(64 * L.tiles), L.lds, st, b->meshes, its, start, \
+                       dim3(64 * block_tiles(PQ / 10)), L.lds, st, b->meshes, its, start, \
                        L.n_items, k);                                                   \
     break;
         TENO_BATCH_CASES

@@ -62,13 +62,6 @@ def test_characteristic_block_layouts_of_meshes(driver, order, kind):
     assert s["lds"] <= 160 * 1024
 
 
-@pytest.mark.parametrize("order,n,tiles", [(3, 64, 4), (5, 64, 4), (6, 64, 4), (5, 90, 4), (6, 90, 4),
-                                           (5, 91, 8), (6, 91, 8), (4, 91, 4)])
-def test_tiles_per_block_by_mesh_size(driver, order, n, tiles):
-    # up to 1,024 tiles, blocks of eight would leave compute units empty
-    assert _mesh(driver, inputs.jittered_periodic_mesh(n, 3), order)["bwaves"] == tiles
-
-
 # (angle, growth): radii 1 : e^growth over a sector of that angle; 0: a jittered
 # periodic mesh; -1: a box stretched eightfold
 @pytest.mark.parametrize("order", [3, 4, 5, 6])

@@ -23,9 +23,8 @@ pytestmark = pytest.mark.gpu
                                      (6, 90), (6, 91)])
 def test_small_mesh_reconstruction_equals_blocks(order, n):
     """Small meshes are reconstructed a tile per workgroup, a wavefront per stencil
-    (up to 512 tiles of 16 cells; order 3 above), batches always by blocks (of four
-    tiles up to 1,024 tiles, of eight at orders 5 and 6 above): the same bits, by
-    the schemes' selection and by the flags of the first step frozen."""
+    (up to 512 tiles of 16 cells; 1,024 at order 3), batches always by blocks: the
+    same bits, and those of the residual with its flags frozen."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
