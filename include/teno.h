@@ -87,7 +87,7 @@ typedef struct teno_info {
   int32_t n_cell, n_face, order, n_quad;
   int32_t n_coef_large, rows_large;  /* unknowns / rows of the large stencil */
   int32_t n_coef_small, rows_small;  /* 5 / 11 for the third-order stencils  */
-  int64_t matrix_doubles_per_cell;   /* pseudo-inverse entries kept on host  */
+  int64_t matrix_doubles_per_cell;   /* pseudo-inverse entries of a cell      */
   int64_t device_bytes;              /* library-owned device memory          */
   double min_rcond;                  /* min over stencils of min|R_jj|/max|R_jj| */
   int64_t face_state_doubles;        /* one stage's face states in the library  */

@@ -2,7 +2,9 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/teno.h"
@@ -23,12 +25,9 @@ struct Dims {
   int rows = 0;    // all stencil rows: 3 * 11 small + nl
   int rows4 = 0;   // rows rounded up to a multiple of 4 (int4 loads)
   int J = 0;       // operator entries per cell: 3 * 5 * 11 + nu * nl
-  int lblk = 0;    // stored entries of the large stencil (see block_entries)
-  int Jp = 0;      // stored entries per cell: 3 small blocks + lblk
-  bool dense = true;  // operator blocks of odd row length stored rows by lane
 };
 
-Dims dims_for(int order, int nq_req, bool dense);
+Dims dims_for(int order, int nq_req);
 
 // Largest number of distinct stencil members that 16 consecutive cells of the
 // internal order may have.
@@ -117,6 +116,32 @@ constexpr int adj_words(int nl) { return (lane_groups(nl) + 1) / 2; }  // 16 bit
 void set_error(const std::string& msg);
 int fail(int code, const std::string& msg);
 
+// Vectors whose elements resize leaves unset: their pages are first touched by the
+// threads that fill them.
+template <class T>
+struct Unset : std::allocator<T> {
+  template <class U>
+  struct rebind {
+    typedef Unset<U> other;
+  };
+  template <class U>
+  void construct(U* p) {
+    ::new ((void*)p) U;
+  }
+  template <class U, class... A>
+  void construct(U* p, A&&... a) {
+    ::new ((void*)p) U(std::forward<A>(a)...);
+  }
+};
+
+// Operator entries by position (packed_M_offset), formed on request: nothing is
+// stored, so a whole stencil is better read through stencil_operator.
+struct Mesh;
+struct Operators {
+  const Mesh* mesh = nullptr;
+  double operator[](int64_t at) const;
+};
+
 struct Mesh {
   // ---- geometry, user order ----
   int nv = 0, nc = 0, nf = 0;
@@ -143,12 +168,12 @@ struct Mesh {
 
   // ---- packed device images, internal order, tile-major ----
   int n_pad = 0, n_tiles = 0;
+  Operators M;                  // after set-up
   std::vector<int32_t> idx;     // [n_tiles][rows4][16][4] stencil members (internal; host)
   // distinct stencil members of each tile (the adjoint's accumulators)
   int ustride = 0;              // list length per tile (largest count, rounded up)
   std::vector<int32_t> tmem;    // [n_tiles][ustride] sorted, padded with the last
   std::vector<int32_t> tcount;  // [n_tiles] distinct members of each tile (unpadded)
-  std::vector<double> M;        // [n_tiles][Jp/2][kTile][2] operator entries (pairs)
   std::vector<int32_t> nbinfo;  // [n_pad][4]: 3 neighbours + packed edge/side bits
   std::vector<double> geo;      // [n_pad][10]: (nx, ny, len) x 3 edges, area
   std::vector<int32_t> user_of; // [n_pad] user id (diagnostics)
@@ -167,10 +192,10 @@ struct Mesh {
   std::vector<int32_t> boff;       // [n_blocks + 1] first member of a block
   std::vector<int32_t> bmem;       // [n_blocks][bmax] member cells (internal), the block's own
                                    // first; rest 0: read at once, without boff
-  std::vector<double> brec;        // geometry records, rec_units units each
+  std::vector<double, Unset<double>> brec;  // geometry records, rec_units units each
   std::vector<uint32_t> bslot;     // [n_tiles][slot_words][64]
-  std::vector<double> N;           // [n_tiles][normal_quads][64][2]
-  std::vector<double> jac;         // [n_pad][4]: a third of the map's columns, block frame
+  std::vector<double, Unset<double>> N;     // [n_tiles][normal_quads][64][2]
+  std::vector<double, Unset<double>> jac;   // [n_pad][4]: a third of the map's columns, block frame
   std::vector<float> centre;       // [n_pad][4][2]: centre of each stencil's basis, block
                                    // frame, relative to the cell
   // cells solved with operators (-1 in pack)
@@ -192,44 +217,10 @@ struct Mesh {
 constexpr int small_row(int k, int s) { return kSmallRows * k + s; }
 constexpr int large_row(int s) { return 3 * kSmallRows + s; }
 
-// Operator entries of one stencil (M^T: nrow rows of L coefficients), kept on
-// the host for teno_mesh_lsq_operator, in one of two block layouts (offsets in
-// doubles within the block of a tile of kTile cells):
-//  * rows by lane (dense meshes, odd L): groups of four rows, each as L planes
-//    of [cell][row];
-//  * entry pairs (even L, or any L on meshes that are not dense): M^T row by
-//    row as pairs, [pair][cell][2], odd rows padded with a zero.
-// Meshes reconstructed in conservative variables are dense.
-constexpr bool lane_rows(int L, bool dense) { return dense && (L & 1); }
-constexpr bool large_lane_rows(int L, bool dense) { return lane_rows(L, dense); }
-constexpr int stored_row(int L) { return L + (L & 1); }
-constexpr int block_entries(int nrow, int L, bool dense) {
-  return lane_rows(L, dense) ? nrow * L : nrow * stored_row(L);
-}
-constexpr int group_rows(int nrow, int j) { return nrow - 4 * j < 4 ? nrow - 4 * j : 4; }
-constexpr int block_offset(int nrow, int L, bool dense, int c, int s, int l) {
-  return lane_rows(L, dense)
-             ? 4 * kTile * L * (s / 4) + (l * kTile + c) * group_rows(nrow, s / 4) + (s % 4)
-             : (((s * stored_row(L) + l) >> 1) * kTile + c) * 2 + ((s * stored_row(L) + l) & 1);
-}
-constexpr int small_block(bool dense) { return block_entries(kSmallRows, kSmallCoef, dense); }
-constexpr int large_block(int nrow, int L, bool dense) {
-  return block_entries(nrow, L, large_lane_rows(L, dense));
-}
-constexpr int large_block_offset(int nrow, int L, bool dense, int c, int s, int l) {
-  return block_offset(nrow, L, large_lane_rows(L, dense), c, s, l);
-}
-
-// The operators of a tile: the three small stencils' blocks, then the
-// large stencil's, Jp * kTile doubles in all.  Block k (3 = large) starts at
-// block_start(k, dense) * kTile.
-constexpr int block_start(int k, bool dense) { return small_block(dense) * k; }
+// Entry l of row s of stencil k (3 = large) of an internal cell.
 inline int64_t packed_M_offset(const Dims& d, int internal, int k, int s, int l) {
-  const int t = internal / kTile, c = internal % kTile;
-  const bool big = k == 3;
-  return ((int64_t)t * d.Jp + block_start(k, d.dense)) * kTile +
-         (big ? large_block_offset(d.nl, d.nu, d.dense, c, s, l)
-              : block_offset(kSmallRows, kSmallCoef, d.dense, c, s, l));
+  return (int64_t)internal * d.J + (k < 3 ? (k * kSmallRows + s) * kSmallCoef
+                                          : 3 * kSmallRows * kSmallCoef + s * d.nu) + l;
 }
 
 inline int64_t packed_idx_index(const Mesh& m, int internal, int row) {
@@ -240,6 +231,9 @@ inline int64_t packed_idx_index(const Mesh& m, int internal, int row) {
 int mesh_create(int32_t n_vert, const double* xy, int32_t n_cell, const int32_t* tri,
                 const double* period, Mesh& m);
 int mesh_setup(Mesh& m, const teno_params& p);
+// M[l][s] of stencil k of (user) cell, in the monomials xi^a eta^b of the reference
+// triangle less their means, formed on request.
+void stencil_operator(const Mesh& m, int cell, int k, double* M);
 
 }  // namespace teno
 

@@ -17,8 +17,9 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <thread>
 #include <mutex>
+#include <thread>
+#include <utility>
 
 #include "internal.h"
 
@@ -33,7 +34,7 @@ int fail(int code, const std::string& msg) {
 }
 const char* last_error() { return g_error.c_str(); }
 
-Dims dims_for(int order, int nq_req, bool dense) {
+Dims dims_for(int order, int nq_req) {
   Dims d;
   d.order = order;
   d.r = order - 1;
@@ -44,9 +45,6 @@ Dims dims_for(int order, int nq_req, bool dense) {
   d.rows = 3 * kSmallRows + d.nl;
   d.rows4 = (d.rows + 3) / 4;
   d.J = 3 * kSmallCoef * kSmallRows + d.nu * d.nl;
-  d.dense = dense;
-  d.lblk = large_block(d.nl, d.nu, dense);
-  d.Jp = 3 * small_block(dense) + d.lblk;
   return d;
 }
 
@@ -395,13 +393,13 @@ struct RadonRule {
 };
 typedef RadonRule<double> Radon;
 
-// Householder QR of the m x n row-major matrix A, then
-//   Op[l][s] = (R^{-1} Q_1^T)[l][s] * scale[s].
-// Returns min|R_jj|/max|R_jj| (0 on breakdown: not above `tiny`).
+// Householder QR of the m x n row-major matrix A in place: R on and above the
+// diagonal, vectors (v_j = 1) below, factors in beta.  Returns min|R_jj|/max|R_jj|
+// (0 on breakdown: not above `tiny`).
 template <class T>
-T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
-  // A row-major [m][n]; Householder vectors stored in place below the diagonal
-  std::vector<T> vj(m), beta(n);
+T householder(int m, int n, std::vector<T>& A, std::vector<T>& beta, T tiny) {
+  beta.resize(n);
+  std::vector<T> w(n);
   for (int j = 0; j < n; ++j) {
     T nrm2 = 0.0;
     for (int i = j; i < m; ++i) nrm2 += A[(size_t)i * n + j] * A[(size_t)i * n + j];
@@ -415,12 +413,19 @@ T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
     T vv = 1.0;
     for (int i = j + 1; i < m; ++i) vv += A[(size_t)i * n + j] * A[(size_t)i * n + j];
     beta[j] = 2.0 / vv;
+    // the columns to the right, row by row (each column's sum in row order)
+    for (int c = j + 1; c < n; ++c) w[c] = A[(size_t)j * n + c];
+    for (int i = j + 1; i < m; ++i) {
+      const T v = A[(size_t)i * n + j];
+      for (int c = j + 1; c < n; ++c) w[c] += v * A[(size_t)i * n + c];
+    }
     for (int c = j + 1; c < n; ++c) {
-      T s = A[(size_t)j * n + c];
-      for (int i = j + 1; i < m; ++i) s += A[(size_t)i * n + j] * A[(size_t)i * n + c];
-      s *= beta[j];
-      A[(size_t)j * n + c] -= s;
-      for (int i = j + 1; i < m; ++i) A[(size_t)i * n + c] -= s * A[(size_t)i * n + j];
+      w[c] *= beta[j];
+      A[(size_t)j * n + c] -= w[c];
+    }
+    for (int i = j + 1; i < m; ++i) {
+      const T v = A[(size_t)i * n + j];
+      for (int c = j + 1; c < n; ++c) A[(size_t)i * n + c] -= w[c] * v;
     }
     A[(size_t)j * n + j] = alpha;
   }
@@ -431,6 +436,16 @@ T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
     rmin = std::min(rmin, d);
   }
   if (!(rmin > tiny * rmax)) return 0;
+  return rmin / rmax;
+}
+
+// Op[l][s] = (R^{-1} Q_1^T)[l][s] * scale[s] of A = Q_1 R (m x n, row-major; A is
+// overwritten).  Returns householder's ratio.
+template <class T>
+T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
+  std::vector<T> beta;
+  const T rc = householder(m, n, A, beta, tiny);
+  if (rc == 0) return 0;
   // Q_1 (m x n): apply H_{n-1} ... H_0 to the first n columns of I
   std::vector<T> Q((size_t)m * n, 0.0);
   for (int j = 0; j < n; ++j) Q[(size_t)j * n + j] = 1.0;
@@ -452,7 +467,7 @@ T pinv_scaled(int m, int n, std::vector<T>& A, const T* scale, T* Op, T tiny) {
     }
     for (int l = 0; l < n; ++l) Op[(size_t)l * m + s] = x[l] * scale[s];
   }
-  return rmin / rmax;
+  return rc;
 }
 
 double pinv_scaled(int m, int n, std::vector<double>& A, const double* scale, double* Op) {
@@ -484,19 +499,43 @@ static void lsq_rows(const Mesh& m, const Basis& B, const Radon& rule, int i, co
     }
     // reference-space volume: |V_s| / |det J|
     vol[s] = m.area[j] / det;
-    for (int l = 0; l < B.n; ++l) {
-      double acc = 0.0;
-      for (int g = 0; g < 7; ++g) {
-        double xi = rule.l[g][0] * q[0][0] + rule.l[g][1] * q[1][0] + rule.l[g][2] * q[2][0];
-        double eta = rule.l[g][0] * q[0][1] + rule.l[g][1] * q[1][1] + rule.l[g][2] * q[2][1];
-        double p = 1.0;
-        for (int t = 0; t < B.ea[l]; ++t) p *= xi;
-        for (int t = 0; t < B.eb[l]; ++t) p *= eta;
-        acc += rule.w[g] * p;
+    // (xi^a eta^b as xi ... xi eta ... eta, each from the one before)
+    double acc[21] = {};
+    for (int g = 0; g < 7; ++g) {
+      const double xi = rule.l[g][0] * q[0][0] + rule.l[g][1] * q[1][0] + rule.l[g][2] * q[2][0];
+      const double eta = rule.l[g][0] * q[0][1] + rule.l[g][1] * q[1][1] + rule.l[g][2] * q[2][1];
+      double p[21];
+      for (int l = 0; l < B.n; ++l) {
+        const int deg = B.ea[l] + B.eb[l], first = deg * (deg - 1) / 2 - 1;  // of degree deg - 1
+        p[l] = B.eb[l] == 0 ? (deg == 1 ? xi : p[first] * xi)
+                            : (deg == 1 ? eta : p[first + B.eb[l] - 1] * eta);
+        acc[l] += rule.w[g] * p[l];
       }
-      A[(size_t)s * B.n + l] = vol[s] * (acc - B.mean[l]);
     }
+    for (int l = 0; l < B.n; ++l) A[(size_t)s * B.n + l] = vol[s] * (acc[l] - B.mean[l]);
   }
+}
+
+void stencil_operator(const Mesh& m, int cell, int k, double* M) {
+  const bool big = k == 3;
+  const int nrow = big ? m.d.nl : kSmallRows, t = m.inv[cell];
+  int32_t mem[64];
+  for (int s = 0; s < nrow; ++s)
+    mem[s] = m.perm[m.idx[packed_idx_index(m, t, big ? large_row(s) : small_row(k, s))]];
+  std::vector<double> A, vol;
+  lsq_rows(m, basis_of(big ? m.d.r : 2), Radon(), cell, mem, nrow, A, vol);
+  pinv_scaled(nrow, big ? m.d.nu : kSmallCoef, A, vol.data(), M);
+}
+
+double Operators::operator[](int64_t at) const {
+  const Dims& d = mesh->d;
+  const int cell = mesh->perm[at / d.J], small = kSmallRows * kSmallCoef;
+  int e = (int)(at % d.J);
+  const int k = e < 3 * small ? e / small : 3, n = k == 3 ? d.nu : kSmallCoef, nrow = k == 3 ? d.nl : kSmallRows;
+  e -= k * small;
+  std::vector<double> M((size_t)n * nrow);
+  stencil_operator(*mesh, cell, k, M.data());
+  return M[(size_t)(e % n) * nrow + e / n];
 }
 
 // Morton code of a point in [0,1)^2 on a 2^16 grid.
@@ -534,24 +573,35 @@ typedef long double Ext;
 
 // E[H_a(x + X) H_b(y + Y)] for 0 <= a + b <= r from the central moments
 // mu[a][b] = E[H_a(X) H_b(Y)] (the binomial shift of an Appell sequence)
+// (by degree, unrolled: a column's moments stay in registers)
+template <int n>
+static inline __attribute__((always_inline)) void shift_line(Ext x, Ext (&v)[6]) {
+#pragma GCC unroll 6
+  for (int i = 1; i <= n; ++i)
+#pragma GCC unroll 6
+    for (int a = n; a >= i; --a) v[a] += x * v[a - 1];
+}
+template <int r, int b = 0>
+static inline __attribute__((always_inline)) void shift_lines(Ext x, const Ext (&in)[6][6], Ext (&out)[6][6]) {
+  Ext v[6];
+#pragma GCC unroll 6
+  for (int a = 0; a <= r - b; ++a) v[a] = in[a][b];
+  shift_line<r - b>(x, v);
+#pragma GCC unroll 6
+  for (int a = 0; a <= r - b; ++a) out[b][a] = v[a];
+  if constexpr (b < r) shift_lines<r, b + 1>(x, in, out);
+}
+template <int r>
+static void shift_moments(Ext x, Ext y, const Ext (&mu)[6][6], Ext (&out)[6][6]) {
+  Ext t[6][6];  // [b][a]
+  shift_lines<r>(x, mu, t);
+  shift_lines<r>(y, t, out);
+}
 static void shift_moments(int r, Ext x, Ext y, const Ext (&mu)[6][6], Ext (&out)[6][6]) {
-  Ext t[6][6];
-  for (int b = 0; b <= r; ++b) {
-    Ext v[6];
-    const int n = r - b;
-    for (int a = 0; a <= n; ++a) v[a] = mu[a][b];
-    for (int i = 1; i <= n; ++i)
-      for (int a = n; a >= i; --a) v[a] += x * v[a - 1];
-    for (int a = 0; a <= n; ++a) t[a][b] = v[a];
-  }
-  for (int a = 0; a <= r; ++a) {
-    Ext v[6];
-    const int n = r - a;
-    for (int b = 0; b <= n; ++b) v[b] = t[a][b];
-    for (int i = 1; i <= n; ++i)
-      for (int b = n; b >= i; --b) v[b] += y * v[b - 1];
-    for (int b = 0; b <= n; ++b) out[a][b] = v[b];
-  }
+  if (r == 2) shift_moments<2>(x, y, mu, out);
+  if (r == 3) shift_moments<3>(x, y, mu, out);
+  if (r == 4) shift_moments<4>(x, y, mu, out);
+  if (r == 5) shift_moments<5>(x, y, mu, out);
 }
 
 // X = (A^T A)^-1 of the m x n row-major A: Cholesky, or the triangular factor
@@ -559,22 +609,64 @@ static void shift_moments(int r, Ext x, Ext y, const Ext (&mu)[6][6], Ext (&out)
 static void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& X) {
   std::vector<Ext> L((size_t)n * n, 0);
   bool ok = true;
-  for (int j = 0; j < n && ok; ++j)
-    for (int i = j; i < n; ++i) {
+  std::vector<Ext> G((size_t)n * n);  // upper triangle of A^T A, four sums at a time
+  for (int j = 0; j < n; ++j) {
+    int i = j;
+    for (; i + 3 < n; i += 4) {
+      Ext s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+      for (int k = 0; k < m; ++k) {
+        const Ext* a = &A[(size_t)k * n];
+        const Ext x = a[j];
+        s0 += a[i] * x;
+        s1 += a[i + 1] * x;
+        s2 += a[i + 2] * x;
+        s3 += a[i + 3] * x;
+      }
+      Ext* g = &G[(size_t)j * n + i];
+      g[0] = s0;
+      g[1] = s1;
+      g[2] = s2;
+      g[3] = s3;
+    }
+    for (; i < n; ++i) {
       Ext s = 0;
       for (int k = 0; k < m; ++k) s += A[(size_t)k * n + i] * A[(size_t)k * n + j];
-      const Ext d0 = s;
-      for (int k = 0; k < j; ++k) s -= L[(size_t)i * n + k] * L[(size_t)j * n + k];
-      if (i == j) {
-        if (!(s > d0 * 1e-16L)) {
-          ok = false;
-          break;
-        }
-        L[(size_t)j * n + j] = std::sqrt(s);
-      } else {
-        L[(size_t)i * n + j] = s / L[(size_t)j * n + j];
-      }
+      G[(size_t)j * n + i] = s;
     }
+  }
+  // Cholesky, four rows of a column at a time
+  for (int j = 0; j < n && ok; ++j) {
+    const Ext* lj = &L[(size_t)j * n];
+    Ext s = G[(size_t)j * n + j];
+    for (int k = 0; k < j; ++k) s -= lj[k] * lj[k];
+    if (!(s > G[(size_t)j * n + j] * 1e-16L)) {
+      ok = false;
+      break;
+    }
+    const Ext piv = std::sqrt(s);
+    L[(size_t)j * n + j] = piv;
+    int i = j + 1;
+    for (; i + 3 < n; i += 4) {
+      const Ext *g = &G[(size_t)j * n + i], *l0 = &L[(size_t)i * n], *l1 = l0 + n, *l2 = l1 + n, *l3 = l2 + n;
+      Ext s0 = g[0], s1 = g[1], s2 = g[2], s3 = g[3];
+      for (int k = 0; k < j; ++k) {
+        const Ext x = lj[k];
+        s0 -= l0[k] * x;
+        s1 -= l1[k] * x;
+        s2 -= l2[k] * x;
+        s3 -= l3[k] * x;
+      }
+      L[(size_t)i * n + j] = s0 / piv;
+      L[(size_t)(i + 1) * n + j] = s1 / piv;
+      L[(size_t)(i + 2) * n + j] = s2 / piv;
+      L[(size_t)(i + 3) * n + j] = s3 / piv;
+    }
+    for (; i < n; ++i) {
+      Ext t = G[(size_t)j * n + i];
+      for (int k = 0; k < j; ++k) t -= L[(size_t)i * n + k] * lj[k];
+      L[(size_t)i * n + j] = t / piv;
+    }
+  }
   if (!ok) {
     for (int j = 0; j < n; ++j) {
       Ext nrm = 0;
@@ -594,20 +686,41 @@ static void normal_inverse(int m, int n, std::vector<Ext>& A, std::vector<Ext>& 
       for (int c = j + 1; c < n; ++c) L[(size_t)c * n + j] = A[(size_t)j * n + c];  // L = R^T
     }
   }
-  // L^-1 (lower triangular), then X = L^-T L^-1
-  std::vector<Ext> Li((size_t)n * n, 0);
-  for (int c = 0; c < n; ++c)
-    for (int i = c; i < n; ++i) {
-      Ext s = i == c ? 1 : 0;
-      for (int k = c; k < i; ++k) s -= L[(size_t)i * n + k] * Li[(size_t)k * n + c];
-      Li[(size_t)i * n + c] = s / L[(size_t)i * n + i];
+  // L^-1 (lower triangular; four columns at a time, zeros above the diagonal),
+  // then X = L^-T L^-1
+  std::vector<Ext> Li((size_t)n * (n + 4), 0);
+  const int w = n + 4;
+  for (int i = 0; i < n; ++i) {
+    const Ext* l = &L[(size_t)i * n];
+    for (int c = 0; c <= i; c += 4) {
+      Ext s0 = i == c, s1 = i == c + 1, s2 = i == c + 2, s3 = i == c + 3;
+      for (int k = c; k < i; ++k) {
+        const Ext x = l[k], *q = &Li[(size_t)k * w + c];
+        s0 -= x * q[0];
+        s1 -= x * q[1];
+        s2 -= x * q[2];
+        s3 -= x * q[3];
+      }
+      Ext* q = &Li[(size_t)i * w + c];
+      q[0] = s0 / l[i];
+      q[1] = s1 / l[i];
+      q[2] = s2 / l[i];
+      q[3] = s3 / l[i];
     }
+  }
   X.assign((size_t)n * n, 0);
   for (int i = 0; i < n; ++i)
-    for (int j = i; j < n; ++j) {
-      Ext s = 0;
-      for (int k = j; k < n; ++k) s += Li[(size_t)k * n + i] * Li[(size_t)k * n + j];
-      X[(size_t)i * n + j] = X[(size_t)j * n + i] = s;
+    for (int j = i; j < n; j += 4) {
+      Ext s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+      for (int k = j; k < n; ++k) {
+        const Ext x = Li[(size_t)k * w + i], *q = &Li[(size_t)k * w + j];
+        s0 += x * q[0];
+        s1 += x * q[1];
+        s2 += x * q[2];
+        s3 += x * q[3];
+      }
+      const Ext s[4] = {s0, s1, s2, s3};
+      for (int q = 0; q < 4 && j + q < n; ++q) X[(size_t)i * n + j + q] = X[(size_t)(j + q) * n + i] = s[q];
     }
 }
 
@@ -825,6 +938,33 @@ struct Image {
   bool operator==(const Image& o) const { return id == o.id && kx == o.kx && ky == o.ky; }
 };
 
+// Images and the slots they were first given, open addressing.
+struct ImageSlots {
+  std::vector<std::pair<Image, int>> at;
+  size_t used = 0;
+  explicit ImageSlots(size_t n) : at(n, {Image{-1, 0, 0}, 0}) {}
+  size_t place(const Image& im) const {
+    uint64_t h = (uint64_t)(uint32_t)im.id << 16 ^ (uint64_t)(uint32_t)(im.kx * 256 + im.ky);
+    size_t k = (h * 0x9E3779B97F4A7C15ull >> 20) & (at.size() - 1);
+    while (at[k].first.id >= 0 && !(at[k].first == im)) k = (k + 1) & (at.size() - 1);
+    return k;
+  }
+  bool add(const Image& im, int slot) {  // false: was there
+    if (2 * used >= at.size()) {
+      ImageSlots twice(2 * at.size());
+      for (auto& e : at)
+        if (e.first.id >= 0) twice.add(e.first, e.second);
+      *this = std::move(twice);
+    }
+    auto& e = at[place(im)];
+    if (e.first.id >= 0) return false;
+    e = {im, slot};
+    ++used;
+    return true;
+  }
+  int slot(const Image& im) const { return at[place(im)].second; }
+};
+
 // Packed order of positions [lo, hi): bisection along the longer side of the
 // box of the centroids (wrapped on periodic axes), at multiples of `unit` cells
 // down to one block, then of a tile.
@@ -892,6 +1032,10 @@ static void pack_blocks(Mesh& m) {
         im.id = m.pack[std::min(t0 + c, nc - 1)];
         image_of(im.id, origin, im.kx, im.ky);
       }
+      // the block's own cells, then the other members by id
+      ImageSlots seen(2048);
+      u = own;
+      for (const Image& im : own) seen.add(im, 0);
       for (int t = t0; t < t1; ++t)
         for (int row = 0; row < d.rows; ++row) {
           Image im;
@@ -899,16 +1043,9 @@ static void pack_blocks(Mesh& m) {
           image_of(im.id, m.pack[t], im.kx, im.ky);
           im.kx += own[t - t0].kx;
           im.ky += own[t - t0].ky;
-          u.push_back(im);
+          if (seen.add(im, 0)) u.push_back(im);
         }
-      std::sort(u.begin(), u.end());
-      u.erase(std::unique(u.begin(), u.end()), u.end());
-      std::vector<Image> so(own);
-      std::sort(so.begin(), so.end());
-      u.erase(std::remove_if(u.begin(), u.end(),
-                             [&](const Image& x) { return std::binary_search(so.begin(), so.end(), x); }),
-              u.end());
-      u.insert(u.begin(), own.begin(), own.end());
+      std::sort(u.begin() + cells, u.end());
       int cur = top.load();
       while ((int)u.size() > cur && !top.compare_exchange_weak(cur, (int)u.size())) {
       }
@@ -1027,6 +1164,8 @@ static void pack_blocks(Mesh& m) {
     };
     std::vector<Ext> A, X, op;
     int32_t mem[64];
+    ImageSlots at_slot(2048);
+    for (size_t k = 0; k < u.size(); ++k) at_slot.add(u[k], (int)k);
     for (int c = 0; c < cells; ++c) {
       const int t = t0 + c, tile = t / kTile, tc = t % kTile;
       if (tile >= m.n_tiles) break;
@@ -1071,10 +1210,7 @@ static void pack_blocks(Mesh& m) {
           image_of(im.id, m.pack[t], im.kx, im.ky);
           im.kx += u[c].kx;
           im.ky += u[c].ky;
-          // a member among the block's own cells, or in the sorted rest
-          auto at = std::lower_bound(u.begin() + cells, u.end(), im);
-          if (at == u.end() || !(*at == im)) at = std::find(u.begin(), u.begin() + cells, im);
-          const int slot = (int)(at - u.begin());
+          const int slot = at_slot.slot(im);
           put(tc * 4 + s % 4, grp0 + s / 4, slot);
           slots[s] = slot;
           const double* R = &rec[(size_t)slot * (nu + 1)];
@@ -1172,7 +1308,7 @@ int mesh_setup(Mesh& m, const teno_params& p) {
   if (p.power < 1 || p.power > 16) return fail(TENO_EARG, "power must be 1..16");
   if (p.n_quad != 0 && (p.n_quad < 2 || p.n_quad > 3)) return fail(TENO_EARG, "n_quad must be 0, 2 or 3");
   m.prm = p;
-  m.d = dims_for(p.order, p.n_quad, p.characteristic == 0);
+  m.d = dims_for(p.order, p.n_quad);
   const Dims& d = m.d;
   const int nc = m.nc;
   // stencil rows are addressed as cell * 4 ceil(rows / 4) + row in 32 bits
@@ -1205,9 +1341,8 @@ int mesh_setup(Mesh& m, const teno_params& p) {
   m.n_pad = m.n_tiles * kTile;
   try {
     m.idx.assign((size_t)m.n_tiles * d.rows4 * kTile * 4, 0);
-    m.M.assign((size_t)m.n_tiles * d.Jp * kTile, 0.0);
   } catch (...) {
-    return fail(TENO_ENOMEM, "host allocation of packed operators failed");
+    return fail(TENO_ENOMEM, "host allocation of the stencils failed");
   }
 
   Bins bins;
@@ -1220,7 +1355,7 @@ int mesh_setup(Mesh& m, const teno_params& p) {
   double rc_min = 1.0;
   parallel_for(nc, p.n_threads, [&](int i) {
     std::vector<Hit> scratch;
-    std::vector<double> A, vol, op;
+    std::vector<double> A, vol, beta;
     int32_t mem[64];
     const int t = m.inv[i];
     double rc_local = 1.0;
@@ -1251,18 +1386,14 @@ int mesh_setup(Mesh& m, const teno_params& p) {
         }
       }
       lsq_rows(m, B, rule, i, mem, nrow, A, vol);
-      op.assign((size_t)B.n * nrow, 0.0);
-      double rc = pinv_scaled(nrow, B.n, A, vol.data(), op.data());
+      const double rc = householder(nrow, B.n, A, beta, 1e-13);
       if (rc == 0.0) {
         report(TENO_ERANK, "rank-deficient least-squares matrix at cell " + std::to_string(i));
         return;
       }
       rc_local = std::min(rc_local, rc);
-      for (int s = 0; s < nrow; ++s) {
+      for (int s = 0; s < nrow; ++s)
         m.idx[packed_idx_index(m, t, big ? large_row(s) : small_row(k, s))] = m.inv[mem[s]];
-        for (int l = 0; l < B.n; ++l)
-          m.M[packed_M_offset(d, t, k, s, l)] = op[(size_t)l * nrow + s];
-      }
     }
     std::lock_guard<std::mutex> g(mu);
     rc_min = std::min(rc_min, rc_local);
@@ -1350,11 +1481,10 @@ int mesh_setup(Mesh& m, const teno_params& p) {
   {
     std::atomic<int> top{1};
     parallel_for(m.n_tiles, p.n_threads, [&](int tile) {
-      std::vector<int32_t> u;
+      ImageSlots u(1024);
       for (int t = tile * kTile; t < std::min(nc, (tile + 1) * kTile); ++t)
-        for (int r = 0; r < d.rows; ++r) u.push_back(m.idx[packed_idx_index(m, t, r)]);
-      std::sort(u.begin(), u.end());
-      const int n = (int)(std::unique(u.begin(), u.end()) - u.begin());
+        for (int r = 0; r < d.rows; ++r) u.add({m.idx[packed_idx_index(m, t, r)], 0, 0}, 0);
+      const int n = (int)u.used;
       int cur = top.load();
       while (n > cur && !top.compare_exchange_weak(cur, n)) {
       }
@@ -1446,6 +1576,7 @@ int mesh_setup(Mesh& m, const teno_params& p) {
     for (size_t e = 0; e < m.kept_rows.size(); ++e)
       if (kept_row(e)) m.rev_ent[fill[m.kept_rows[e]]++] = m.n_tiles * m.ustride + (int32_t)e;
   }
+  m.M.mesh = &m;
   m.ready = true;
   return TENO_OK;
 }

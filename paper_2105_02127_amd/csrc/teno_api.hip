@@ -569,13 +569,12 @@ int teno_mesh_lsq_operator(const teno_mesh* m, int32_t cell, int32_t k, double* 
   const Mesh& x = m->m;
   if (!x.ready) return fail(TENO_EARG, "teno_mesh_setup not called");
   if (cell < 0 || cell >= x.nc || k < 0 || k > 3) return fail(TENO_EARG, "cell or stencil out of range");
-  const int t = x.inv[cell];
-  const bool big = k == 3;
-  const int nrow = big ? x.d.nl : kSmallRows, nco = big ? x.d.nu : kSmallCoef;
-  for (int l = 0; l < nco; ++l)
-    for (int s = 0; s < nrow; ++s)
-      M[(size_t)l * nrow + s] = x.M[packed_M_offset(x.d, t, k, s, l)];
-  return nrow;
+  try {
+    stencil_operator(x, cell, k, M);
+  } catch (const std::bad_alloc&) {
+    return fail(TENO_ENOMEM, "host allocation of an operator failed");
+  }
+  return k == 3 ? x.d.nl : kSmallRows;
 }
 
 void teno_mesh_destroy(teno_mesh* m) { delete m; }
@@ -1055,7 +1054,7 @@ int batch_plan(teno_batch* b) {
   for (int m = 0; m < n; ++m) morder[m] = m;
   if (T.item_order == 1)
     std::stable_sort(morder.begin(), morder.end(), [&](int x, int y) {
-      return b->sv[x]->d.Jp > b->sv[y]->d.Jp;
+      return b->sv[x]->d.order > b->sv[y]->d.order;
     });
   // reconstruction items, grouped per launch
   std::vector<int2> items;
@@ -1083,7 +1082,7 @@ int batch_plan(teno_batch* b) {
       order = s->d.order;
       for (int t = 0; t < s->n_blocks; ++t) {
         items.push_back(make_int2(m, t));
-        cost.push_back(s->bwaves * ((double)s->d.Jp + 4.0 * s->d.rows4 * 4));
+        cost.push_back(s->bwaves * ((double)s->d.J + 4.0 * s->d.rows4 * 4));
       }
     }
     const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);

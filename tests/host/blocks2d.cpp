@@ -45,7 +45,7 @@ struct Range {
 };
 
 static void check_layout(int order, int waves, int members, int buffers, bool characteristic) {
-  const Dims d = dims_for(order, 0, !characteristic);
+  const Dims d = dims_for(order, 0);
   const int stride = buffer_stride(d.nu, members, waves, characteristic);
   const int total = group_lds_bytes(stride, members, buffers);
   char at[160];
@@ -274,6 +274,8 @@ struct Exact {
 static double operator_worst(const Mesh& m, int cell, int k, int r, int n, int nrow,
                              const std::vector<Quad>& op, const Quad* mean) {
   double worst = 0.0;
+  std::vector<double> M((size_t)n * nrow);
+  stencil_operator(m, m.perm[cell], k, M.data());
   for (int e = 0; e < 3; ++e)
     for (int q = 0; q < 3; ++q) {
       const Quad p = (Quad)0.5 + (q - 1) * (Quad)0.3872983346207417;
@@ -290,7 +292,7 @@ static double operator_worst(const Mesh& m, int cell, int k, int r, int n, int n
             for (int i = 1; i <= j; ++i) f *= i;
             for (int i = d - j + 1; i <= d + 2; ++i) f /= i;
             a += op[(size_t)s * n + l] * (x[l] - mean[l]);
-            b += (Quad)m.M[packed_M_offset(m.d, cell, k, s, l)] * (y[l] - (Quad)f);
+            b += (Quad)M[(size_t)l * nrow + s] * (y[l] - (Quad)f);
           }
         t += std::fabs((double)(b - a)) + 1.1e-16 * std::fabs((double)a);
       }
@@ -449,7 +451,11 @@ int main(int argc, char** argv) {
   set_up(m, order, variant, ch);
   check_layout(order, m.bwaves, m.bmax, m.nbuf, ch != 0);
   const int stride = buffer_stride(m.d.nu, m.bmax, m.bwaves, ch != 0);
-  std::printf("bwaves %d nbuf %d bmax %d blocks %d lds %d\n", m.bwaves, m.nbuf, m.bmax,
-              (int)m.boff.size() - 1, group_lds_bytes(stride, m.bmax, m.nbuf));
+  long peak = 0;  // kB (ru_maxrss would count the parent's)
+  std::ifstream status("/proc/self/status");
+  for (std::string line; std::getline(status, line);)
+    if (std::sscanf(line.c_str(), "VmHWM: %ld", &peak) == 1) break;
+  std::printf("bwaves %d nbuf %d bmax %d blocks %d lds %d peak_kb %ld\n", m.bwaves, m.nbuf, m.bmax,
+              (int)m.boff.size() - 1, group_lds_bytes(stride, m.bmax, m.nbuf), peak);
   return 0;
 }

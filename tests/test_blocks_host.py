@@ -62,6 +62,13 @@ def test_characteristic_block_layouts_of_meshes(driver, order, kind):
     assert s["lds"] <= 160 * 1024
 
 
+def test_setup_stores_no_operators(driver):
+    # order 6: the device arrays take 3.0 KB a cell, the operators would take 8.3 KB
+    m = inputs.jittered_periodic_mesh(150, 3)
+    s = _mesh(driver, m, 6)
+    assert s["peak_kb"] * 1024 < 8000 * m.n_cell, s
+
+
 # (angle, growth): radii 1 : e^growth over a sector of that angle; 0: a jittered
 # periodic mesh; -1: a box stretched eightfold
 @pytest.mark.parametrize("order", [3, 4, 5, 6])
