@@ -316,11 +316,11 @@ __device__ __forceinline__ unsigned list_offset(TENO_CONST BlockArgs& b, int k) 
 // read; nothing is returned in a register.
 __device__ __forceinline__ void lds_copy16(const void* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :: "s"(lds), "v"(src) : "memory");
+               :: "s"(lds), "v"(src) : "m0", "memory");
 }
 __device__ __forceinline__ void lds_copy4(const void* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
-               :: "s"(lds), "v"(src) : "memory");
+               :: "s"(lds), "v"(src) : "m0", "memory");
 }
 // A uniform load through the scalar cache (of data that no kernel writes); the
 // copies' memory clobbers would otherwise turn it into a vector load.

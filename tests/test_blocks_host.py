@@ -1,6 +1,7 @@
 """Host checks (no GPU) of what set-up packs for the triangle kernels' blocks,
 through the driver tests/host/blocks2d.cpp."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -60,6 +61,16 @@ def test_characteristic_block_layouts_of_meshes(driver, order, kind):
          "strip": lambda: inputs.jittered_box_mesh(400, 12, 4, lx=400.0, ly=12.0)}[kind]()
     s = _mesh(driver, m, order, characteristic=1)
     assert s["lds"] <= 160 * 1024
+
+
+def test_inline_assembly_names_m0():
+    # a copy to LDS sets m0; unnamed, the compiler may keep something else there
+    for name in ("kernels.hpp", "kernels3.hpp"):
+        src = open(os.path.join(ROOT, "paper_2105_02127_amd", "csrc", name)).read()
+        for asm in re.findall(r"asm volatile\((.*?)\);", src, flags=re.S):
+            text, _, operands = asm.rpartition(":")
+            if re.search(r"s_mov_b32 m0|\bm0,", asm):
+                assert '"m0"' in operands, asm
 
 
 def test_setup_stores_no_operators(driver):
