@@ -77,6 +77,25 @@ constexpr int group_lds_bytes(int stride, int members, int buffers) {
   return buffers * (stride + ids_bytes(members));
 }
 constexpr int kLdsPerCu = 160 * 1024;
+// A tile by itself (small meshes): its staged block; over it, once read, the
+// coefficients [15 + nu][64] and in characteristic variables the Gram matrices.
+constexpr int small_lds_bytes(int nu, int members, bool characteristic) {
+  const int staged = block_lds_bytes(nu, members);
+  const int coef = (3 * 5 + nu) * 512 + (characteristic ? gram_bytes(1) : 0);
+  return staged > coef ? staged : coef;
+}
+// The adjoint: the block's records, and an accumulator per member of each tile.
+constexpr int adjoint_lds_bytes(int nu, int members, int waves, int ustride) {
+  return 16 * rec_units(nu) * members + waves * ustride * 4 * (int)sizeof(double);
+}
+constexpr int kSlotBits = 10;       // of a member's slot in its block
+constexpr int kMaxAdjMembers = 512; // of a tile: nine bits of the adjoint's slots
+constexpr bool layout_fits(int nu, int waves, int members, int buffers, int ustride, bool characteristic) {
+  return members <= 1 << kSlotBits && ustride <= kMaxAdjMembers &&
+         group_lds_bytes(buffer_stride(nu, members, waves, characteristic), members, buffers) <= kLdsPerCu &&
+         small_lds_bytes(nu, members, characteristic) <= kLdsPerCu &&
+         adjoint_lds_bytes(nu, members, waves, ustride) <= kLdsPerCu;
+}
 // Tiles (wavefronts) per block: workgroups of four, two or more to a CU, at
 // orders 3 and 4; at orders 5 and 6, whose records are longer and whose
 // registers allow two wavefronts per SIMD, one of eight, whose cells share more
@@ -95,7 +114,6 @@ constexpr int normal_quads(int nu) { return 3 * sym_quads(kSmallCoef) + sym_quad
 // member slots, ten bits each, three to a word, stencil by stencil and j by j,
 // in words [word][64 lanes].  Lanes without a row name their own cell
 // (difference 0).
-constexpr int kSlotBits = 10;
 constexpr int row_groups(int nrow) { return (nrow + 3) / 4; }
 constexpr int lane_groups(int nl) { return 3 * row_groups(kSmallRows) + row_groups(nl); }
 constexpr int slot_words(int nl) { return (lane_groups(nl) + 2) / 3; }

@@ -1655,14 +1655,6 @@ __attribute__((amdgpu_waves_per_eu(recon_waves(P)))) void k_reconstruct_char(Rec
 constexpr int small_tiles(int order, bool characteristic_teno) {
   return order > 3 ? 512 : (characteristic_teno ? 4096 : 1024);
 }
-// LDS: the staged block; over it, once read, the coefficients [15 + NU][64] and in
-// characteristic variables the Gram matrices.
-constexpr int small_lds_bytes(int nu, int members, bool characteristic) {
-  const int staged = block_lds_bytes(nu, members);
-  const int coef = (3 * kSmallCoef + nu) * 512 + (characteristic ? gram_bytes(1) : 0);
-  return staged > coef ? staged : coef;
-}
-
 // wavefronts per SIMD: as many workgroups on a CU
 constexpr int small_waves(int p) { return p == 3 ? 4 : 2; }
 

@@ -997,7 +997,10 @@ static void pack_bisect(Mesh& m, int lo, int hi, int unit, int threads) {
   }
 }
 
-static void pack_blocks(Mesh& m) {
+// False: no layout fits.  (Cells that are compact in no sense, which the limit on
+// 16 consecutive ones has let through, may scatter more when bisected: then tiles
+// are the runs of the internal order that the limit speaks of.)
+static bool pack_blocks(Mesh& m, int most_tiles, bool bisect) {
   const Dims& d = m.d;
   const int nc = m.nc, r = d.r, nu = d.nu, units = rec_units(nu);
   // images relative to the origin cell o (both internal): K of cell j
@@ -1013,16 +1016,16 @@ static void pack_blocks(Mesh& m) {
   std::vector<std::vector<Image>> lists;
   int n_blocks = 0;
   // as many tiles per block as the LDS allows
-  for (m.bwaves = block_tiles(d.order), m.nbuf = 2;;) {
+  for (m.bwaves = most_tiles, m.nbuf = 2;;) {
     const int W = m.bwaves, cells = W * kTile;
     n_blocks = (m.n_tiles + W - 1) / W;
     for (int t = 0; t < nc; ++t) m.pack[t] = t;
-    pack_bisect(m, 0, nc, cells,
+    if (bisect) pack_bisect(m, 0, nc, cells,
                 m.prm.n_threads > 0 ? m.prm.n_threads : (int)std::max(1u, std::thread::hardware_concurrency()));
     for (int t = 0; t < nc; t += kTile)
       std::sort(m.pack.begin() + t, m.pack.begin() + std::min(nc, t + kTile));
     lists.assign(n_blocks, {});
-    std::atomic<int> top{0};
+    std::atomic<int> top{0}, top_tile{0};
     parallel_for(n_blocks, m.prm.n_threads, [&](int b) {
       std::vector<Image>& u = lists[b];
       const int t0 = b * cells, t1 = std::min(nc, t0 + cells), origin = m.pack[t0];
@@ -1033,10 +1036,12 @@ static void pack_blocks(Mesh& m) {
         image_of(im.id, origin, im.kx, im.ky);
       }
       // the block's own cells, then the other members by id
-      ImageSlots seen(2048);
+      ImageSlots seen(2048), tile(512);
       u = own;
       for (const Image& im : own) seen.add(im, 0);
-      for (int t = t0; t < t1; ++t)
+      int most = 0;
+      for (int t = t0; t < t1; ++t) {
+        if (t % kTile == 0) tile = ImageSlots(512);
         for (int row = 0; row < d.rows; ++row) {
           Image im;
           im.id = m.idx[packed_idx_index(m, m.pack[t], row)];
@@ -1044,22 +1049,34 @@ static void pack_blocks(Mesh& m) {
           im.kx += own[t - t0].kx;
           im.ky += own[t - t0].ky;
           if (seen.add(im, 0)) u.push_back(im);
+          tile.add({im.id, 0, 0}, 0);
         }
+        most = std::max(most, (int)tile.used);
+      }
+      for (int cur = top_tile.load(); most > cur && !top_tile.compare_exchange_weak(cur, most);) {
+      }
       std::sort(u.begin() + cells, u.end());
       int cur = top.load();
       while ((int)u.size() > cur && !top.compare_exchange_weak(cur, (int)u.size())) {
       }
     }, 1);
     m.bmax = top.load();
-    const int stride = buffer_stride(nu, m.bmax, W, m.prm.characteristic != 0);
-    if (group_lds_bytes(stride, m.bmax, m.nbuf) <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || W == 1)
+    const bool ch = m.prm.characteristic != 0;
+    const int lds = group_lds_bytes(buffer_stride(nu, m.bmax, W, ch), m.bmax, m.nbuf);
+    if (layout_fits(nu, W, m.bmax, m.nbuf, (top_tile.load() + 15) / 16 * 16, ch) &&
+        (lds <= (m.nbuf == 2 ? lds_budget(W) : kLdsPerCu / 2) || (W == 1 && m.nbuf == 1)))
       break;
+    if (W == 1 && m.nbuf == 1) {
+      if (!bisect) return false;
+      bisect = false;
+      continue;
+    }
     // two buffers do not fit: one, in workgroups of four or fewer
     if (m.nbuf == 2 && W == 4) {
       m.nbuf = 1;
     } else {
       m.nbuf = 1;
-      m.bwaves = W / 2;
+      m.bwaves = std::max(1, W / 2);
     }
   }
   m.boff.assign(n_blocks + 1, 0);
@@ -1296,6 +1313,7 @@ static void pack_blocks(Mesh& m) {
   }, 1);
   for (int t : at)
     if (keep[t]) m.pack[t] = -1;
+  return true;
 }
 
 int mesh_setup(Mesh& m, const teno_params& p) {
@@ -1495,7 +1513,8 @@ int mesh_setup(Mesh& m, const teno_params& p) {
                                      std::to_string(kMaxTileMembers) +
                                      "); keep the default cell reordering");
   }
-  pack_blocks(m);
+  if (!pack_blocks(m, block_tiles(d.order), true))
+    return fail(TENO_ESTENCIL, "a tile's distinct stencil members do not fit the device's local memory");
 
   // ---- distinct members of each (packed) tile, the adjoint's accumulators ----
   {
@@ -1535,8 +1554,6 @@ int mesh_setup(Mesh& m, const teno_params& p) {
         }
       }
     });
-    if (umax.load() > 512)
-      return fail(TENO_ESTENCIL, "a tile has more than 512 distinct stencil members");
     m.ustride = (umax.load() + 15) / 16 * 16;
     m.tmem.assign((size_t)m.n_tiles * m.ustride, 0);
     m.tcount.assign(m.n_tiles, 0);

@@ -404,8 +404,7 @@ int launch_vjp(teno_solver* s, const double* U, const uint16_t* flags, const dou
                            dim3(256), 0, st, ff, (const int*)s->bface, s->n_bface);
       hipLaunchKernelGGL((k_adj_recon<decltype(P)::value, decltype(NQ)::value>),
                          dim3(s->n_blocks), dim3(64 * s->bwaves),
-                         (size_t)16 * rec_units(s->d.nu) * s->bmax +
-                             (size_t)s->bwaves * s->ustride * 4 * sizeof(double),
+                         (size_t)adjoint_lds_bytes(s->d.nu, s->bmax, s->bwaves, s->ustride),
                          st, ra);
       if (s->n_kept > 0)
         hipLaunchKernelGGL((k_adj_recon_kept<decltype(P)::value, decltype(NQ)::value>),

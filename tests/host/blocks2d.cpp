@@ -1,10 +1,11 @@
 // Test driver (CPU only) of the triangle kernels' block data: the LDS layout of
-// the staged blocks and what set-up packs for them.  Built with csrc/setup.cpp
-// and run by tests/test_blocks_host.py:
+// the staged blocks and what set-up packs for them.  Includes csrc/setup.cpp, whose
+// internals it calls; run by tests/test_blocks_host.py:
 //   blocks2d layout                                every layout, ranges disjoint
 //   blocks2d mesh <dir> <tag> order variant char   one mesh's blocks
-//   blocks2d solve <dir> <tag> order every         the least squares of the block
-//       data in the kernels' arithmetic, against a 128-bit solution
+//   blocks2d solve <dir> <tag> order every [runs]  the least squares of the block
+//       data in the kernels' arithmetic, against a 128-bit solution (runs: packed
+//       again in tiles that are runs of the internal order)
 //   blocks2d faces <dir> <tag> order every         face states of the linear scheme
 //       in 128 bits at every so-manieth cell: <tag>.u holds the states, user order;
 //       writes <tag>.cells and <tag>.faces [cell][point][4]
@@ -20,14 +21,10 @@
 #include <string>
 #include <vector>
 
-#include "../../paper_2105_02127_amd/csrc/internal.h"
+#include "../../paper_2105_02127_amd/csrc/setup.cpp"
 #include "../../paper_2105_02127_amd/csrc/tables.h"
 
 using namespace teno;
-
-namespace teno {
-const char* last_error();
-}
 
 static void die(const std::string& what) {
   std::fprintf(stderr, "FAILED: %s\n", what.c_str());
@@ -75,6 +72,17 @@ static void check_layout(int order, int waves, int members, int buffers, bool ch
 
 static int all_layouts() {
   int n = 0;
+  // what does not fit is told apart: slots past their ten bits, the adjoint's
+  // accumulators, two buffers, a single one
+  for (int order = 3; order <= 6; ++order) {
+    const int nu = dims_for(order, 0).nu;
+    const int one = kLdsPerCu / (block_lds_bytes(nu, 1) + 4) - 64;  // members that surely fit
+    if (!layout_fits(nu, 1, one < 1024 ? one : 1024, 1, 384, true)) die("a layout that fits was refused");
+    if (layout_fits(nu, 1, 1025, 1, 16, false) || layout_fits(nu, 1, 16, 1, 528, false) ||
+        layout_fits(nu, 1, kLdsPerCu / block_lds_bytes(nu, 1) + 1, 1, 16, false) ||
+        layout_fits(nu, 8, one / 2 + 128, 2, 16, false) || layout_fits(nu, 8, one / 2, 1, 512, false))
+      die("a layout that does not fit was accepted");
+  }
   for (int order = 3; order <= 6; ++order)
     for (int waves = 1; waves <= block_tiles(order); waves *= 2)
       for (int members = waves * kTile; members <= 1 << kSlotBits; ++members)
@@ -431,8 +439,9 @@ int main(int argc, char** argv) {
   if (argc < 5) return 2;
   load_mesh(std::string(argv[2]) + "/" + argv[3], m);
   const int order = std::atoi(argv[4]);
-  if (argc == 6 && !std::strcmp(argv[1], "solve")) {
+  if ((argc == 6 || argc == 7) && !std::strcmp(argv[1], "solve")) {
     set_up(m, order, 0, 0);
+    if (argc == 7 && (!pack_blocks(m, 1, false) || m.bwaves != 1)) die("no layout in runs");
     solve_all(m, std::atoi(argv[5]));
     return 0;
   }
@@ -450,6 +459,7 @@ int main(int argc, char** argv) {
   const int variant = std::atoi(argv[5]), ch = std::atoi(argv[6]);
   set_up(m, order, variant, ch);
   check_layout(order, m.bwaves, m.bmax, m.nbuf, ch != 0);
+  if (!layout_fits(m.d.nu, m.bwaves, m.bmax, m.nbuf, m.ustride, ch != 0)) die("a layout that does not fit");
   const int stride = buffer_stride(m.d.nu, m.bmax, m.bwaves, ch != 0);
   long peak = 0;  // kB (ru_maxrss would count the parent's)
   std::ifstream status("/proc/self/status");

@@ -20,8 +20,7 @@ def driver(tmp_path_factory):
     tmp = str(tmp_path_factory.mktemp("blocks2d"))
     exe = os.path.join(tmp, "blocks2d")
     subprocess.run(["g++", "-O2", "-std=c++17", "-pthread", "-ffp-contract=off",
-                    os.path.join(ROOT, "tests", "host", "blocks2d.cpp"),
-                    os.path.join(ROOT, "paper_2105_02127_amd", "csrc", "setup.cpp"), "-o", exe],
+                    os.path.join(ROOT, "tests", "host", "blocks2d.cpp"), "-o", exe],
                    check=True, capture_output=True)
     return tmp, exe
 
@@ -78,6 +77,15 @@ def test_setup_stores_no_operators(driver):
     m = inputs.jittered_periodic_mesh(150, 3)
     s = _mesh(driver, m, 6)
     assert s["peak_kb"] * 1024 < 8000 * m.n_cell, s
+
+
+@pytest.mark.parametrize("order", [3, 6])
+def test_tiles_of_runs(driver, order):
+    # the packing that set-up falls back to where bisected tiles do not fit
+    tmp, exe = driver
+    _write(tmp, "r", inputs.jittered_box_mesh(20, 17, 5))
+    for line in _run(exe, "solve", tmp, "r", order, 7, "runs").splitlines():
+        assert float(line.split()[-1]) <= 1.0, line
 
 
 # (angle, growth): radii 1 : e^growth over a sector of that angle; 0: a jittered
