@@ -154,6 +154,50 @@ def test_characteristic_past_the_first_blocks(oracle_mod, order, variant):
              order=order)
 
 
+@pytest.mark.parametrize("order,n,aspect,variant,characteristic,tiles,buffers", [
+    (6, 300, 4, 0, 0, 4, 1), (6, 200, 4, 0, 1, 4, 1), (6, 240, 1, 2, 1, 8, 2), (5, 200, 16, 0, 0, 4, 1), (6, 200, 16, 0, 0, 2, 1),
+    (4, 250, 16, 0, 0, 4, 1), (4, 250, 16, 0, 1, 4, 1), (3, 300, 32, 0, 0, 4, 2), (3, 300, 48, 0, 1, 4, 1)])
+def test_block_layouts_past_the_first_blocks(oracle_mod, driver, order, n, aspect, variant,  # noqa: F811
+                                             characteristic, tiles, buffers):
+    """Every layout of the staged blocks (asked of set-up) with more blocks than
+    workgroups, so that buffers alternate or one is filled again: face states and
+    flags at sampled cells, bars as above; stretched meshes with the TENO selection
+    only, for the reason above."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2105_02127_amd import teno
+    print(f"[case] past the first blocks order={order} n={n} aspect={aspect} variant={variant} "
+          f"characteristic={characteristic}", flush=True)
+    m = inputs.jittered_periodic_mesh(n, 41)
+    U = inputs.make_state(m, "random_lines")
+    m.xy = np.ascontiguousarray(m.xy * [1.0, 1.0 / aspect])
+    m.period = (1.0, 1.0 / aspect)
+    tmp, exe = driver
+    _write(tmp, "b", m)
+    w = _run(exe, "mesh", tmp, "b", order, variant, characteristic).split()
+    layout = dict(zip(w[::2], map(int, w[1::2])))
+    assert (layout["bwaves"], layout["nbuf"]) == (tiles, buffers), layout
+    # a CU holds at most as many workgroups as its LDS
+    assert layout["blocks"] > 256 * (160 * 1024 // layout["lds"])
+    kw = dict(order=order, fallback=1, variant=variant, characteristic=characteristic)
+    lm = teno.Mesh(m.xy, m.tri, period=m.period).setup(**kw)
+    sv = teno.Solver(lm)
+    om = oracle_mod.OracleMesh(m.xy, m.tri, period=m.period)
+    om.setup(oracle_mod.params(**kw), all_cells=False)
+    cells = np.unique(np.random.default_rng(order).integers(0, m.n_cell, 120))
+    fp, ofl, _, odg = om.reconstruct_cells(U, cells)
+    flags = sv.empty_flags()
+    fs = sv.reconstruct(torch.as_tensor(U[lm.perm], device="cuda"), flags=flags)
+    inv = np.empty(m.n_cell, np.int64)
+    inv[lm.perm] = np.arange(m.n_cell)
+    got = fs[:, torch.as_tensor(inv[cells], device="cuda")].permute(1, 0, 2).cpu().numpy()
+    assert_states(got, fp.reshape(len(cells), -1, 4), what="face states")
+    if variant != 2:
+        gfl = flags.cpu().numpy().view(np.uint16)[..., inv[cells]]
+        check_flags(gfl.T if characteristic else gfl, ofl, odg["tie_mask"])
+
+
 def _graded(order, angle, growth, **kw):
     import torch
     if not torch.cuda.is_available():
