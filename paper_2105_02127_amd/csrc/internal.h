@@ -102,6 +102,13 @@ constexpr bool layout_fits(int nu, int waves, int members, int buffers, int ustr
 // members.
 constexpr int block_tiles(int order) { return order >= 5 ? 8 : 4; }
 constexpr int kMaxBlockTiles = 8;
+// Time of a block's reconstruction relative to others', by which a batch's ranges
+// are balanced: us of 180,000 cells by order, for the tiles that the block has.
+constexpr double block_cost(int order, int tiles_per_block, int n_tiles, int block) {
+  const int left = n_tiles - block * tiles_per_block;
+  const double us = order == 3 ? 49.0 : (order == 4 ? 69.0 : (order == 5 ? 109.0 : 178.0));
+  return us * (left < tiles_per_block ? left : tiles_per_block);
+}
 // LDS a workgroup of w tiles may take to keep eight wavefronts on a CU
 constexpr int lds_budget(int w) { return w >= 8 ? kLdsPerCu : kLdsPerCu / 8 * w; }
 // Packed symmetric inverses of the normal matrices of a cell's stencils: three

@@ -1081,7 +1081,7 @@ int batch_plan(teno_batch* b) {
       order = s->d.order;
       for (int t = 0; t < s->n_blocks; ++t) {
         items.push_back(make_int2(m, t));
-        cost.push_back(s->bwaves * ((double)s->d.J + 4.0 * s->d.rows4 * 4));
+        cost.push_back(block_cost(s->d.order, s->bwaves, s->n_tiles, t));
       }
     }
     const int tiles = pq == 0 ? kMaxBlockTiles : block_tiles(order);

@@ -83,6 +83,13 @@ static int all_layouts() {
         layout_fits(nu, 8, one / 2 + 128, 2, 16, false) || layout_fits(nu, 8, one / 2, 1, 512, false))
       die("a layout that does not fit was accepted");
   }
+  // a batch charges a mesh for the tiles it has
+  for (int order = 3; order <= 6; ++order)
+    for (int tiles = 1; tiles <= 20; ++tiles) {
+      double sum = 0.0;
+      for (int b = 0; b * block_tiles(order) < tiles; ++b) sum += block_cost(order, block_tiles(order), tiles, b);
+      if (sum != tiles * block_cost(order, 1, 1, 0)) die("the cost of a part of a block");
+    }
   for (int order = 3; order <= 6; ++order)
     for (int waves = 1; waves <= block_tiles(order); waves *= 2)
       for (int members = waves * kTile; members <= 1 << kSlotBits; ++members)
