@@ -55,8 +55,8 @@ def algorithmic_bytes_stage(order: int) -> int:
     return ops + 8 * (nu + 1) + 64 + idx + 3 * 32 + 68
 
 
-def traffic_from_profiles(workload: str):
-    """HBM bytes per reconstruction launch from the committed rocprofv3 PMC
+def profile_value(workload: str, key: str):
+    """A figure of the reconstruction launch from the committed rocprofv3 PMC
     summary, or None when the kernel source changed since it was taken."""
     path = os.path.join(ROOT, "profiles", f"k_reconstruct_{workload}_pmc.txt")
     if not os.path.exists(path):
@@ -69,7 +69,7 @@ def traffic_from_profiles(workload: str):
     if vals.get("kernel_source_sha256_16") != kernel_source_hash():
         return None
     try:
-        return float(vals["hbm_bytes_per_launch"])
+        return float(vals[key])
     except (KeyError, ValueError):
         return None
 
@@ -551,7 +551,7 @@ def main():
     bytes_stage = algorithmic_bytes_stage(order) * n_cell
     achieved = bytes_stage / (k1_ms * 1e-3) / 1e9 if k1_ms > 0 else None
     step_gbs = 3 * bytes_stage / (elapsed / args.steps) / 1e9
-    traffic = traffic_from_profiles(w["name"])
+    traffic = profile_value(w["name"], "hbm_bytes_per_launch")
     out = {
         "metric": METRIC if order == 5 else f"cell-updates/s per RK stage ({order}th-order, Euler)",
         "value": value,
@@ -576,7 +576,11 @@ def main():
                             "reconstruction") if diag["fallbacks"] else None,
                    "stage": "reconstruct + HLL flux + gather + RK update; dt once per step, "
                             "formed by the last stage's update"},
-        "roofline": {"bound": "fp64 issue", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        # the fraction is of HBM; what holds the kernel back is the issue of
+        # FP64 instructions (the share of SIMD cycles that start one)
+        "roofline": {"bound": "hbm", "limited_by": "fp64 issue",
+                     "issue_frac": profile_value(w["name"], "valu_issue_frac"),
+                     "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS if achieved else None,
                      "traffic": traffic,
                      "kernel": "k_reconstruct",

@@ -249,9 +249,10 @@ __device__ __forceinline__ void hll_vjp(const double uL[4], const double uR[4], 
 // order 5) and bound this kernel to HBM: 461 us per launch on 524,288 cells at
 // order 5 (5.7 TB/s).  N is symmetric (1.2 KB), and A_s follows from the
 // member's own central moments by a Taylor shift, a few multiply-adds per entry
-// from a record that the whole block shares: 310 us, bound by FP64 issue (65-73%
-// of the cycles) with memory at 3.5 TB/s.  At orders 3, 4, 6 (180,000 cells):
-// 73, 105, 270 us stored, 49, 69, 178 us like this.
+// from a record that the whole block shares: 285 to 315 us by state, bound by
+// vector issue (67% of the SIMDs' cycles: 3,140 instructions a tile, seven tenths
+// of them FP64) with memory at 3.5 TB/s.  At orders 3, 4, 6 (180,000 cells):
+// 73, 105, 270 us stored, 49, 65, 165 us like this.
 //
 // Precision: the normal matrix squares the condition of A, so the basis is
 // chosen to keep that small: moments in a frame that gives the block's
@@ -313,7 +314,10 @@ __device__ __forceinline__ unsigned list_offset(TENO_CONST BlockArgs& b, int k) 
 // go to lds + 16 l (4 l); lds is uniform.  The copies are counted with the
 // wavefront's other memory operations and are complete after lds_copy_wait.
 // In assembly, because the compiler waits for such a copy before any later LDS
-// read; nothing is returned in a register.
+// read; nothing is returned in a register.  m0 is named as clobbered because it is:
+// the compiler warns that it will not save a reserved register, and need not.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_copy16(const void* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                :: "s"(lds), "v"(src) : "m0", "memory");
@@ -322,6 +326,7 @@ __device__ __forceinline__ void lds_copy4(const void* src, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
                :: "s"(lds), "v"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // A uniform load through the scalar cache (of data that no kernel writes); the
 // copies' memory clobbers would otherwise turn it into a vector load.
 __device__ __forceinline__ int scalar_load(const int* p, int i) {
@@ -2287,7 +2292,9 @@ __device__ __forceinline__ void adj_rows(const CellView& cv, const Slots& slots,
   });
 }
 
-// The adjoint's: 72 against 78 us at order 4 with three (131,072 cells).
+// The adjoint's: three at order 4 too, 44.5 against 50.1 us where most cells keep
+// the large stencil alone (131,072 cells, random lines, which smooth out along a
+// rollout) and 64.0 against 73.8 us where few do (random states of every cell).
 constexpr int adj_waves(int p) { return p <= 4 ? 3 : 2; }
 
 template <int P, int NQ>

@@ -552,23 +552,23 @@ static uint32_t spread16(uint32_t x) {
 // matrix-free least squares: block member lists, geometry records and the
 // inverses of the normal matrices
 // ---------------------------------------------------------------------------
-// The operators a = M d of the least squares are never stored on the device:
-// with rows A_s (moments of the member about the target, in any basis) and
-// weights |V_s|, a = (sum_s |V_s|^2 A_s A_s^T)^-1 sum_s |V_s|^2 A_s d_s.  The
-// normal matrix squares the condition of the rows, so the basis is chosen to
-// be almost orthogonal over the stencil: the frame of a block whitens the
-// displacements of its stencils (also on stretched and sheared meshes), the
-// polynomials are Hermite's, and each stencil's are centred on its members'
-// mean (one-sided small stencils, stencils at a wall).  The matrices are formed
-// and inverted in extended precision and stored in FP64.  On jittered meshes
-// the face values of random data come out closer to 128 bits than with the
-// stored operators of the reference triangle's monomials (rms, orders 3-6:
-// x 0.3-0.02), and the rounding noise of their sums is x 0.7-1.9 of a
-// plain product M d (orders 3-6, boxes included; monomials about the target
-// would give x 2-55).  On graded meshes a few stencils, one-sided ones above
-// all, would lose digits that their operators keep (to 2.6e-7 against 1e-10 on
-// a sector of 4 rad with radii 1 : e^6): normal_bound finds those, and their
-// cells keep their operators.
+// The operators a = M d of the least squares are not stored (but for the cells
+// named below): with rows A_s (moments of the member about the target, in any
+// basis) and weights |V_s|, a = (sum_s |V_s|^2 A_s A_s^T)^-1 sum_s |V_s|^2 A_s
+// d_s.  The normal matrix squares the condition of the rows, so the basis is
+// chosen to be almost orthogonal over the stencil: the frame of a block
+// whitens the displacements of its stencils (also on stretched and sheared
+// meshes), the polynomials are Hermite's, and each stencil's are centred on
+// its members' mean (one-sided small stencils, stencils at a wall).  The
+// matrices are formed and inverted in extended precision and stored in FP64.
+// On jittered meshes the face values of random data come out closer to 128
+// bits than with the stored operators of the reference triangle's monomials
+// (rms, orders 3-6: x 0.3-0.02), and the rounding noise of their sums is x
+// 0.7-1.9 of a plain product M d (orders 3-6, boxes included; monomials about
+// the target would give x 2-55).  On graded meshes a few stencils, one-sided
+// ones above all, would lose digits that their operators keep (to 2.6e-7
+// against 1e-10 on a sector of 4 rad with radii 1 : e^6): normal_bound finds
+// those, and their cells keep their operators.
 typedef long double Ext;
 
 // E[H_a(x + X) H_b(y + Y)] for 0 <= a + b <= r from the central moments
